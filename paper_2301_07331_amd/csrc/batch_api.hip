@@ -572,9 +572,14 @@ int hlc_xmatch_batch(const hlc_job* jobs, int32_t njobs, const double* a_ra, con
   if (opts->capacity > 0 && (!out_pairs || (!(opts->flags & HLC_NO_SEP) && !out_sep_arcsec)))
     return HLC_E_INVAL;
   try {
-    return sort_output(
-        batch_impl(jobs, njobs, a_ra, a_dec, b_ra, b_dec, out_pairs, out_sep_arcsec, job_pair_count, opts),
-        out_pairs, out_sep_arcsec, opts, int64_t(1) << 31, int64_t(1) << 31);
+    const int st = batch_impl(jobs, njobs, a_ra, a_dec, b_ra, b_dec, out_pairs, out_sep_arcsec, job_pair_count, opts);
+    if (st != HLC_OK || !(opts->flags & HLC_SORTED)) return st;
+    int64_t na = 1, nb = 1;  // the indices lie below the jobs' last sources
+    for (int32_t j = 0; j < njobs; ++j) {
+      na = std::max(na, jobs[j].a_off + jobs[j].na);
+      nb = std::max(nb, jobs[j].b_off + jobs[j].nb);
+    }
+    return sort_output(st, out_pairs, out_sep_arcsec, opts, na, nb);
   } catch (const std::bad_alloc&) {
     return HLC_E_NOMEM;
   } catch (...) {

@@ -92,6 +92,35 @@ void launch_ranges(const uint32_t* keysA, const DevCount& na, const uint32_t* ki
                    const uint32_t* keysB, const uint32_t* zstartB, const int32_t* zmarg, const double* zdelta,
                    const Geom& g, GroupRanges* out, hipStream_t s);
 
+// ---- pair_order.hip --------------------------------------------------------
+// pairs (and separations, if sep) ordered by (a, b), a < na
+constexpr uint32_t PAIR_ORDER_LDS = 4096;  // pairs that one block orders
+struct PairRec {
+  uint32_t a, b;
+  double sep;
+};
+struct PairOrderSizes {
+  uint32_t K, chunks;  // buckets of a; chunks counted and scattered by a block each
+};
+struct PairOrderWs {
+  uint32_t *counts, *totals, *starts;  // K * chunks, K, K + 1
+  PairRec* rec;                        // n
+};
+PairOrderSizes pair_order_sizes(uint32_t n, uint64_t na);
+// n <= PAIR_ORDER_LDS, in place
+void launch_pair_order_block(uint2* pairs, double* sep, uint32_t n, hipStream_t s);
+// whether a bucket pass is the better way (else: sort_pairs)
+bool pair_order_fits(uint32_t n, const PairOrderSizes& z);
+// through one bucket pass. What *over (mapped host memory) then says:
+//   0: done; PAIR_ORDER_ROUNDS: buckets too large for a block are left to
+//   launch_pair_order_rounds; PAIR_ORDER_NONE: a bucket is far too large, the
+//   pairs stayed as they were
+constexpr unsigned long long PAIR_ORDER_NONE = 1, PAIR_ORDER_ROUNDS = 2;
+void launch_pair_order(uint2* pairs, double* sep, uint32_t n, uint64_t na, const PairOrderSizes& z,
+                       const PairOrderWs& w, unsigned long long* over, hipStream_t s);
+void launch_pair_order_rounds(uint2* pairs, double* sep, uint32_t n, const PairOrderSizes& z, const PairOrderWs& w,
+                              hipStream_t s);
+
 // ---- match.hip -------------------------------------------------------------
 // Output allocation. A single counter bumped by every wave serialises at the
 // memory side (device-scope atomics on one address: a few ns each), so the

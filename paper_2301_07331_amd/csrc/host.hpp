@@ -65,6 +65,8 @@ struct Device {
   unsigned long long* fmsg_dev = nullptr;
   unsigned long long fseq = 0;
 };
+// words of the mapped host memory beside the sample's five
+constexpr int FMSG_ORDER = 6;  // the pair ordering found a bucket too full
 
 extern Device g_dev[MAX_DEVICES];
 // statistics of the last call made on the calling thread

@@ -272,6 +272,42 @@ int sort_output(int st, hlc_pair* pairs, double* sep, const hlc_opts* o, int64_t
   HLC_CHECK(get_device(&dev));
   hipStream_t s = (hipStream_t)o->stream;
   const uint32_t m = (uint32_t)n;
+  uint2* out = reinterpret_cast<uint2*>(pairs);
+  auto done = [&]() -> int {
+    HLC_TRY(hipStreamSynchronize(s));
+    HLC_TRY(hipGetLastError());
+    return HLC_OK;
+  };
+  if (m <= PAIR_ORDER_LDS) {
+    launch_pair_order_block(out, sep, m, s);
+    return done();
+  }
+  // One bucket pass up to 47M pairs (fewer when there are few first indices:
+  // the mean of the buckets decides); the digit sort beyond that, or when a
+  // bucket turns out far too large (pairs crowded on few first indices).
+  const PairOrderSizes z = pair_order_sizes(m, (uint64_t)na);
+  if (pair_order_fits(m, z)) {
+    PairOrderWs w{};
+    auto lay = [&](Carve& c) {
+      w.counts = c.take<uint32_t>((size_t)z.K * z.chunks);
+      w.totals = c.take<uint32_t>(z.K);
+      w.starts = c.take<uint32_t>((size_t)z.K + 1);
+      w.rec = c.take<PairRec>(m);
+    };
+    Carve sz{nullptr};
+    lay(sz);
+    HLC_CHECK(ensure_ws(*dev, sz.off + 256));
+    Carve c{(char*)dev->ws};
+    lay(c);
+    launch_pair_order(out, sep, m, (uint64_t)na, z, w, dev->fmsg_dev + FMSG_ORDER, s);
+    HLC_CHECK(done());
+    const unsigned long long over = __atomic_load_n(&dev->fmsg_host[FMSG_ORDER], __ATOMIC_ACQUIRE);
+    if (over == 0ull) return HLC_OK;
+    if (over == PAIR_ORDER_ROUNDS) {
+      launch_pair_order_rounds(out, sep, m, z, w, s);
+      return done();
+    }
+  }
   uint32_t *keys = nullptr, *vals = nullptr;
   uint2* tp = nullptr;
   double* ts = nullptr;
@@ -288,10 +324,8 @@ int sort_output(int st, hlc_pair* pairs, double* sep, const hlc_opts* o, int64_t
   HLC_CHECK(ensure_ws(*dev, sz.off + 256));
   Carve c{(char*)dev->ws};
   lay(c);
-  sort_pairs(reinterpret_cast<uint2*>(pairs), sep, m, bits_for(na), bits_for(nb), keys, vals, tp, ts, sc, s);
-  HLC_TRY(hipStreamSynchronize(s));
-  HLC_TRY(hipGetLastError());
-  return HLC_OK;
+  sort_pairs(out, sep, m, bits_for(na), bits_for(nb), keys, vals, tp, ts, sc, s);
+  return done();
 }
 
 }  // namespace hlc

@@ -1,0 +1,105 @@
+"""HLC_SORTED at the edges of the pair ordering: one block in LDS (up to 4,096 pairs), the bucket pass (blocks of 2,048
+or 8,192 pairs), full bins (indices in dense clusters), buckets taken in rounds and buckets far too large (digit
+sort)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+SEP_TOL = 1e-9  # arcsec: the interface's bound on a separation
+
+
+def _sky(groups, rng):
+    """groups = [(sites, ka, kb)]: per site ka A sources at one point and kb (< 70,000) B sources a little north of it, each at
+    its own distance; sites 0.01 deg apart or more."""
+    a_dec, b_dec, a_ra, b_ra, b_off, site_a, site_b = [], [], [], [], [], [], []
+    site = 0
+    for sites, ka, kb in groups:
+        for _ in range(sites):
+            ra, dec = 0.25 + (site % 1400) * 0.25, -60.0 + (site // 1400) * 0.015625
+            off = (np.arange(kb) + 1) * 2.0 ** -28  # deg: 1.3e-5 arcsec steps, all below the radius
+            a_ra.append(np.full(ka, ra)); a_dec.append(np.full(ka, dec)); site_a.append(np.full(ka, site))
+            b_ra.append(np.full(kb, ra)); b_dec.append(dec + off); b_off.append(off * 3600.0)
+            site_b.append(np.full(kb, site))
+            site += 1
+    cat = np.concatenate
+    a = [cat(x) for x in (a_ra, a_dec, site_a)]
+    b = [cat(x) for x in (b_ra, b_dec, site_b, b_off)]
+    if rng is not None:
+        pa, pb = rng.permutation(len(a[0])), rng.permutation(len(b[0]))
+        a, b = [x[pa] for x in a], [x[pb] for x in b]
+    return a, b
+
+
+def _expected(a, b):
+    """(a, b, separation) of every same-site pair, ordered by (a, b)."""
+    order = np.argsort(b[2], kind="stable")
+    lo = np.searchsorted(b[2][order], a[2], "left")
+    hi = np.searchsorted(b[2][order], a[2], "right")
+    m = hi - lo
+    ia = np.repeat(np.arange(len(a[0])), m)
+    ib = order[np.repeat(lo, m) + np.arange(m.sum()) - np.repeat(np.cumsum(m) - m, m)]
+    k = np.lexsort((ib, ia))
+    return ia[k], ib[k], b[3][ib[k]]
+
+
+CASES = {
+    "one": [(1, 1, 1)],
+    "two": [(2, 1, 1)],
+    "wave": [(65, 1, 1)],
+    "block_full": [(4096, 1, 1)],
+    "block_full_dense": [(1, 64, 64)],
+    "buckets": [(4097, 1, 1)],
+    "buckets_dense": [(1, 70, 70)],
+    "buckets_many": [(70001, 1, 2)],
+    "bucket_per_source": [(3, 2, 3000)],
+    "too_few_sources": [(1, 1, 30000)],
+    "rounds": [(20000, 1, 1), (1, 1, 5000)],
+    "rounds_two_dense_sources": [(20000, 1, 1), (1, 2, 1500)],
+    "one_source_too_many": [(20000, 1, 1), (1, 1, 18000)],
+    "large_buckets": [(70000, 1, 20)],
+    "large_rounds": [(70000, 1, 20), (1, 3, 4000)],
+}
+
+
+@pytest.mark.parametrize("shuffled", [False, True])
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_pair_order(case, shuffled):
+    import torch
+    import paper_2301_07331_amd as hlc
+
+    a, b = _sky(CASES[case], np.random.default_rng(3) if shuffled else None)
+    ia, ib, sep = _expected(a, b)
+    n = len(ia)
+    t = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (a[0], a[1], b[0], b[1])]
+    for with_sep in (True, False):
+        pairs = torch.full((n + 3, 2), -7, dtype=torch.int32, device="cuda")
+        out = torch.full((n + 3,), -7.0, dtype=torch.float64, device="cuda")
+        flags = hlc.HLC_SORTED | (0 if with_sep else hlc.HLC_NO_SEP)
+        st, got = hlc.hlc_xmatch(*t, 1.0, pairs, out if with_sep else None, flags=flags)
+        assert (st, got) == (hlc.HLC_OK, n)
+        p = pairs.cpu().numpy()
+        assert np.array_equal(p[:n, 0], ia) and np.array_equal(p[:n, 1], ib)
+        assert (p[n:] == -7).all()  # nothing past the pairs
+        o = out.cpu().numpy()
+        assert (o[n:] == -7.0).all()
+        if with_sep:
+            assert np.abs(o[:n] - sep).max() <= SEP_TOL
+        else:
+            assert (o == -7.0).all()
+
+
+@pytest.mark.parametrize("njobs", [5000, 9001])
+def test_pair_order_repeated_pair(njobs):
+    """The same pair from every one of many overlapping jobs: equal keys, more than a block holds."""
+    import torch
+    import paper_2301_07331_amd as hlc
+
+    t = [torch.tensor([v], dtype=torch.float64, device="cuda") for v in (10.0, 20.0, 10.0, 20.0 + 2.0 ** -20)]
+    jobs = hlc.job_table([(0, 1, 0, 1, 1.0)] * njobs)
+    pairs = torch.full((njobs + 1, 2), -7, dtype=torch.int32, device="cuda")
+    sep = torch.full((njobs + 1,), -7.0, dtype=torch.float64, device="cuda")
+    st, n = hlc.hlc_xmatch_batch(jobs, *t, pairs, sep, None, flags=hlc.HLC_SORTED)
+    assert (st, n) == (hlc.HLC_OK, njobs)
+    assert (pairs[:n] == 0).all() and (pairs[n:] == -7).all() and (sep[n:] == -7.0).all()
+    assert (sep[:n] - 3600.0 * 2.0 ** -20).abs().max().item() <= SEP_TOL
