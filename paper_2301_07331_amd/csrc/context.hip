@@ -30,9 +30,9 @@ int get_device(Device** out, int* dev_id) {
     HLC_TRY(hipEventCreateWithFlags(&d.fork, hipEventDisableTiming));
     HLC_TRY(hipEventCreateWithFlags(&d.bsorted, hipEventDisableTiming));
     HLC_TRY(hipEventCreateWithFlags(&d.prepped, hipEventDisableTiming));
-    HLC_TRY(hipHostMalloc(&d.fmsg_host, 64, hipHostMallocMapped | hipHostMallocCoherent));
-    std::memset(d.fmsg_host, 0, 64);
-    HLC_TRY(hipHostGetDevicePointer((void**)&d.fmsg_dev, d.fmsg_host, 0));
+    HLC_TRY(hipHostMalloc(&d.msg, sizeof(HostMsg), hipHostMallocMapped | hipHostMallocCoherent));
+    std::memset(d.msg, 0, sizeof(HostMsg));
+    HLC_TRY(hipHostGetDevicePointer((void**)&d.msg_dev, d.msg, 0));
     d.init = true;
   }
   *out = &d;
@@ -155,7 +155,7 @@ void hlc_shutdown(void) {
     if (d.ws) (void)hipFree(d.ws);
     if (d.cnt) (void)hipFree(d.cnt);
     if (d.cnt_host) (void)hipHostFree(d.cnt_host);
-    if (d.fmsg_host) (void)hipHostFree(d.fmsg_host);
+    if (d.msg) (void)hipHostFree(d.msg);
     for (auto& e : d.ev)
       if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : {d.fork, d.bsorted, d.prepped})

@@ -97,13 +97,42 @@ Geom make_geom(double r_arcsec, double h_as, int64_t na, int64_t nb, int ra_bits
   return g;
 }
 
-// Launches the footprint sample of a call; returns its sequence number for
-// frame_finish.
-unsigned long long frame_sample(Device& dev, const double* a_ra, const double* a_dec, int64_t na,
-                                const double* b_ra, const double* b_dec, int64_t nb, hipStream_t s) {
+FrameQuery frame_begin(Device& dev, const double* a_ra, const double* a_dec, int64_t na, const double* b_ra,
+                       const double* b_dec, int64_t nb, hipStream_t s) {
+  FrameQuery q{++dev.fseq, 1u, !dev.last_full};
+  if (q.exact)
+    q.slots = launch_extent(a_ra, a_dec, (uint32_t)na, b_ra, b_dec, (uint32_t)nb, dev.msg_dev->ext, q.seq, s);
+  else
+    launch_extent_sample(a_ra, a_dec, (uint32_t)na, b_ra, b_dec, (uint32_t)nb, dev.msg_dev->ext, q.seq, s);
+  return q;
+}
+
+// The slots' box once every slot carries seq: polled in host memory (no stream
+// round trip); a result that does not show up falls back to a stream
+// synchronisation.
+static int wait_box(Device& dev, unsigned long long seq, uint32_t slots, hipStream_t s, Box* out) {
+  const auto t0 = std::chrono::steady_clock::now();
+  bool synced = false;
+  for (uint32_t i = 0; i < slots; ++i) {
+    while (__atomic_load_n(&dev.msg->ext[i].seq, __ATOMIC_ACQUIRE) != seq) {
+      if (synced) return HLC_E_DEVICE;
+      if (std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(50)) {
+        HLC_TRY(hipStreamSynchronize(s));
+        HLC_TRY(hipGetLastError());
+        synced = true;
+      }
+    }
+  }
+  *out = read_box(dev.msg->ext, slots);
+  return HLC_OK;
+}
+
+int exact_box(Device& dev, const double* a_ra, const double* a_dec, int64_t na, const double* b_ra,
+              const double* b_dec, int64_t nb, hipStream_t s, Box* out) {
   const unsigned long long seq = ++dev.fseq;
-  launch_extent_sample(a_ra, a_dec, (uint32_t)na, b_ra, b_dec, (uint32_t)nb, dev.cnt, dev.fmsg_dev, seq, s);
-  return seq;
+  const uint32_t slots =
+      launch_extent(a_ra, a_dec, (uint32_t)na, b_ra, b_dec, (uint32_t)nb, dev.msg_dev->ext, seq, s);
+  return wait_box(dev, seq, slots, s, out);
 }
 
 bool quarter_sky(const Box& b) {
@@ -126,36 +155,14 @@ Frame frame_of_box(const Box& b) {
   return f;
 }
 
-int frame_finish(Device& dev, unsigned long long seq, const double* a_ra, const double* a_dec, int64_t na,
+int frame_finish(Device& dev, FrameQuery q, const double* a_ra, const double* a_dec, int64_t na,
                  const double* b_ra, const double* b_dec, int64_t nb, hipStream_t s, Frame* out) {
   *out = Frame{};
-  Counters* hc = dev.cnt_host;
-  auto read_ext = [&]() -> int {
-    HLC_TRY(hipMemcpyAsync(hc->ext, dev.cnt->ext, sizeof(hc->ext), hipMemcpyDeviceToHost, s));
-    HLC_TRY(hipStreamSynchronize(s));
-    return HLC_OK;
-  };
-  auto box = [&]() { return read_box(*hc); };
-  // the sample's result is polled in host memory (no stream round trip); a
-  // result that does not show up falls back to a stream synchronisation
-  {
-    volatile unsigned long long* msg = dev.fmsg_host;
-    const auto t0 = std::chrono::steady_clock::now();
-    while (__atomic_load_n(&dev.fmsg_host[4], __ATOMIC_ACQUIRE) != seq) {
-      if (std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(50)) {
-        HLC_TRY(hipStreamSynchronize(s));
-        HLC_TRY(hipGetLastError());
-        if (__atomic_load_n(&dev.fmsg_host[4], __ATOMIC_ACQUIRE) != seq) return HLC_E_DEVICE;
-      }
-    }
-    for (int k = 0; k < 4; ++k) hc->ext[k] = msg[k];
-  }
-  Box b = box();
+  Box b;
+  HLC_CHECK(wait_box(dev, q.seq, q.slots, s, &b));
   if (!b.any || quarter_sky(b)) return HLC_OK;
-  launch_extent(a_ra, a_dec, (uint32_t)na, dev.cnt, s);
-  launch_extent(b_ra, b_dec, (uint32_t)nb, dev.cnt, s);
-  HLC_CHECK(read_ext());
-  *out = frame_of_box(box());
+  if (!q.exact) HLC_CHECK(exact_box(dev, a_ra, a_dec, na, b_ra, b_dec, nb, s, &b));
+  *out = frame_of_box(b);
   return HLC_OK;
 }
 

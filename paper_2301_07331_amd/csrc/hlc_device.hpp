@@ -85,9 +85,6 @@ struct Counters {
   unsigned long long aux[2];      // entry counts of multi-entry keygens (A, B)
   unsigned long long region_max;  // largest pair-region fill (compaction)
   unsigned long long cand_max;    // largest candidate-region fill
-  // data footprint, each as a max of order-preserving codes of non-negative
-  // doubles: ~code(dec + 90), code(dec + 90), ~code(ra), code(ra)
-  unsigned long long ext[4];
 };
 
 struct Rec64 {      // FP64 working record (32 B)

@@ -58,13 +58,20 @@ void radix_sort(uint32_t* keys, uint32_t* vals, const DevCount& n, int key_bits,
                 hipStream_t s, bool from_alt = false, int lo_bit = 0, uint32_t hist_done = 0,
                 uint32_t iota = 0);
 
-// footprint of the valid sources into Counters::ext (max-combined): a
-// sample of at most 2 x 4096 sources (overwrites; also written to msg[0..3]
-// in mapped host memory, then msg[4] = seq), or every source (combines)
+// Footprint of the valid sources: each value a max of order-preserving codes
+// of non-negative doubles, ~code(dec + 90), code(dec + 90), ~code(ra),
+// code(ra); one slot per block, combined by the host. Slots in mapped host
+// memory get `seq` after their values (0: none).
+constexpr uint32_t EXTENT_SLOTS = 256;  // most blocks of the passes below
+struct ExtentSlot {
+  unsigned long long v[4], seq, pad_[3];
+};
+// a sample of at most 2 x 4096 sources into one slot
 void launch_extent_sample(const double* ra1, const double* dec1, uint32_t n1, const double* ra2, const double* dec2,
-                          uint32_t n2, Counters* cnt, unsigned long long* msg, unsigned long long seq,
-                          hipStream_t s);
-void launch_extent(const double* ra, const double* dec, uint32_t n, Counters* cnt, hipStream_t s);
+                          uint32_t n2, ExtentSlot* out, unsigned long long seq, hipStream_t s);
+// every source; returns the number of slots filled
+uint32_t launch_extent(const double* ra1, const double* dec1, uint32_t n1, const double* ra2, const double* dec2,
+                       uint32_t n2, ExtentSlot* out, unsigned long long seq, hipStream_t s);
 void launch_zone_tables(const Geom& g, int32_t* zmarg, double* zdelta, hipStream_t s);
 void launch_zone_starts(const uint32_t* keys, const DevCount& n, const Geom& g, uint32_t* zstart,
                         hipStream_t s);
@@ -287,10 +294,12 @@ void launch_cand(const MatchArgs& a, const OutArgs& o, bool fp32, hipStream_t s)
 void launch_certify(const double* a_ra, const double* a_dec, const double* b_ra,
                     const double* b_dec, double r_arcsec, double H_lo, double H_hi,
                     const Radii& rad, const OutArgs& o, hipStream_t s);
-// codes (order-preserving) of the largest error of each side; err bit 8 on a
-// negative or non-finite error
-void launch_err_max(const double* err, uint32_t n, unsigned long long* out_code, Counters* cnt,
-                    hipStream_t s);
+// codes (bit patterns) of the largest error of each side, a pair of words per
+// block; ERR_BAD (above every valid code) for a negative or non-finite error;
+// returns the number of blocks
+constexpr unsigned long long ERR_BAD = ~0ull;
+uint32_t launch_err_max(const double* e1, uint32_t n1, const double* e2, uint32_t n2, unsigned long long* out,
+                        hipStream_t s);
 
 // paper-scheme emulation: up to five (pixel, index) entries per record,
 // appended after the counter *count (device)

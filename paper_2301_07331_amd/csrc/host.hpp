@@ -29,6 +29,13 @@ constexpr double ETA64 = 4e-15;  // bound on |chord_fp64 - chord| (unit sphere)
 // ---------------------------------------------------------------------------
 // per-device context (context.hip)
 // ---------------------------------------------------------------------------
+// Written by kernels, read by the host.
+struct HostMsg {
+  ExtentSlot ext[EXTENT_SLOTS];              // the footprint passes' slots (polled)
+  unsigned long long err[2 * EXTENT_SLOTS];  // the largest error radii
+  unsigned long long order;                  // what the pair ordering left to do
+};
+
 struct Device {
   bool init = false;
   void* ws = nullptr;
@@ -59,14 +66,11 @@ struct Device {
   double cand_per_b = 0.0;
   int ncu = 0;  // compute units (persistent grids)
   bool last_full = true;  // the last call's frame was the whole sphere
-  // the footprint sample's result, written by the kernel into mapped host
-  // memory (4 values, then the call's sequence number) and polled
-  unsigned long long* fmsg_host = nullptr;
-  unsigned long long* fmsg_dev = nullptr;
+  // mapped host memory: what kernels tell the host without a copy
+  HostMsg* msg = nullptr;
+  HostMsg* msg_dev = nullptr;  // its device address
   unsigned long long fseq = 0;
 };
-// words of the mapped host memory beside the sample's five
-constexpr int FMSG_ORDER = 6;  // the pair ordering found a bucket too full
 
 extern Device g_dev[MAX_DEVICES];
 // statistics of the last call made on the calling thread
@@ -157,23 +161,36 @@ struct Box {
   bool any;
   double dlo, dhi, rlo, rhi;
 };
-inline Box read_box(const Counters& h) {
+inline Box read_box(const ExtentSlot* slots, uint32_t n) {
+  unsigned long long v[4] = {0ull, 0ull, 0ull, 0ull};
+  for (uint32_t i = 0; i < n; ++i)
+    for (int k = 0; k < 4; ++k) v[k] = std::max(v[k], slots[i].v[k]);
   Box b;
-  b.any = h.ext[1] != 0ull;
-  b.dlo = ext_value(~h.ext[0]) - 90.0;
-  b.dhi = ext_value(h.ext[1]) - 90.0;
-  b.rlo = ext_value(~h.ext[2]);
-  b.rhi = ext_value(h.ext[3]);
+  b.any = v[1] != 0ull;
+  b.dlo = ext_value(~v[0]) - 90.0;
+  b.dhi = ext_value(v[1]) - 90.0;
+  b.rlo = ext_value(~v[2]);
+  b.rhi = ext_value(v[3]);
   return b;
 }
 
-// The frame of a call's data: a sample of both catalogues first; where its
-// box covers over a quarter of the sphere the whole sphere is the frame,
-// otherwise one pass over every source gives the exact box.
-unsigned long long frame_sample(Device& dev, const double* a_ra, const double* a_dec, int64_t na,
-                                const double* b_ra, const double* b_dec, int64_t nb, hipStream_t s);
-int frame_finish(Device& dev, unsigned long long seq, const double* a_ra, const double* a_dec, int64_t na,
+// The frame of a call's data. When the last call's frame was the whole sphere,
+// a sample of both catalogues first: where its box covers over a quarter of
+// the sphere the whole sphere is the frame, otherwise one pass over every
+// source gives the exact box. After a call with a smaller frame that pass runs
+// at once (a sample would only add a round trip).
+struct FrameQuery {
+  unsigned long long seq;
+  uint32_t slots;
+  bool exact;
+};
+FrameQuery frame_begin(Device& dev, const double* a_ra, const double* a_dec, int64_t na, const double* b_ra,
+                       const double* b_dec, int64_t nb, hipStream_t s);
+int frame_finish(Device& dev, FrameQuery q, const double* a_ra, const double* a_dec, int64_t na,
                  const double* b_ra, const double* b_dec, int64_t nb, hipStream_t s, Frame* out);
+// the exact box of every valid source of both catalogues
+int exact_box(Device& dev, const double* a_ra, const double* a_dec, int64_t na, const double* b_ra,
+              const double* b_dec, int64_t nb, hipStream_t s, Box* out);
 // the box covers over a quarter of the sphere (the whole sphere is the frame)
 bool quarter_sky(const Box& b);
 // the frame of an exact box of every valid source (a small margin added)

@@ -26,7 +26,8 @@ __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
 struct ScratchDev {
   bool init = false;
   unsigned char* base = nullptr;  // device address of `scratch` on this device
-  Counters host_cnt;              // host copy of the counters (plain memory)
+  Counters host_cnt;              // host copies (plain memory): the counters,
+  ExtentSlot host_ext[EXTENT_SLOTS];  // the footprint slots
   uint64_t hint_stage = 0, hint_cand = 0;
 };
 ScratchDev g_scratch[MAX_DEVICES];
@@ -103,11 +104,12 @@ int noalloc_impl(const double* a_ra, const double* a_dec, int64_t na, const doub
   }
   // the frame: the exact box of every source (the whole sphere when it
   // covers over a quarter of it)
-  launch_zero_counters(ctx.cnt, s);
-  launch_extent(a_ra, a_dec, (uint32_t)na, ctx.cnt, s);
-  launch_extent(b_ra, b_dec, (uint32_t)nb, ctx.cnt, s);
-  HLC_CHECK(read_counters(ctx, s, false));
-  const Box box = read_box(*ctx.cnt_host);
+  ExtentSlot* ext = static_cast<ExtentSlot*>(ctx.ws);
+  const uint32_t slots = launch_extent(a_ra, a_dec, (uint32_t)na, b_ra, b_dec, (uint32_t)nb, ext, 0ull, s);
+  HLC_TRY(hipMemcpyAsync(sd->host_ext, ext, slots * sizeof(ExtentSlot), hipMemcpyDeviceToHost, s));
+  HLC_TRY(hipStreamSynchronize(s));
+  HLC_TRY(hipGetLastError());
+  const Box box = read_box(sd->host_ext, slots);
   const Frame f = (!box.any || quarter_sky(box)) ? Frame{} : frame_of_box(box);
   Geom g = make_geom(r_arcsec, tuned_height(o), na, nb, tuned_bins(o), f);
   g.frac_sorted = tuned_fraction_sort(o) ? 1 : 0;

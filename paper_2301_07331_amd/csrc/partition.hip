@@ -851,22 +851,38 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ key
   out[grp] = R;
 }
 
-// largest error radius (order-preserving code of a non-negative double is its
-// bit pattern); bit 8 of err flags a negative or non-finite value
-__global__ __launch_bounds__(256) void k_err_max(const double* __restrict__ err, uint32_t n,
-                                                 unsigned long long* __restrict__ out, Counters* cnt) {
-  uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  unsigned long long c = 0ull;
-  if (i < n) {
-    const double e = err[i];
-    if (e >= 0.0 && e <= 1.0e300) c = (unsigned long long)__double_as_longlong(e);
-    else atomicOr(&cnt->err, 8u);
+// Largest error radius of each side (order-preserving code of a non-negative
+// double is its bit pattern), ERR_BAD for a negative or non-finite one: one
+// code per block and side, combined by the host, which needs them anyway. One
+// atomic per wave on one word took 180 us for a million radii (11 ns each, in
+// turn); both sides now take 6 us, bound by the loads.
+__global__ __launch_bounds__(256) void k_err_max(const double* __restrict__ e1, uint32_t n1,
+                                                 const double* __restrict__ e2, uint32_t n2,
+                                                 unsigned long long* out) {
+  __shared__ unsigned long long s_m[4];
+  for (int side = 0; side < 2; ++side) {
+    const double* __restrict__ err = side ? e2 : e1;
+    const uint32_t n = side ? n2 : n1, step = gridDim.x * 256u;
+    unsigned long long c = 0ull;
+#pragma unroll 8
+    for (uint64_t i = (uint64_t)blockIdx.x * 256u + threadIdx.x; i < n; i += step) {
+      const double e = err[i];
+      const unsigned long long v =
+          (e >= 0.0 && e <= 1.0e300) ? (unsigned long long)__double_as_longlong(e + 0.0) : ERR_BAD;
+      c = v > c ? v : c;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      const unsigned long long o = __shfl_xor(c, off);
+      c = o > c ? o : c;
+    }
+    if ((threadIdx.x & 63u) == 0) s_m[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int k = 1; k < 4; ++k) c = s_m[k] > c ? s_m[k] : c;
+      out[2u * blockIdx.x + (uint32_t)side] = c;
+    }
+    __syncthreads();
   }
-  for (int off = 32; off > 0; off >>= 1) {
-    unsigned long long o = __shfl_xor(c, off);
-    c = o > c ? o : c;
-  }
-  if ((threadIdx.x & 63) == 0 && c) atomicMax(out, c);
 }
 
 // ---------------------------------------------------------------------------
@@ -981,11 +997,10 @@ __device__ inline unsigned long long ord_code(double v) {  // v >= 0
   return (unsigned long long)__double_as_longlong(v);
 }
 
-// Block-wide max of e[4] into cnt->ext: atomically (several blocks), or
-// stored (one block; then also mirrored to msg[0..3] in host memory,
-// followed by msg[4] = seq once the four values are visible there).
-__device__ inline void ext_reduce(unsigned long long e[4], Counters* cnt, bool block_level,
-                                  unsigned long long* msg = nullptr, unsigned long long seq = 0ull) {
+// Block-wide max of e[4] into one slot, then, where the slot lies in mapped
+// host memory and is polled, the call's sequence number once the four values
+// are visible there.
+__device__ inline void ext_reduce(unsigned long long e[4], ExtentSlot* out, unsigned long long seq) {
 #pragma unroll
   for (int k = 0; k < 4; ++k)
     for (int d = 32; d > 0; d >>= 1) {
@@ -998,20 +1013,14 @@ __device__ inline void ext_reduce(unsigned long long e[4], Counters* cnt, bool b
     for (int k = 0; k < 4; ++k) s_e[w][k] = e[k];
   __syncthreads();
   if (threadIdx.x == 0) {
-    unsigned long long m[4];
     for (int k = 0; k < 4; ++k) {
-      m[k] = 0ull;
-      for (uint32_t u = 0; u < (blockDim.x >> 6); ++u) m[k] = s_e[u][k] > m[k] ? s_e[u][k] : m[k];
+      unsigned long long m = 0ull;
+      for (uint32_t u = 0; u < (blockDim.x >> 6); ++u) m = s_e[u][k] > m ? s_e[u][k] : m;
+      out->v[k] = m;
     }
-    if (block_level) {
-      for (int k = 0; k < 4; ++k) atomicMax(&cnt->ext[k], m[k]);
-    } else {
-      for (int k = 0; k < 4; ++k) cnt->ext[k] = m[k];
-      if (msg) {
-        for (int k = 0; k < 4; ++k) msg[k] = m[k];
-        __threadfence_system();
-        msg[4] = seq;
-      }
+    if (seq) {
+      __threadfence_system();
+      *(volatile unsigned long long*)&out->seq = seq;
     }
   }
 }
@@ -1037,8 +1046,8 @@ __device__ inline uint32_t sample_index(uint32_t run, uint32_t lane, uint32_t n)
 __global__ __launch_bounds__(1024) void k_extent_sample(const double* __restrict__ ra1,
                                                         const double* __restrict__ dec1, uint32_t n1,
                                                         const double* __restrict__ ra2,
-                                                        const double* __restrict__ dec2, uint32_t n2, Counters* cnt,
-                                                        unsigned long long* msg, unsigned long long seq) {
+                                                        const double* __restrict__ dec2, uint32_t n2,
+                                                        ExtentSlot* out, unsigned long long seq) {
   constexpr int PER = 4;  // runs per wave and catalogue (16 waves x 4 = 64 runs)
   const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
   double a[2 * PER], d[2 * PER];
@@ -1054,16 +1063,37 @@ __global__ __launch_bounds__(1024) void k_extent_sample(const double* __restrict
   unsigned long long e[4] = {0ull, 0ull, 0ull, 0ull};
 #pragma unroll
   for (int j = 0; j < 2 * PER; ++j) ext_add(e, a[j], d[j]);
-  ext_reduce(e, cnt, false, msg, seq);
+  ext_reduce(e, out, seq);
 }
 
-// Every source; one atomic per value and block.
-__global__ __launch_bounds__(256) void k_extent(const double* __restrict__ ra, const double* __restrict__ dec,
-                                                uint32_t n, Counters* cnt) {
+// Every source of both catalogues, a slot per block (combined by the host).
+// Eight loads of each coordinate in flight: a million sources a side take
+// 8 us; 64 dependent trips of few blocks took 40 us a side.
+constexpr uint32_t EXT_THREADS = 512, EXT_PER = 8;
+__global__ __launch_bounds__(EXT_THREADS) void k_extent(const double* __restrict__ ra1,
+                                                        const double* __restrict__ dec1, uint32_t n1,
+                                                        const double* __restrict__ ra2,
+                                                        const double* __restrict__ dec2, uint32_t n2,
+                                                        ExtentSlot* out, unsigned long long seq) {
   unsigned long long e[4] = {0ull, 0ull, 0ull, 0ull};
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    ext_add(e, ra[i], dec[i]);
-  ext_reduce(e, cnt, true);
+  for (int side = 0; side < 2; ++side) {
+    const double* __restrict__ ra = side ? ra2 : ra1;
+    const double* __restrict__ dec = side ? dec2 : dec1;
+    const uint32_t n = side ? n2 : n1;
+    for (uint64_t b = (uint64_t)blockIdx.x * EXT_THREADS * EXT_PER; b < n;
+         b += (uint64_t)gridDim.x * EXT_THREADS * EXT_PER) {
+      double a[EXT_PER], d[EXT_PER];
+#pragma unroll
+      for (uint32_t j = 0; j < EXT_PER; ++j) {
+        const uint64_t i = b + j * EXT_THREADS + threadIdx.x;
+        a[j] = i < n ? ra[i] : -1.0;  // (-1: not a position)
+        d[j] = i < n ? dec[i] : 0.0;
+      }
+#pragma unroll
+      for (uint32_t j = 0; j < EXT_PER; ++j) ext_add(e, a[j], d[j]);
+    }
+  }
+  ext_reduce(e, out + blockIdx.x, seq);
 }
 
 }  // namespace
@@ -1090,10 +1120,11 @@ void launch_equal_ranges(const uint32_t* keysA, const DevCount& na, const uint32
   k_equal_ranges<<<cdiv(ng, 256), 256, 0, s>>>(keysA, na, lb, keysB, nb, out);
 }
 
-void launch_err_max(const double* err, uint32_t n, unsigned long long* out_code, Counters* cnt,
-                    hipStream_t s) {
-  if (n == 0) return;
-  k_err_max<<<cdiv(n, 256), 256, 0, s>>>(err, n, out_code, cnt);
+uint32_t launch_err_max(const double* e1, uint32_t n1, const double* e2, uint32_t n2, unsigned long long* out,
+                        hipStream_t s) {
+  const uint32_t blocks = std::min<uint32_t>(EXTENT_SLOTS, std::max(1u, cdiv(std::max(n1, n2), 256 * 8)));
+  k_err_max<<<blocks, 256, 0, s>>>(e1, n1, e2, n2, out);
+  return blocks;
 }
 
 void launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t s) {
@@ -1185,14 +1216,16 @@ void sort_pairs(uint2* pairs, double* sep, uint32_t n, int bits_a, int bits_b, u
 }
 
 void launch_extent_sample(const double* ra1, const double* dec1, uint32_t n1, const double* ra2, const double* dec2,
-                          uint32_t n2, Counters* cnt, unsigned long long* msg, unsigned long long seq,
-                          hipStream_t s) {
-  k_extent_sample<<<1, 1024, 0, s>>>(ra1, dec1, n1, ra2, dec2, n2, cnt, msg, seq);
+                          uint32_t n2, ExtentSlot* out, unsigned long long seq, hipStream_t s) {
+  k_extent_sample<<<1, 1024, 0, s>>>(ra1, dec1, n1, ra2, dec2, n2, out, seq);
 }
 
-void launch_extent(const double* ra, const double* dec, uint32_t n, Counters* cnt, hipStream_t s) {
-  if (n == 0) return;
-  k_extent<<<std::min<uint32_t>(1024, cdiv(n, 256 * 64)), 256, 0, s>>>(ra, dec, n, cnt);
+uint32_t launch_extent(const double* ra1, const double* dec1, uint32_t n1, const double* ra2, const double* dec2,
+                       uint32_t n2, ExtentSlot* out, unsigned long long seq, hipStream_t s) {
+  const uint32_t blocks =
+      std::min<uint32_t>(EXTENT_SLOTS, std::max(1u, cdiv(std::max(n1, n2), EXT_THREADS * EXT_PER)));
+  k_extent<<<blocks, EXT_THREADS, 0, s>>>(ra1, dec1, n1, ra2, dec2, n2, out, seq);
+  return blocks;
 }
 
 void launch_zone_tables(const Geom& g, int32_t* zmarg, double* zdelta, hipStream_t s) {

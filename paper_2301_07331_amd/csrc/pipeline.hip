@@ -299,9 +299,9 @@ int sort_output(int st, hlc_pair* pairs, double* sep, const hlc_opts* o, int64_t
     HLC_CHECK(ensure_ws(*dev, sz.off + 256));
     Carve c{(char*)dev->ws};
     lay(c);
-    launch_pair_order(out, sep, m, (uint64_t)na, z, w, dev->fmsg_dev + FMSG_ORDER, s);
+    launch_pair_order(out, sep, m, (uint64_t)na, z, w, &dev->msg_dev->order, s);
     HLC_CHECK(done());
-    const unsigned long long over = __atomic_load_n(&dev->fmsg_host[FMSG_ORDER], __ATOMIC_ACQUIRE);
+    const unsigned long long over = __atomic_load_n(&dev->msg->order, __ATOMIC_ACQUIRE);
     if (over == 0ull) return HLC_OK;
     if (over == PAIR_ORDER_ROUNDS) {
       launch_pair_order_rounds(out, sep, m, z, w, s);

@@ -334,10 +334,9 @@ int stream_impl(const double* a_ra_h, const double* a_dec_h, int64_t na, const d
   HLC_TRY(hipStreamWaitEvent(s, sc.ev_copy, 0));
 
   // 2. the frame from B's footprint; B partitioned once
-  launch_zero_counters(dev->cnt, s);
-  launch_extent(B_ra, B_dec, nB, dev->cnt, s);
-  HLC_CHECK(read_counters(*dev, s, false));
-  const Frame f = frame_around(read_box(*dev->cnt_host), r_arcsec);
+  Box box;
+  HLC_CHECK(exact_box(*dev, nullptr, nullptr, 0, B_ra, B_dec, nB, s, &box));
+  const Frame f = frame_around(box, r_arcsec);
   const Geom g = make_geom(r_arcsec, tuned_height(o), na, nb, tuned_bins(o), f);
   launch_zero_counters(dev->cnt, s);
   HLC_TRY(hipEventRecord(sc.ev_t0, s));

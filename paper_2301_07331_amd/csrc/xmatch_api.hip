@@ -24,7 +24,7 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   const bool self = (o->flags & HLC_SELF) != 0;
   if (prof) HLC_TRY(hipEventRecord(dev->ev[0], s));
   const int64_t na_frame = self ? 0 : na;
-  const unsigned long long seq = frame_sample(*dev, a_ra, a_dec, na_frame, b_ra, b_dec, nb, s);
+  const FrameQuery fq = frame_begin(*dev, a_ra, a_dec, na_frame, b_ra, b_dec, nb, s);
   const uint32_t nB = (uint32_t)nb;
   // self-match: A's entries are B's (halo copies included)
   const uint32_t nA = self ? 2 * nB : (uint32_t)na;
@@ -57,7 +57,7 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   // buffers do not depend on the frame). They are kept if the sample
   // confirms the frame, else computed again.
   bool spec = false;
-  if (!self && dev->last_full) {
+  if (!self && !fq.exact) {
     Carve sizing{nullptr};
     lay(sizing);
     if (sizing.off + 256 <= dev->ws_bytes) {
@@ -76,7 +76,7 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
     }
   }
   Frame f;
-  HLC_CHECK(frame_finish(*dev, seq, a_ra, a_dec, na_frame, b_ra, b_dec, nb, s, &f));
+  HLC_CHECK(frame_finish(*dev, fq, a_ra, a_dec, na_frame, b_ra, b_dec, nb, s, &f));
   dev->last_full = is_full(f);
   const bool keep = spec && dev->last_full;  // the speculative keys stand
   g = make_geom(r_arcsec, tuned_height(o), na, nb, tuned_bins(o), f);
@@ -199,19 +199,18 @@ int hlc_xmatch_radii(const double* a_ra, const double* a_dec, const double* a_er
     Device* dev = nullptr;
     HLC_CHECK(get_device(&dev));
     hipStream_t s = (hipStream_t)opts->stream;
-    HLC_CHECK(ensure_ws(*dev, 1024));
-    unsigned long long* codes = (unsigned long long*)dev->ws;
-    launch_zero_counters(dev->cnt, s);
-    launch_zero_u64(codes, 2, s);
-    launch_err_max(a_err, (uint32_t)na, codes, dev->cnt, s);
-    launch_err_max(b_err, (uint32_t)nb, codes + 1, dev->cnt, s);
-    unsigned long long h_codes[2];
-    HLC_TRY(hipMemcpyAsync(h_codes, codes, sizeof h_codes, hipMemcpyDeviceToHost, s));
-    HLC_CHECK(read_counters(*dev, s, false));
-    if (dev->cnt_host->err) return HLC_E_INVAL;
+    const uint32_t nc = launch_err_max(a_err, (uint32_t)na, b_err, (uint32_t)nb, dev->msg_dev->err, s);
+    HLC_TRY(hipStreamSynchronize(s));
+    HLC_TRY(hipGetLastError());
+    unsigned long long ca = 0ull, cb = 0ull;
+    for (uint32_t i = 0; i < nc; ++i) {
+      ca = std::max(ca, dev->msg->err[2 * i]);
+      cb = std::max(cb, dev->msg->err[2 * i + 1]);
+    }
+    if (ca == ERR_BAD || cb == ERR_BAD) return HLC_E_INVAL;
     double ea, eb;
-    std::memcpy(&ea, &h_codes[0], 8);
-    std::memcpy(&eb, &h_codes[1], 8);
+    std::memcpy(&ea, &ca, 8);
+    std::memcpy(&eb, &cb, 8);
     double rmax = k_sigma * std::sqrt(ea * ea + eb * eb) * (1.0 + 1e-12);
     if (!(rmax <= 3600.0)) return HLC_E_INVAL;
     // all errors zero: only identical positions match; any positive filter
