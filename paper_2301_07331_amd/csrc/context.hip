@@ -7,7 +7,9 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
+#include <utility>
 
 #include "host.hpp"
 
@@ -53,10 +55,72 @@ int dev_alloc(void** p, size_t bytes) {
   hipError_t e = hipMalloc(p, bytes);
   if (e != hipSuccess) {
     (void)hipGetLastError();
+    // once more with the current device's pool given back
+    int dev = 0;
+    if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < MAX_DEVICES) pool_release(g_dev[dev]);
+    e = hipMalloc(p, bytes);
+  }
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
     *p = nullptr;
     return HLC_E_NOMEM;
   }
   return HLC_OK;
+}
+
+static std::mutex g_pool_lock;
+
+int pool_take(Device& d, size_t bytes, void** p, size_t* got) {
+  if (alloc_fails(bytes)) return HLC_E_NOMEM;
+  {
+    std::lock_guard<std::mutex> hold(g_pool_lock);
+    PoolBlock* best = nullptr;
+    for (PoolBlock& b : d.pool)
+      if (b.p && b.bytes >= bytes && b.bytes / 2 <= bytes && (!best || b.bytes < best->bytes)) best = &b;
+    if (best) {
+      *p = best->p;
+      *got = best->bytes;
+      *best = PoolBlock();
+      return HLC_OK;
+    }
+  }
+  *got = bytes;
+  return dev_alloc(p, bytes);
+}
+
+// (the block freed longest ago makes room: a loop's own block stays whatever
+// other programs' parts left here)
+void pool_put(Device& d, void* p, size_t bytes) {
+  void* out[POOL_BLOCKS + 1] = {};
+  {
+    std::lock_guard<std::mutex> hold(g_pool_lock);
+    // pool[0] is the newest
+    int k = POOL_BLOCKS - 1;
+    out[k] = d.pool[k].p;
+    for (; k > 0; --k) d.pool[k] = d.pool[k - 1];
+    d.pool[0] = PoolBlock{p, bytes};
+    size_t kept = 0;
+    for (int i = 0; i < POOL_BLOCKS; ++i) {
+      kept += d.pool[i].bytes;
+      if (kept > POOL_BYTES) {
+        kept -= d.pool[i].bytes;
+        out[i == POOL_BLOCKS - 1 ? POOL_BLOCKS : i] = d.pool[i].p;
+        d.pool[i] = PoolBlock();
+      }
+    }
+  }
+  for (void* q : out)
+    if (q) (void)hipFree(q);
+}
+
+void pool_release(Device& d) {
+  PoolBlock all[POOL_BLOCKS];
+  {
+    std::lock_guard<std::mutex> hold(g_pool_lock);
+    for (int k = 0; k < POOL_BLOCKS; ++k) std::swap(all[k], d.pool[k]);
+  }
+  for (PoolBlock& b : all)
+    if (b.p) (void)hipFree(b.p);
 }
 
 
@@ -151,6 +215,7 @@ int hlc_last_stats(hlc_stats* out) {
 void hlc_shutdown(void) {
   batch_release_all();
   for (auto& d : g_dev) {
+    pool_release(d);  // (a part may have been freed since the last shutdown)
     if (!d.init) continue;
     if (d.ws) (void)hipFree(d.ws);
     if (d.cnt) (void)hipFree(d.cnt);

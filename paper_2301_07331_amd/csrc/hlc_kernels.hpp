@@ -88,6 +88,9 @@ void launch_layout64(const uint32_t* vals, const DevCount& n, const double* ra, 
 // (and the sorted (ra, dec) when radec is not null)
 void launch_layout32(const uint32_t* vals, const DevCount& n, const double* ra, const double* dec,
                      CellRec32* rec, double2* radec, hipStream_t s, const double2* il = nullptr);
+// both, and the sorted (ra, dec), from the keygen's records
+void launch_layout_both(const uint32_t* vals, const DevCount& n, const double2* il, Rec64* r64, CellRec32* r32,
+                        double2* radec, hipStream_t s);
 // lb[i] = number of B keys below keysA[i]; splits: merge_splits_len words of scratch
 size_t merge_splits_len(uint64_t na_cap, uint64_t nb_cap);
 void launch_merge_lb(const uint32_t* keysA, const DevCount& na, const uint32_t* keysB,

