@@ -25,7 +25,7 @@ namespace hlc {
 
 namespace {
 
-constexpr uint32_t PO_MEAN = 1024;       // mean pairs per bucket up to PO_RUNS buckets
+constexpr uint32_t PO_MEAN = 768;        // mean pairs per bucket up to PO_RUNS buckets (a self-match, i < j, has twice that first)
 constexpr uint32_t PO_RUNS = 1024;       // buckets up to which a scatter tile leaves in runs of 8 records
 constexpr uint32_t PO_MEAN_L = 10240;    // mean that more buckets keep, up to PO_BUCKETS of them
 constexpr uint32_t PO_BUCKETS = 2048;
@@ -36,9 +36,9 @@ constexpr uint32_t PO_CHUNK_THREADS = 1024;
 constexpr uint32_t PO_BIN_MAX = 48;      // a fuller bin: compare-exchange network instead of ranks
 constexpr uint32_t PO_OUTER = 1024;      // bins that split a bucket too large for LDS
 // The ordering blocks, by the buckets' mean: 2,048 pairs by 512 threads (four
-// blocks per CU hide each other's barriers) up to 1,280; 6,144 by 1,024 (two
+// blocks per CU hide each other's barriers) up to 1,000; 6,144 by 1,024 (two
 // per CU) up to 5,120; 12,288 by 1,024 beyond.
-constexpr uint32_t PO_CAP_S = 2048, PO_THREADS_S = 512, PO_MEAN_S = 1280;
+constexpr uint32_t PO_CAP_S = 2048, PO_THREADS_S = 512, PO_MEAN_S = 1000;
 constexpr uint32_t PO_CAP_M = 6144, PO_MEAN_M = 5120;
 constexpr uint32_t PO_CAP_L = 12288, PO_THREADS_L = 1024;
 constexpr uint32_t PO_OVER = 65536;      // a larger bucket (16-bit places in it): digit sort
