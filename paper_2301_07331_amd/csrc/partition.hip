@@ -666,7 +666,7 @@ __device__ inline uint32_t wave_lower(const uint32_t* __restrict__ keys, uint32_
     const uint32_t c = (uint32_t)__popcll(__ballot(below));  // (the first c probes)
     const uint64_t at = (uint64_t)l + (uint64_t)(c + 1u) * step - 1u;  // probe c: not below, or past r
     l += c * step;
-    if (at < r) r = (uint32_t)at;
+    if (c < 64u && at < r) r = (uint32_t)at;  // (all below: nothing is known of the rest)
     if (l > r) l = r;
   }
   const bool at_least = l + lane < r && (keys[l + lane] >> shift) >= i;
