@@ -101,7 +101,8 @@ typedef struct hlc_tuning {
   int32_t fraction_sort;     /* hlc_xmatch, hlc_xmatch_radii: 1 = the          *
                               * partition also sorts the RA sub-bin bits (one  *
                               * more radix pass; narrower windows inside dense *
-                              * clumps); 0 = not                               */
+                              * clumps); 0 = where a sample finds the sources  *
+                              * crowded                                        */
   int32_t batch_tile;        /* batched form: sources per partition tile (256, *
                               * 512, 1024 or 2048; 0 = autotuned and cached)   */
   int32_t batch_blocks_per_cu; /* batched form: blocks of the persistent match *

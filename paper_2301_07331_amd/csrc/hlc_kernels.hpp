@@ -66,12 +66,18 @@ constexpr uint32_t EXTENT_SLOTS = 256;  // most blocks of the passes below
 struct ExtentSlot {
   unsigned long long v[4], seq, pad_[3];
 };
-// a sample of at most 2 x 4096 sources into one slot
+// a sample of at most 2 x 4096 sources into one slot; with `crowd` also the
+// number of times that a sampled source of side 1 (of side 2 if that is empty)
+// lies in the cell of a run of sampled sources of side 2 (pad_[0]), a cell
+// being a square that holds GROUP sources at the mean density of the sample's
+// box
 void launch_extent_sample(const double* ra1, const double* dec1, uint32_t n1, const double* ra2, const double* dec2,
-                          uint32_t n2, ExtentSlot* out, unsigned long long seq, hipStream_t s);
-// every source; returns the number of slots filled
+                          uint32_t n2, bool crowd, ExtentSlot* out, unsigned long long seq, hipStream_t s);
+// every source; returns the number of slots filled; with `sample`, that sample
+// (crowd) as well
 uint32_t launch_extent(const double* ra1, const double* dec1, uint32_t n1, const double* ra2, const double* dec2,
-                       uint32_t n2, ExtentSlot* out, unsigned long long seq, hipStream_t s);
+                       uint32_t n2, ExtentSlot* out, unsigned long long seq, hipStream_t s,
+                       ExtentSlot* sample = nullptr);
 void launch_zone_tables(const Geom& g, int32_t* zmarg, double* zdelta, hipStream_t s);
 void launch_zone_starts(const uint32_t* keys, const DevCount& n, const Geom& g, uint32_t* zstart,
                         hipStream_t s);

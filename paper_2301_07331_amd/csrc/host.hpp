@@ -32,6 +32,7 @@ constexpr double ETA64 = 4e-15;  // bound on |chord_fp64 - chord| (unit sphere)
 // Written by kernels, read by the host.
 struct HostMsg {
   ExtentSlot ext[EXTENT_SLOTS];              // the footprint passes' slots (polled)
+  ExtentSlot sample;                         // the sample's (polled); pad_[0]: its shared cells
   unsigned long long err[2 * EXTENT_SLOTS];  // the largest error radii
   unsigned long long order;                  // what the pair ordering left to do
 };
@@ -81,6 +82,7 @@ struct Device {
   double cand_per_b = 0.0;
   int ncu = 0;  // compute units (persistent grids)
   bool last_full = true;  // the last call's frame was the whole sphere
+  bool last_crowded = false;  // and its sources were crowded (what a speculative keygen assumes)
   // mapped host memory: what kernels tell the host without a copy
   HostMsg* msg = nullptr;
   HostMsg* msg_dev = nullptr;  // its device address
@@ -203,11 +205,18 @@ struct FrameQuery {
   unsigned long long seq;
   uint32_t slots;
   bool exact;
+  bool crowd;  // the sample also says how crowded the sources are
 };
+// Sources of the larger side from which it does: below, the crowded tests that
+// a fourth radix pass saves (500 an A source: 50 us at 2^19) cost no more than
+// the pass and the 10 us that the count adds to the sample.
+constexpr int64_t CROWD_MIN = 1 << 19;
 FrameQuery frame_begin(Device& dev, const double* a_ra, const double* a_dec, int64_t na, const double* b_ra,
                        const double* b_dec, int64_t nb, hipStream_t s);
+// (qs: the stream that frame_begin was given)
 int frame_finish(Device& dev, FrameQuery q, const double* a_ra, const double* a_dec, int64_t na,
-                 const double* b_ra, const double* b_dec, int64_t nb, hipStream_t s, Frame* out);
+                 const double* b_ra, const double* b_dec, int64_t nb, hipStream_t s, hipStream_t qs, Frame* out,
+                 bool* crowded);
 // the exact box of every valid source of both catalogues
 int exact_box(Device& dev, const double* a_ra, const double* a_dec, int64_t na, const double* b_ra,
               const double* b_dec, int64_t nb, hipStream_t s, Box* out);

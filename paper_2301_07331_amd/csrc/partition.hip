@@ -1012,31 +1012,34 @@ __device__ inline unsigned long long ord_code(double v) {  // v >= 0
   return (unsigned long long)__double_as_longlong(v);
 }
 
-// Block-wide max of e[4] into one slot, then, where the slot lies in mapped
-// host memory and is polled, the call's sequence number once the four values
-// are visible there.
-__device__ inline void ext_reduce(unsigned long long e[4], ExtentSlot* out, unsigned long long seq) {
+// Block-wide max of e[4] (every thread gets it; up to 16 waves); one thread's
+// store of it into a slot, then, where the slot lies in mapped host memory and
+// is polled, the call's sequence number once the values are visible there.
+__device__ inline void ext_block_max(unsigned long long e[4], unsigned long long (*s_e)[4]) {
 #pragma unroll
   for (int k = 0; k < 4; ++k)
     for (int d = 32; d > 0; d >>= 1) {
       const unsigned long long o = __shfl_xor(e[k], d);
       e[k] = o > e[k] ? o : e[k];
     }
-  __shared__ unsigned long long s_e[16][4];  // up to 16 waves
   const uint32_t w = threadIdx.x >> 6;
   if ((threadIdx.x & 63u) == 0)
     for (int k = 0; k < 4; ++k) s_e[w][k] = e[k];
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int k = 0; k < 4; ++k) {
-      unsigned long long m = 0ull;
-      for (uint32_t u = 0; u < (blockDim.x >> 6); ++u) m = s_e[u][k] > m ? s_e[u][k] : m;
-      out->v[k] = m;
-    }
-    if (seq) {
-      __threadfence_system();
-      *(volatile unsigned long long*)&out->seq = seq;
-    }
+  if (threadIdx.x < 4u) {
+    unsigned long long m = 0ull;
+    for (uint32_t u = 0; u < (blockDim.x >> 6); ++u) m = max(m, s_e[u][threadIdx.x]);
+    s_e[0][threadIdx.x] = m;
+  }
+  __syncthreads();
+  for (int k = 0; k < 4; ++k) e[k] = s_e[0][k];
+}
+
+__device__ inline void ext_store(const unsigned long long e[4], ExtentSlot* out, unsigned long long seq) {
+  for (int k = 0; k < 4; ++k) out->v[k] = e[k];
+  if (seq) {
+    __threadfence_system();
+    *(volatile unsigned long long*)&out->seq = seq;
   }
 }
 
@@ -1058,11 +1061,36 @@ __device__ inline uint32_t sample_index(uint32_t run, uint32_t lane, uint32_t n)
   return min(start, n - 64u) + lane;
 }
 
-__global__ __launch_bounds__(1024) void k_extent_sample(const double* __restrict__ ra1,
-                                                        const double* __restrict__ dec1, uint32_t n1,
-                                                        const double* __restrict__ ra2,
-                                                        const double* __restrict__ dec2, uint32_t n2,
-                                                        ExtentSlot* out, unsigned long long seq) {
+// The sample's crowding: side 2's sampled sources go into an LDS hash table of
+// the cells they lie in, with a bit for each couple of the 64 runs; side 1's
+// then look their cells up and count the couples of the others. The couple of
+// the same number is left out: in sorted catalogues it may lie in the same
+// place, and a self-match's holds the source itself. One CU does this while
+// nothing else can run, so it is its chain that counts: a thread's four
+// probes go side by side and the table has four slots an entry.
+constexpr uint32_t CROWD_SLOTS = 16384;  // (every probe sequence ends)
+struct CrowdTable {
+  uint32_t tag[CROWD_SLOTS];
+  uint32_t runs[CROWD_SLOTS];
+};
+
+// cell of a position: Dec strips of side c, cut at c of sky (at the strip's
+// middle); never 0xffffffff, the empty tag
+struct CrowdGrid {
+  float d0, a0, c, inv_c;
+};
+__device__ inline uint32_t crowd_cell(const CrowdGrid& g, double a, double d) {
+  const float z = fminf(floorf(fmaxf((float)d - g.d0, 0.0f) * g.inv_c), 32767.0f);
+  const float w = __cosf((g.d0 + (z + 0.5f) * g.c) * 0.017453293f) * g.inv_c;
+  const float x = fminf(fmaxf(floorf(((float)a - g.a0) * w), 0.0f), 65535.0f);
+  return ((uint32_t)z << 16) | (uint32_t)x;
+}
+__device__ inline uint32_t crowd_hash(uint32_t cell) { return (cell * 2654435761u) >> 18; }
+
+template <bool CROWD>
+__device__ inline void sample_block(const double* __restrict__ ra1, const double* __restrict__ dec1, uint32_t n1,
+                                    const double* __restrict__ ra2, const double* __restrict__ dec2, uint32_t n2,
+                                    ExtentSlot* out, unsigned long long seq, unsigned long long (*s_e)[4]) {
   constexpr int PER = 4;  // runs per wave and catalogue (16 waves x 4 = 64 runs)
   const uint32_t lane = threadIdx.x & 63u, w = threadIdx.x >> 6;
   double a[2 * PER], d[2 * PER];
@@ -1078,25 +1106,113 @@ __global__ __launch_bounds__(1024) void k_extent_sample(const double* __restrict
   unsigned long long e[4] = {0ull, 0ull, 0ull, 0ull};
 #pragma unroll
   for (int j = 0; j < 2 * PER; ++j) ext_add(e, a[j], d[j]);
-  ext_reduce(e, out, seq);
+  ext_block_max(e, s_e);
+  if constexpr (CROWD) {
+    __shared__ CrowdTable T;
+    __shared__ uint32_t s_met;
+    for (uint32_t i = threadIdx.x; i < CROWD_SLOTS; i += 1024u) {
+      T.tag[i] = 0xffffffffu;
+      T.runs[i] = 0u;
+    }
+    if (threadIdx.x == 0) s_met = 0u;
+    // the box and the side of a square that holds GROUP sources at its density
+    const float d0 = (float)(__longlong_as_double((long long)~e[0]) - 90.0);
+    const float d1 = (float)(__longlong_as_double((long long)e[1]) - 90.0);
+    const float a0 = (float)__longlong_as_double((long long)~e[2]), a1 = (float)__longlong_as_double((long long)e[3]);
+    constexpr float D2R = 0.017453293f;
+    const float area = fmaxf((__sinf(d1 * D2R) - __sinf(d0 * D2R)) / D2R * (a1 - a0), 1e-9f);
+    const float c = sqrtf((float)GROUP * area / (float)max(n1, n2));
+    const CrowdGrid grid{d0, a0, c, 1.0f / c};
+    __syncthreads();
+    uint32_t cell[PER], h[PER], open = 0u;
+    auto start = [&](const double (&ra)[2 * PER], const double (&de)[2 * PER], int first) {
+      open = 0u;
+#pragma unroll
+      for (int j = 0; j < PER; ++j) {
+        cell[j] = crowd_cell(grid, ra[first + j], de[first + j]);
+        h[j] = crowd_hash(cell[j]);
+        if (valid_pos(ra[first + j], de[first + j])) open |= 1u << j;
+      }
+    };
+    auto couple = [&](int j) { return 1u << ((w + 16u * (uint32_t)j) >> 1); };
+    start(a, d, PER);
+    while (open) {
+      uint32_t was[PER];
+#pragma unroll
+      for (int j = 0; j < PER; ++j)
+        was[j] = (open >> j & 1u) ? atomicCAS(&T.tag[h[j]], 0xffffffffu, cell[j]) : 0u;
+#pragma unroll
+      for (int j = 0; j < PER; ++j) {
+        if (!(open >> j & 1u)) continue;
+        if (was[j] == 0xffffffffu || was[j] == cell[j]) {
+          atomicOr(&T.runs[h[j]], couple(j));
+          open &= ~(1u << j);
+        } else {
+          h[j] = (h[j] + 1u) & (CROWD_SLOTS - 1u);
+        }
+      }
+    }
+    __syncthreads();
+    uint32_t met = 0u;
+    if (n1) start(a, d, 0);
+    else start(a, d, PER);
+    while (open) {
+      uint32_t tag[PER], runs[PER];
+#pragma unroll
+      for (int j = 0; j < PER; ++j) {
+        tag[j] = T.tag[h[j]];
+        runs[j] = T.runs[h[j]];
+      }
+#pragma unroll
+      for (int j = 0; j < PER; ++j) {
+        if (!(open >> j & 1u)) continue;
+        if (tag[j] == cell[j]) met += (uint32_t)__popc(runs[j] & ~couple(j));
+        if (tag[j] == cell[j] || tag[j] == 0xffffffffu) open &= ~(1u << j);
+        else h[j] = (h[j] + 1u) & (CROWD_SLOTS - 1u);
+      }
+    }
+    for (int off = 32; off > 0; off >>= 1) met += __shfl_xor(met, off);
+    if (lane == 0) atomicAdd(&s_met, met);
+    __syncthreads();
+    if (threadIdx.x == 0) out->pad_[0] = s_met;
+  }
+  if (threadIdx.x == 0) ext_store(e, out, seq);
 }
 
-// Every source of both catalogues, a slot per block (combined by the host).
-// Eight loads of each coordinate in flight: a million sources a side take
-// 8 us; 64 dependent trips of few blocks took 40 us a side.
-constexpr uint32_t EXT_THREADS = 512, EXT_PER = 8;
-__global__ __launch_bounds__(EXT_THREADS) void k_extent(const double* __restrict__ ra1,
+template <bool CROWD>
+__global__ __launch_bounds__(1024) void k_extent_sample(const double* __restrict__ ra1,
                                                         const double* __restrict__ dec1, uint32_t n1,
                                                         const double* __restrict__ ra2,
                                                         const double* __restrict__ dec2, uint32_t n2,
                                                         ExtentSlot* out, unsigned long long seq) {
+  __shared__ unsigned long long s_e[16][4];
+  sample_block<CROWD>(ra1, dec1, n1, ra2, dec2, n2, out, seq, s_e);
+}
+
+// Every source of both catalogues, a slot per block (combined by the host);
+// with CROWD, block 0 takes the sample instead, beside the others. Four loads
+// of each coordinate in flight: a million sources a side take 8 us; 64
+// dependent trips of few blocks took 40 us a side.
+constexpr uint32_t EXT_THREADS = 1024, EXT_PER = 4;
+template <bool CROWD>
+__global__ __launch_bounds__(EXT_THREADS) void k_extent(const double* __restrict__ ra1,
+                                                        const double* __restrict__ dec1, uint32_t n1,
+                                                        const double* __restrict__ ra2,
+                                                        const double* __restrict__ dec2, uint32_t n2,
+                                                        ExtentSlot* out, ExtentSlot* sample,
+                                                        unsigned long long seq) {
+  __shared__ unsigned long long s_e[16][4];
+  if (CROWD && blockIdx.x == 0) {
+    sample_block<CROWD>(ra1, dec1, n1, ra2, dec2, n2, sample, seq, s_e);
+    return;
+  }
+  const uint32_t blk = blockIdx.x - (CROWD ? 1u : 0u), nblk = gridDim.x - (CROWD ? 1u : 0u);
   unsigned long long e[4] = {0ull, 0ull, 0ull, 0ull};
   for (int side = 0; side < 2; ++side) {
     const double* __restrict__ ra = side ? ra2 : ra1;
     const double* __restrict__ dec = side ? dec2 : dec1;
     const uint32_t n = side ? n2 : n1;
-    for (uint64_t b = (uint64_t)blockIdx.x * EXT_THREADS * EXT_PER; b < n;
-         b += (uint64_t)gridDim.x * EXT_THREADS * EXT_PER) {
+    for (uint64_t b = (uint64_t)blk * EXT_THREADS * EXT_PER; b < n; b += (uint64_t)nblk * EXT_THREADS * EXT_PER) {
       double a[EXT_PER], d[EXT_PER];
 #pragma unroll
       for (uint32_t j = 0; j < EXT_PER; ++j) {
@@ -1108,7 +1224,8 @@ __global__ __launch_bounds__(EXT_THREADS) void k_extent(const double* __restrict
       for (uint32_t j = 0; j < EXT_PER; ++j) ext_add(e, a[j], d[j]);
     }
   }
-  ext_reduce(e, out + blockIdx.x, seq);
+  ext_block_max(e, s_e);
+  if (threadIdx.x == 0) ext_store(e, out + blk, seq);
 }
 
 }  // namespace
@@ -1231,15 +1348,17 @@ void sort_pairs(uint2* pairs, double* sep, uint32_t n, int bits_a, int bits_b, u
 }
 
 void launch_extent_sample(const double* ra1, const double* dec1, uint32_t n1, const double* ra2, const double* dec2,
-                          uint32_t n2, ExtentSlot* out, unsigned long long seq, hipStream_t s) {
-  k_extent_sample<<<1, 1024, 0, s>>>(ra1, dec1, n1, ra2, dec2, n2, out, seq);
+                          uint32_t n2, bool crowd, ExtentSlot* out, unsigned long long seq, hipStream_t s) {
+  if (crowd) k_extent_sample<true><<<1, 1024, 0, s>>>(ra1, dec1, n1, ra2, dec2, n2, out, seq);
+  else k_extent_sample<false><<<1, 1024, 0, s>>>(ra1, dec1, n1, ra2, dec2, n2, out, seq);
 }
 
 uint32_t launch_extent(const double* ra1, const double* dec1, uint32_t n1, const double* ra2, const double* dec2,
-                       uint32_t n2, ExtentSlot* out, unsigned long long seq, hipStream_t s) {
+                       uint32_t n2, ExtentSlot* out, unsigned long long seq, hipStream_t s, ExtentSlot* sample) {
   const uint32_t blocks =
       std::min<uint32_t>(EXTENT_SLOTS, std::max(1u, cdiv(std::max(n1, n2), EXT_THREADS * EXT_PER)));
-  k_extent<<<blocks, EXT_THREADS, 0, s>>>(ra1, dec1, n1, ra2, dec2, n2, out, seq);
+  if (sample) k_extent<true><<<blocks + 1, EXT_THREADS, 0, s>>>(ra1, dec1, n1, ra2, dec2, n2, out, sample, seq);
+  else k_extent<false><<<blocks, EXT_THREADS, 0, s>>>(ra1, dec1, n1, ra2, dec2, n2, out, nullptr, seq);
   return blocks;
 }
 

@@ -24,7 +24,6 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   const bool self = (o->flags & HLC_SELF) != 0;
   if (prof) HLC_TRY(hipEventRecord(dev->ev[0], s));
   const int64_t na_frame = self ? 0 : na;
-  const FrameQuery fq = frame_begin(*dev, a_ra, a_dec, na_frame, b_ra, b_dec, nb, s);
   const uint32_t nB = (uint32_t)nb;
   // self-match: A's entries are B's (halo copies included)
   const uint32_t nA = self ? 2 * nB : (uint32_t)na;
@@ -34,7 +33,7 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   Geom g = make_geom(r_arcsec, tuned_height(o), na, nb, tuned_bins(o), Frame{});
   // (set before A's speculative keygen: the number of radix passes decides
   // which buffer that keygen writes)
-  g.frac_sorted = tuned_fraction_sort(o) ? 1 : 0;
+  g.frac_sorted = tuned_fraction_sort(o) || dev->last_crowded ? 1 : 0;
   Side A, B;
   SortScratch sc, scA;
   MatchWs w;
@@ -57,30 +56,38 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   // buffers do not depend on the frame). They are kept if the sample
   // confirms the frame, else computed again.
   bool spec = false;
-  if (!self && !fq.exact) {
+  if (!self && dev->last_full) {
     Carve sizing{nullptr};
     lay(sizing);
-    if (sizing.off + 256 <= dev->ws_bytes) {
-      Carve c{(char*)dev->ws};
-      lay(c);
-      if (prof) HLC_TRY(hipEventRecord(dev->ev[14], s));
-      launch_zero_counters(dev->cnt, s);
-      // B's on the caller's stream, launched first (B's chain is the longer
-      // one), A's beside it on the side stream, where A's sort follows (the
-      // places of B's buffers do not depend on the frame either)
-      HLC_TRY(hipEventRecord(dev->fork, s));
-      partition_keys(*dev, b_ra, b_dec, nB, g, true, !fp32, fp32, sc, 2u, B, slB, s);
-      HLC_TRY(hipStreamWaitEvent(dev->side, dev->fork, 0));
-      partition_keys(*dev, a_ra, a_dec, nA, g, false, !fp32, fp32, scA, 1u, A, slA, dev->side);
-      spec = true;
-    }
+    spec = sizing.off + 256 <= dev->ws_bytes;
+  }
+  FrameQuery fq;
+  if (spec) {
+    Carve c{(char*)dev->ws};
+    lay(c);
+    if (prof) HLC_TRY(hipEventRecord(dev->ev[14], s));
+    launch_zero_counters(dev->cnt, s);
+    // B's on the caller's stream, launched first (B's chain is the longer
+    // one); the sample and A's keygen beside it on the side stream, where A's
+    // sort follows (the places of B's buffers do not depend on the frame
+    // either)
+    HLC_TRY(hipEventRecord(dev->fork, s));
+    HLC_TRY(hipStreamWaitEvent(dev->side, dev->fork, 0));
+    fq = frame_begin(*dev, a_ra, a_dec, na_frame, b_ra, b_dec, nb, dev->side);
+    partition_keys(*dev, b_ra, b_dec, nB, g, true, !fp32, fp32, sc, 2u, B, slB, s);
+    partition_keys(*dev, a_ra, a_dec, nA, g, false, !fp32, fp32, scA, 1u, A, slA, dev->side);
+  } else {
+    fq = frame_begin(*dev, a_ra, a_dec, na_frame, b_ra, b_dec, nb, s);
   }
   Frame f;
-  HLC_CHECK(frame_finish(*dev, fq, a_ra, a_dec, na_frame, b_ra, b_dec, nb, s, &f));
+  bool crowded = false;
+  HLC_CHECK(frame_finish(*dev, fq, a_ra, a_dec, na_frame, b_ra, b_dec, nb, s, spec ? dev->side : s, &f, &crowded));
   dev->last_full = is_full(f);
-  const bool keep = spec && dev->last_full;  // the speculative keys stand
+  const int spec_frac = g.frac_sorted;
+  dev->last_crowded = crowded;
   g = make_geom(r_arcsec, tuned_height(o), na, nb, tuned_bins(o), f);
-  g.frac_sorted = tuned_fraction_sort(o) ? 1 : 0;
+  g.frac_sorted = tuned_fraction_sort(o) || crowded ? 1 : 0;
+  const bool keep = spec && dev->last_full && g.frac_sorted == spec_frac;  // the speculative keys stand
   Carve sizing{nullptr};
   lay(sizing);
   HLC_CHECK(ensure_ws(*dev, sizing.off + 256));
