@@ -111,8 +111,8 @@ Geom make_geom(double r_arcsec, double h_as, int64_t na, int64_t nb, int ra_bits
 }
 
 FrameQuery frame_begin(Device& dev, const double* a_ra, const double* a_dec, int64_t na, const double* b_ra,
-                       const double* b_dec, int64_t nb, hipStream_t s) {
-  FrameQuery q{++dev.fseq, 0u, !dev.last_full, std::max(na, nb) >= CROWD_MIN};
+                       const double* b_dec, int64_t nb, bool crowd, hipStream_t s) {
+  FrameQuery q{++dev.fseq, 0u, !dev.last_full, crowd};
   if (q.exact)
     q.slots = launch_extent(a_ra, a_dec, (uint32_t)na, b_ra, b_dec, (uint32_t)nb, dev.msg_dev->ext, q.seq, s,
                             q.crowd ? &dev.msg_dev->sample : nullptr);

@@ -59,7 +59,9 @@ struct Geom {
 struct DevCount {
   uint32_t base, cap;
   const unsigned long long* extra;
+  const unsigned int* none = nullptr;  // device flag: set, there are no entries
   __device__ uint32_t get() const {
+    if (none && *none) return 0u;
     unsigned long long v = (unsigned long long)base + (extra ? *extra : 0ull);
     return v < cap ? (uint32_t)v : cap;
   }
@@ -82,6 +84,8 @@ struct Counters {
   unsigned long long n_ties;      // decided in double-double
   unsigned int err;               // bit 0: bad coordinate in A, bit 1: in B
   unsigned int queue;             // work-queue head of persistent kernels
+  unsigned int sort_over;         // a bucket of the bucket sort outgrew its block
+  unsigned int pad_;
   unsigned long long aux[2];      // entry counts of multi-entry keygens (A, B)
   unsigned long long region_max;  // largest pair-region fill (compaction)
   unsigned long long cand_max;    // largest candidate-region fill

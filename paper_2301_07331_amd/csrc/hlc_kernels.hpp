@@ -10,7 +10,8 @@ namespace hlc {
 
 // ---- partition.hip ---------------------------------------------------------
 void launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t s);
-void launch_zero_counters(Counters* c, hipStream_t s);
+// (and up to two bucket-sort samples of BS_FINE words)
+void launch_zero_counters(Counters* c, hipStream_t s, uint32_t* fine1 = nullptr, uint32_t* fine2 = nullptr);
 struct SortScratch {
   uint32_t* keys_alt;
   uint32_t* vals_alt;
@@ -26,6 +27,14 @@ struct KeygenHist {
   uint32_t cap;
   int shift;
 };
+// The bucket sort's sample: sources i with (i & mask) == 0 counted in fine by
+// bucket_fine of their key (and of their Dec-halo copy's).
+struct KeygenSample {
+  uint32_t* fine;
+  uint32_t mask;
+  unsigned long long mul;
+};
+
 // keys/vals of n sources: one entry per source, plus the Dec-halo copies
 // appended after n when `halo` is set (with iota_vals, the value of source
 // i, i itself, is left to the sort's first pass); with radec also each
@@ -34,7 +43,8 @@ struct KeygenHist {
 // certification read
 void launch_keygen(const double* ra, const double* dec, uint32_t n, const Geom& g, bool halo,
                    uint32_t err_bit, uint32_t* keys, uint32_t* vals, Counters* cnt, hipStream_t s,
-                   double2* radec = nullptr, const KeygenHist* kh = nullptr, bool iota_vals = false);
+                   double2* radec = nullptr, const KeygenHist* kh = nullptr, bool iota_vals = false,
+                   const KeygenSample* ks = nullptr);
 // tiles of the first pass whose counts a keygen of n sources fills
 uint32_t keygen_hist_tiles(uint32_t n);
 
@@ -107,6 +117,56 @@ void launch_key_index(const uint32_t* keys, const DevCount& n, int shift, uint32
 void launch_ranges(const uint32_t* keysA, const DevCount& na, const uint32_t* kidx, int kshift, uint32_t kT,
                    const uint32_t* keysB, const uint32_t* zstartB, const int32_t* zmarg, const double* zdelta,
                    const Geom& g, GroupRanges* out, hipStream_t s);
+
+// ---- bucket_sort.hip -------------------------------------------------------
+constexpr uint32_t BS_FINE = 8192;     // parts of the key space that make up the buckets
+constexpr uint32_t BS_BUCKETS = 1024;  // most buckets
+constexpr uint32_t BS_MAX = BS_BUCKETS * 1792u;  // most sources of a side
+// part of a key: equal stretches of the keys in use [0, span), mul = bucket_fine_mul(span)
+inline unsigned long long bucket_fine_mul(unsigned long long span) {
+  return ((unsigned long long)BS_FINE << 32) / span;
+}
+__device__ inline uint32_t bucket_fine(uint32_t key, unsigned long long mul) {
+  return min((uint32_t)(((unsigned long long)key * mul) >> 32), BS_FINE - 1u);
+}
+struct BucketPlan {
+  uint32_t K;       // buckets (0: no bucket sort)
+  uint32_t chunks;  // counted and scattered by a block each
+  uint32_t cap;     // entries that an ordering block takes
+  bool direct;      // one block takes them all
+};
+BucketPlan bucket_plan(uint32_t n);
+// the sampled sources of a plan: i with (i & mask) == 0
+uint32_t bucket_sample_mask(uint32_t n, const BucketPlan& p);
+struct BucketWs {
+  uint32_t* fine;                      // BS_FINE: the keygen's sample, cleared before it
+  uint16_t* map;                       // BS_FINE: bucket of a part
+  uint32_t *counts, *totals, *starts;  // chunks * K, K, K + 1
+  uint2* kv;                           // the entries by bucket: key, index
+  double2* rd;                         // and (ra, dec)
+};
+struct BucketIn {
+  const uint32_t *keys, *vals;  // unsorted; entry i < n_src is source i (vals not read)
+  const double *ra, *dec;       // by source
+  uint32_t n_src;
+  DevCount cnt;
+  const uint32_t* starts;  // (set by the launcher, as the rest)
+  const uint2* kv;
+  const double2* rd;
+  const unsigned int* over;
+};
+// sorted; each of the records may be null
+struct BucketOut {
+  uint32_t *keys, *vals;
+  Rec64* r64;
+  CellRec32* r32;
+  double2* radec;
+};
+void launch_bucket_sort(const BucketPlan& p, const BucketIn& in, const BucketOut& out, const BucketWs& w,
+                        unsigned long long fine_mul, Counters* cnt, hipStream_t s);
+// per bucket of K, the exclusive scan of counts[chunk * K + bucket] over the
+// chunks (at most 256), in place, and the totals (pair_order.hip)
+void launch_bucket_scan(uint32_t* counts, uint32_t chunks, uint32_t K, uint32_t* totals, hipStream_t s);
 
 // ---- pair_order.hip --------------------------------------------------------
 // pairs (and separations, if sep) ordered by (a, b), a < na
@@ -260,9 +320,9 @@ struct MatchArgs {
   // sorted index arrays (source index, halo bit included)
   const uint32_t* valsA;
   const uint32_t* valsB;
-  // A read in place (recA64 / recA32 unused): entry p's position is the
-  // keygen's (ra, dec) record of source valsA[p] (srcradA), from which the
-  // filter computes the unit vector or cell record
+  // A read in place (recA64 / recA32 unused): the filter computes the unit
+  // vector or cell record from entry p's position, radecA[p] when the sort
+  // carried it, else the keygen's (ra, dec) record of source valsA[p] (srcradA)
   int a_in_place;
   const uint32_t* keysA;
   const uint32_t* keysB;

@@ -82,6 +82,7 @@ struct Device {
   double cand_per_b = 0.0;
   int ncu = 0;  // compute units (persistent grids)
   bool last_full = true;  // the last call's frame was the whole sphere
+  int digit_calls = 0;        // calls left that take the digit sort at once
   bool last_crowded = false;  // and its sources were crowded (what a speculative keygen assumes)
   // mapped host memory: what kernels tell the host without a copy
   HostMsg* msg = nullptr;
@@ -212,7 +213,7 @@ struct FrameQuery {
 // the pass and the 10 us that the count adds to the sample.
 constexpr int64_t CROWD_MIN = 1 << 19;
 FrameQuery frame_begin(Device& dev, const double* a_ra, const double* a_dec, int64_t na, const double* b_ra,
-                       const double* b_dec, int64_t nb, hipStream_t s);
+                       const double* b_dec, int64_t nb, bool crowd, hipStream_t s);
 // (qs: the stream that frame_begin was given)
 int frame_finish(Device& dev, FrameQuery q, const double* a_ra, const double* a_dec, int64_t na,
                  const double* b_ra, const double* b_dec, int64_t nb, hipStream_t s, hipStream_t qs, Frame* out,
@@ -269,13 +270,16 @@ inline int tuned_items(const hlc_opts* o) {
 // ---------------------------------------------------------------------------
 // One partitioned catalogue.
 struct Side {
+  BucketPlan plan{};  // K > 0: the bucket sort (else the digit sort)
+  BucketWs bws{};
   uint32_t n_src = 0, n_cap = 0;  // sources; entry capacity (2 n_src with a halo)
   DevCount cnt{0, 0, nullptr};    // entries, halo copies included (device-side)
   uint32_t *keys = nullptr, *vals = nullptr;
   Rec64* r64 = nullptr;
   CellRec32* r32 = nullptr;
-  // sorted (ra, dec): FP32 form in the sorted certification layout (see
-  // carve_side), and the paper-scheme emulation's pixel tests
+  // sorted (ra, dec): with the bucket sort, of a side read in place and of an
+  // FP32 side; with the digit sort, in the sorted certification layout (see
+  // carve_side); and for the paper-scheme emulation's pixel tests
   double2* radec = nullptr;
   // (ra, dec) of each source, 16 B, written by the keygen in input order
   // (nullptr: the layout reads the caller's coordinates): the sorted records
@@ -354,6 +358,7 @@ struct Caps {
   uint64_t band;
   uint64_t stage;
   uint64_t cand;
+  bool digit_sort = false;
 };
 
 // pair_regions: pairs staged in regions and compacted (else written straight
@@ -391,6 +396,16 @@ size_t carve_match_ws(Carve& c, MatchWs& w, uint32_t na_entries, const Geom& g, 
 void carve_side(Carve& c, Side& sd, uint32_t cap, bool l64, bool l32, uint32_t n_src = 0, bool layout = true,
                 bool sorted_radec = false);
 void carve_sort(Carve& c, SortScratch& sc, uint32_t nmax);
+// the scratch of the sort that sd.plan names
+void carve_sort(Carve& c, SortScratch& sc, uint32_t nmax, Side& sd);
+// the sort of a side of n sources: through buckets, or digit by digit beyond
+// BS_MAX sources or when the call asks for it
+inline BucketPlan plan_sort(int64_t n, bool digit_sort) {
+  return digit_sort || n < 1 || n > (int64_t)BS_MAX ? BucketPlan{} : bucket_plan((uint32_t)n);
+}
+// A bucket outgrew its block: the call runs again with the digit sort, and the
+// next DIGIT_CALLS calls on the device take it at once.
+constexpr int DIGIT_CALLS = 15;
 
 // the coordinates checked (no pairs: one side is empty)
 int validate_only(const double* a_ra, const double* a_dec, int64_t na, const double* b_ra,

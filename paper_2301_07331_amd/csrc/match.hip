@@ -494,7 +494,7 @@ __device__ inline ARaw load_a(const MatchArgs& a, const ItemHead& h) {
   if constexpr (F32) {
     if (a.a_in_place) {
       // (ra, dec) in place; the cell record as the layout would write it
-      const double2 p = a.srcradA[idx & IDX_MASK];
+      const double2 p = a.radecA ? a.radecA[h.a_pos] : a.srcradA[idx & IDX_MASK];
       double x, y, z;
       unit_vector(p.x, p.y, x, y, z);
       r.ca = encode_cell(x, y, z);
@@ -513,7 +513,7 @@ __device__ inline ARaw load_a(const MatchArgs& a, const ItemHead& h) {
   } else {
     if (a.a_in_place) {
       // (ra, dec) in place; the unit vector as the layout would write it
-      const double2 p = a.srcradA[idx & IDX_MASK];
+      const double2 p = a.radecA ? a.radecA[h.a_pos] : a.srcradA[idx & IDX_MASK];
       unit_vector(p.x, p.y, r.u0, r.u1, r.u2);
     } else {
       const Rec64 s = a.recA64[h.a_pos];

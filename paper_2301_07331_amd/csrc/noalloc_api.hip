@@ -112,27 +112,35 @@ int noalloc_impl(const double* a_ra, const double* a_dec, int64_t na, const doub
   const Box box = read_box(sd->host_ext, slots);
   const Frame f = (!box.any || quarter_sky(box)) ? Frame{} : frame_of_box(box);
   Geom g = make_geom(r_arcsec, tuned_height(o), na, nb, tuned_bins(o), f);
-  g.frac_sorted = tuned_fraction_sort(o) ? 1 : 0;
   const uint32_t nA = (uint32_t)na, nB = (uint32_t)nb;
   Caps caps = scratch_caps(*sd, (uint64_t)(na + nb), (uint64_t)o->capacity);
   double* sep = (o->flags & HLC_NO_SEP) ? nullptr : out_sep;
-  for (int attempt = 0; attempt < 3; ++attempt) {
+  for (int attempt = 0; attempt < 4; ++attempt) {
     Side A, B;
+    A.plan = plan_sort(na, caps.digit_sort);
+    B.plan = plan_sort(nb, caps.digit_sort);
     SortScratch scA, scB;
     MatchWs w;
     auto lay = [&](Carve& c) {
       carve_side(c, A, nA, !fp32, fp32, nA, false);  // A is read in place
-      carve_sort(c, scA, nA);
+      carve_sort(c, scA, nA, A);
       carve_side(c, B, 2 * nB, !fp32, fp32, nB);
-      carve_sort(c, scB, 2 * nB);
+      carve_sort(c, scB, 2 * nB, B);
       carve_match_ws(c, w, nA, g, caps, true);
     };
     Carve sizing{nullptr};
     lay(sizing);
+    if (sizing.off + 256 > ctx.ws_bytes && (A.plan.K || B.plan.K)) {
+      // the digit sort needs less scratch
+      A.plan = B.plan = BucketPlan{};
+      sizing = Carve{nullptr};
+      lay(sizing);
+    }
+    g.frac_sorted = B.plan.K || tuned_fraction_sort(o) ? 1 : 0;
     if (sizing.off + 256 > ctx.ws_bytes) return HLC_E_UNSUPPORTED;  // beyond the scratch array
     Carve c{static_cast<char*>(ctx.ws)};
     lay(c);
-    launch_zero_counters(ctx.cnt, s);
+    launch_zero_counters(ctx.cnt, s, A.bws.fine, B.bws.fine);
     partition_keys(ctx, a_ra, a_dec, nA, g, false, !fp32, fp32, scA, 1u, A, NO_SLOTS, s);
     partition_keys(ctx, b_ra, b_dec, nB, g, true, !fp32, fp32, scB, 2u, B, NO_SLOTS, s);
     HLC_CHECK(partition_sort(ctx, g, !fp32, fp32, scA, A, NO_SLOTS, s));
@@ -144,6 +152,10 @@ int noalloc_impl(const double* a_ra, const double* a_dec, int64_t na, const doub
     if (h.err) {
       *o->n_pairs = 0;
       return HLC_E_INVAL;
+    }
+    if (h.sort_over) {
+      caps.digit_sort = true;
+      continue;
     }
     const bool again = regrow(ctx, h, (uint64_t)o->capacity, caps);
     sd->hint_stage = ctx.hint_stage;

@@ -577,6 +577,10 @@ uint32_t block_cap(uint32_t n, const PairOrderSizes& z) {
 
 }  // namespace
 
+void launch_bucket_scan(uint32_t* counts, uint32_t chunks, uint32_t K, uint32_t* totals, hipStream_t s) {
+  k_po_scan<<<(K + 63) / 64, PO_CHUNK_THREADS, 0, s>>>(counts, chunks, K, totals);
+}
+
 PairOrderSizes pair_order_sizes(uint32_t n, uint64_t na) {
   PairOrderSizes z{};
   z.K = bucket_count(n, na);
@@ -595,7 +599,7 @@ void launch_pair_order(uint2* pairs, double* sep, uint32_t n, uint64_t na, const
   const uint64_t mul = ((uint64_t)z.K << 32) / na;
   const uint32_t chunk = (n + z.chunks - 1) / z.chunks;
   k_po_count<<<z.chunks, PO_CHUNK_THREADS, 0, s>>>(pairs, n, chunk, mul, z.K, w.counts);
-  k_po_scan<<<(z.K + 63) / 64, PO_CHUNK_THREADS, 0, s>>>(w.counts, z.chunks, z.K, w.totals);
+  launch_bucket_scan(w.counts, z.chunks, z.K, w.totals, s);
   k_po_scatter<<<z.chunks, PO_CHUNK_THREADS, 0, s>>>(pairs, sep, n, chunk, mul, z.K, block_cap(n, z), w.counts,
                                                      w.totals, w.starts, w.rec, over);
   switch (block_cap(n, z)) {

@@ -56,68 +56,73 @@ int hlc_partition(const double* ra_deg, const double* dec_deg, int64_t n, double
     // automatic zone height depends on the radius only.
     double h_as = tuned_height(opts);
     if (!(h_as > 0)) h_as = std::min(std::max(64.0 * r_arcsec, 32.0), 3600.0);
-    auto* p = new hlc_part();
-    p->device = dev_id;
-    p->r_build = r_arcsec;
-    p->g = make_geom(r_arcsec, h_as, n, n, tuned_bins(opts));
     const uint32_t nn = (uint32_t)n, cap = 2 * nn;
-    auto lay = [&](Carve& c) {
-      // FP32: sorted (ra, dec) kept with the part for the certification (its
-      // per-source records are scratch)
-      carve_side(c, p->side, cap, true, true, 0, true, true);
-      p->zstart = c.take<uint32_t>((size_t)p->g.nz + 1);
-      p->ra = c.take<double>(std::max(nn, 1u));
-      p->dec = c.take<double>(std::max(nn, 1u));
-    };
-    Carve sizing{nullptr};
-    lay(sizing);
-    int st = pool_take(*dev, sizing.off + 256, &p->mem, &p->mem_bytes);
-    if (st) {
-      delete p;
-      return st;
+    // (attempt 1: the digit sort, where a bucket outgrew its block)
+    for (int attempt = 0; attempt < 2; ++attempt) {
+      auto* p = new hlc_part();
+      p->device = dev_id;
+      p->r_build = r_arcsec;
+      p->g = make_geom(r_arcsec, h_as, n, n, tuned_bins(opts));
+      p->side.plan = plan_sort(n, attempt > 0);
+      p->g.frac_sorted = p->side.plan.K ? 1 : 0;
+      auto lay = [&](Carve& c) {
+        // FP32: sorted (ra, dec) kept with the part for the certification (its
+        // per-source records are scratch)
+        carve_side(c, p->side, cap, true, true, 0, true, true);
+        p->zstart = c.take<uint32_t>((size_t)p->g.nz + 1);
+        p->ra = c.take<double>(std::max(nn, 1u));
+        p->dec = c.take<double>(std::max(nn, 1u));
+      };
+      Carve sizing{nullptr};
+      lay(sizing);
+      int st = pool_take(*dev, sizing.off + 256, &p->mem, &p->mem_bytes);
+      if (st) {
+        delete p;
+        return st;
+      }
+      Carve c{(char*)p->mem};
+      lay(c);
+      // sort scratch and the keygen's per-source records come from the shared
+      // workspace (the part keeps only the sorted entries)
+      SortScratch sc;
+      auto scratch = [&](Carve& c) {
+        carve_sort(c, sc, std::max(cap, 1u), p->side);
+        p->side.srcrad = p->side.plan.K ? nullptr : c.take<double2>(std::max(nn, 1u));
+      };
+      Carve ss{nullptr};
+      scratch(ss);
+      st = ensure_ws(*dev, ss.off + 256);
+      if (st) {
+        release_part(p, true);
+        return st;
+      }
+      Carve cs{(char*)dev->ws};
+      scratch(cs);
+      if (nn && (hipMemcpyAsync(p->ra, ra_deg, (size_t)nn * 8, hipMemcpyDeviceToDevice, s) != hipSuccess ||
+                 hipMemcpyAsync(p->dec, dec_deg, (size_t)nn * 8, hipMemcpyDeviceToDevice, s) != hipSuccess)) {
+        release_part(p, false);
+        return HLC_E_DEVICE;
+      }
+      launch_zero_counters(dev->cnt, s, p->side.bws.fine);
+      st = partition(*dev, p->ra, p->dec, nn, p->g, true, true, true, sc, 1u, p->side, NO_SLOTS, s);
+      p->side.srcrad = nullptr;
+      p->side.bws = BucketWs{};
+      if (st == HLC_OK) {
+        launch_zone_starts(p->side.keys, p->side.cnt, p->g, p->zstart, s);
+        st = read_counters(*dev, s, false);
+      }
+      if (st == HLC_OK && dev->cnt_host->err) st = HLC_E_INVAL;
+      if (st == HLC_OK && !dev->cnt_host->sort_over) {
+        // the entry count is final: keep it on the host side of the part
+        const uint32_t ne = nn + (uint32_t)dev->cnt_host->n_halo;
+        p->side.cnt = DevCount{ne, ne, nullptr};
+        *out = p;
+        return HLC_OK;
+      }
+      release_part(p, st == HLC_OK);
+      if (st != HLC_OK) return st;
     }
-    Carve c{(char*)p->mem};
-    lay(c);
-    // sort scratch and the keygen's per-source records come from the shared
-    // workspace (the part keeps only the sorted entries)
-    SortScratch sc;
-    auto scratch = [&](Carve& c) {
-      carve_sort(c, sc, std::max(cap, 1u));
-      p->side.srcrad = c.take<double2>(std::max(nn, 1u));
-    };
-    Carve ss{nullptr};
-    scratch(ss);
-    st = ensure_ws(*dev, ss.off + 256);
-    if (st) {
-      release_part(p, true);
-      return st;
-    }
-    Carve cs{(char*)dev->ws};
-    scratch(cs);
-    if (nn && (hipMemcpyAsync(p->ra, ra_deg, (size_t)nn * 8, hipMemcpyDeviceToDevice, s) != hipSuccess ||
-               hipMemcpyAsync(p->dec, dec_deg, (size_t)nn * 8, hipMemcpyDeviceToDevice, s) != hipSuccess)) {
-      release_part(p, false);
-      return HLC_E_DEVICE;
-    }
-    launch_zero_counters(dev->cnt, s);
-    st = partition(*dev, p->ra, p->dec, nn, p->g, true, true, true, sc, 1u, p->side, NO_SLOTS, s);
-    p->side.srcrad = nullptr;
-    if (st == HLC_OK) {
-      launch_zone_starts(p->side.keys, p->side.cnt, p->g, p->zstart, s);
-      st = read_counters(*dev, s, false);
-    }
-    if (st == HLC_OK && dev->cnt_host->err) st = HLC_E_INVAL;
-    if (st == HLC_OK) {
-      // the entry count is final: keep it on the host side of the part
-      const uint32_t ne = nn + (uint32_t)dev->cnt_host->n_halo;
-      p->side.cnt = DevCount{ne, ne, nullptr};
-    }
-    if (st != HLC_OK) {
-      release_part(p, false);
-      return st;
-    }
-    *out = p;
-    return HLC_OK;
+    return HLC_E_DEVICE;
   } catch (const std::bad_alloc&) {
     return HLC_E_NOMEM;
   } catch (...) {
@@ -150,6 +155,7 @@ int hlc_xmatch_part(const struct hlc_part* A, const struct hlc_part* B, double r
     const bool prof = (opts->flags & HLC_PROFILE) != 0;
     const bool fp32 = opts->precision == HLC_FP32_RECHECK;
     Geom g = A->g;
+    g.frac_sorted = B->g.frac_sorted;  // (it is B's order that the windows are cut in)
     set_radius(g, r_arcsec);
     if (A->side.n_src == 0 || B->side.n_src == 0) {
       *opts->n_pairs = 0;

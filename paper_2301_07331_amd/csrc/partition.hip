@@ -52,9 +52,13 @@ __global__ void k_copy_pairs(const uint32_t* __restrict__ ks, const uint32_t* __
   }
 }
 
-__global__ void k_zero_counters(Counters* c) {
+__global__ __launch_bounds__(1024) void k_zero_counters(Counters* c, uint32_t* f1, uint32_t* f2) {
   uint32_t* p = reinterpret_cast<uint32_t*>(c);
   for (uint32_t i = threadIdx.x; i < sizeof(Counters) / 4; i += blockDim.x) p[i] = 0u;
+  for (uint32_t* f : {f1, f2})
+    if (f)
+      for (uint32_t i = threadIdx.x; i < BS_FINE / 4; i += blockDim.x)
+        reinterpret_cast<uint4*>(f)[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // ---------------------------------------------------------------------------
@@ -84,14 +88,17 @@ __device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t* total, uin
   return wbase + x - v;
 }
 
-// Each block keys KG_ITEMS * KG_THREADS sources, one radix tile (so that it
-// alone counts the tile's first-pass digits); the Dec-halo copies of the
-// block are placed with a single atomic on the halo counter (one per block
-// keeps the contended counter off the critical path).
-constexpr int KG_ITEMS = 16;
+// Each block keys ITEMS * KG_THREADS sources: 16 a thread before the digit
+// sort, one radix tile (so that it alone counts the tile's first-pass digits);
+// 4 before the bucket sort and 1 before its one-block form, whose catalogues
+// would leave most of the chip idle with 16 (100,000 sources: 13 blocks, 20 to
+// 30 us). The Dec-halo copies of the block are placed with a single atomic on
+// the halo counter (one per block keeps the contended counter off the critical
+// path).
+constexpr int KG_DIGIT = 16, KG_BUCKET = 4, KG_BLOCK = 1;
 constexpr uint32_t KG_THREADS = 512;
-constexpr uint32_t KG_TILE = KG_ITEMS * KG_THREADS;
-static_assert(KG_TILE == (uint32_t)RS_TILE, "a keygen block fills one radix tile");
+static_assert(KG_DIGIT * KG_THREADS == (uint32_t)RS_TILE, "a keygen block fills one radix tile");
+constexpr uint32_t KG_HASH = 512;  // sampled parts of the key space per block
 
 // Besides the keys, each source's (ra, dec) is written in input order as one
 // 16-B record (coalesced), when radec is given: the side's only per-source
@@ -99,6 +106,7 @@ static_assert(KG_TILE == (uint32_t)RS_TILE, "a keygen block fills one radix tile
 // (half the line traffic of two 8-B reads from the caller's arrays) and
 // computes the sorted working record from it; a side that the filter reads
 // in place is read once per entry there, the filter computing the record.
+template <bool SAMPLE, int ITEMS>
 __global__ __launch_bounds__(KG_THREADS) void k_keygen(const double* __restrict__ ra,
                                                 const double* __restrict__ dec, uint32_t n,
                                                 Geom g, int halo, uint32_t err_bit,
@@ -106,12 +114,32 @@ __global__ __launch_bounds__(KG_THREADS) void k_keygen(const double* __restrict_
                                                 uint32_t* __restrict__ vals, Counters* cnt,
                                                 double2* __restrict__ radec, uint32_t* __restrict__ hist,
                                                 uint32_t hist_tiles, int hist_shift, uint32_t hist_full,
-                                                int iota_vals) {
+                                                int iota_vals, KeygenSample ks) {
   constexpr int NW = KG_THREADS / 64;
+  constexpr uint32_t TILE = ITEMS * KG_THREADS;
   __shared__ uint32_t s_w[NW];
   __shared__ unsigned long long s_base;
   __shared__ uint32_t s_h[RS_BINS];
+  // the block's part of the bucket sort's sample: counts by part of the key
+  // space in a small hash table (one word for all was 11 ns an atomic)
+  __shared__ uint32_t s_tag[SAMPLE ? KG_HASH : 1], s_n[SAMPLE ? KG_HASH : 1];
   const uint32_t t = threadIdx.x;
+  if (SAMPLE)
+    for (uint32_t i = t; i < KG_HASH; i += KG_THREADS) {
+      s_tag[i] = 0xffffffffu;
+      s_n[i] = 0u;
+    }
+  auto sample = [&](uint32_t key) {
+    const uint32_t f = bucket_fine(key, ks.mul);
+    for (uint32_t p = 0, h = f & (KG_HASH - 1u); p < 8u; ++p, h = (h + 1u) & (KG_HASH - 1u)) {
+      const uint32_t was = atomicCAS(&s_tag[h], 0xffffffffu, f);
+      if (was == 0xffffffffu || was == f) {
+        atomicAdd(&s_n[h], 1u);
+        return;
+      }
+    }
+    atomicAdd(&ks.fine[f], 1u);
+  };
   // the first radix pass's digit counts of this block's keys (its radix
   // tile), stored whole when the tile holds keygen entries only (tiles below
   // hist_full; the others, which may mix in halo copies, are counted by the
@@ -120,28 +148,28 @@ __global__ __launch_bounds__(KG_THREADS) void k_keygen(const double* __restrict_
   const bool count = hist && rtile < hist_full;
   if (count && t < (uint32_t)RS_BINS) s_h[t] = 0u;
   __syncthreads();
-  const uint32_t base = blockIdx.x * KG_TILE;
-  uint32_t hkey[KG_ITEMS];
+  const uint32_t base = blockIdx.x * TILE;
+  uint32_t hkey[ITEMS];
   uint32_t need = 0;  // bit j: item j has a halo copy
   bool bad = false;
   // every load of the tile in flight before the first use
-  double av[KG_ITEMS], dv[KG_ITEMS];
-  if (base + KG_TILE <= n) {
+  double av[ITEMS], dv[ITEMS];
+  if (base + TILE <= n) {
 #pragma unroll
-    for (int j = 0; j < KG_ITEMS; ++j) {
+    for (int j = 0; j < ITEMS; ++j) {
       av[j] = ra[base + (uint32_t)j * KG_THREADS + t];
       dv[j] = dec[base + (uint32_t)j * KG_THREADS + t];
     }
   } else {
 #pragma unroll
-    for (int j = 0; j < KG_ITEMS; ++j) {
+    for (int j = 0; j < ITEMS; ++j) {
       const uint32_t i = base + (uint32_t)j * KG_THREADS + t;
       av[j] = i < n ? ra[i] : 0.0;
       dv[j] = i < n ? dec[i] : 0.0;
     }
   }
 #pragma unroll
-  for (int j = 0; j < KG_ITEMS; ++j) {
+  for (int j = 0; j < ITEMS; ++j) {
     const uint32_t i = base + (uint32_t)j * KG_THREADS + t;
     hkey[j] = 0u;
     if (i < n) {
@@ -159,6 +187,8 @@ __global__ __launch_bounds__(KG_THREADS) void k_keygen(const double* __restrict_
       keys[i] = key;
       if (!iota_vals) vals[i] = i;  // (else the sort's first pass takes the position)
       if (count) atomicAdd(&s_h[(key >> hist_shift) & 0xffu], 1u);
+      const bool sampled = SAMPLE && (i & ks.mask) == 0u;
+      if (sampled) sample(key);
       if (radec) radec[i] = make_double2(a, d);
       if (halo && ok) {
         // the zone height is >= 2 r, so the padded Dec window reaches at
@@ -168,11 +198,17 @@ __global__ __launch_bounds__(KG_THREADS) void k_keygen(const double* __restrict_
         if (other != z) {
           hkey[j] = make_key(g, other, b) | fr;
           need |= 1u << j;
+          if (sampled) sample(hkey[j]);
         }
       }
     }
   }
   if (bad) atomicOr(&cnt->err, err_bit);
+  if (SAMPLE) {
+    __syncthreads();
+    for (uint32_t i = t; i < KG_HASH; i += KG_THREADS)
+      if (s_n[i]) atomicAdd(&ks.fine[s_tag[i]], s_n[i]);
+  }
   if (count) {
     __syncthreads();
     if (t < (uint32_t)RS_BINS) hist[(size_t)t * hist_tiles + rtile] = s_h[t];
@@ -185,7 +221,7 @@ __global__ __launch_bounds__(KG_THREADS) void k_keygen(const double* __restrict_
   __syncthreads();
   uint64_t pos = (uint64_t)n + s_base + off;
 #pragma unroll
-  for (int j = 0; j < KG_ITEMS; ++j) {
+  for (int j = 0; j < ITEMS; ++j) {
     if (need & (1u << j)) {
       keys[pos] = hkey[j];
       vals[pos] = (base + (uint32_t)j * KG_THREADS + t) | HALO_BIT;
@@ -1265,11 +1301,13 @@ void launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t s) {
   k_fill_u32<<<blocks, 256, 0, s>>>(p, v, n);
 }
 
-void launch_zero_counters(Counters* c, hipStream_t s) { k_zero_counters<<<1, 64, 0, s>>>(c); }
+void launch_zero_counters(Counters* c, hipStream_t s, uint32_t* fine1, uint32_t* fine2) {
+  k_zero_counters<<<1, fine1 || fine2 ? 1024 : 64, 0, s>>>(c, fine1, fine2);
+}
 
 void launch_keygen(const double* ra, const double* dec, uint32_t n, const Geom& g, bool halo,
                    uint32_t err_bit, uint32_t* keys, uint32_t* vals, Counters* cnt, hipStream_t s,
-                   double2* radec, const KeygenHist* kh, bool iota_vals) {
+                   double2* radec, const KeygenHist* kh, bool iota_vals, const KeygenSample* ks) {
   if (n == 0) return;
   uint32_t* hist = nullptr;
   uint32_t tiles = 0, full = 0;
@@ -1281,9 +1319,13 @@ void launch_keygen(const double* ra, const double* dec, uint32_t n, const Geom& 
     // (each of those tiles' counts is stored whole by its block: no clearing)
     hist = full ? kh->counts : nullptr;
   }
-  k_keygen<<<std::max<uint32_t>(1, cdiv(n, KG_TILE)), KG_THREADS, 0, s>>>(
-      ra, dec, n, g, halo ? 1 : 0, err_bit, keys, vals, cnt, radec, hist, tiles, shift,
-      full, iota_vals ? 1 : 0);
+  auto run = [&](auto kernel, uint32_t items, const KeygenSample& k) {
+    kernel<<<cdiv(n, items * KG_THREADS), KG_THREADS, 0, s>>>(ra, dec, n, g, halo ? 1 : 0, err_bit, keys, vals, cnt,
+                                                              radec, hist, tiles, shift, full, iota_vals ? 1 : 0, k);
+  };
+  if (!ks) run(k_keygen<false, KG_DIGIT>, KG_DIGIT, KeygenSample{});
+  else if (ks->fine) run(k_keygen<true, KG_BUCKET>, KG_BUCKET, *ks);
+  else run(k_keygen<false, KG_BLOCK>, KG_BLOCK, *ks);
 }
 
 size_t sort_counts_len(uint32_t n) { return (size_t)RS_BINS * std::max<uint32_t>(1, cdiv(n, RS_TILE)); }

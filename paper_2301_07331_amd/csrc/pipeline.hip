@@ -17,17 +17,30 @@ static bool iota_values(const Geom& g, const Side& sd) {
   return sd.n_cap > 1 && radix_passes(key_bits(g), sort_lo(g)) > 0;
 }
 
+// the parts of the keys in use
+static unsigned long long fine_mul(const Geom& g) {
+  return bucket_fine_mul((unsigned long long)g.nz << (g.rb + g.fb));
+}
+
 void partition_keys(Device& dev, const double* ra, const double* dec, uint32_t n, const Geom& g, bool halo,
                     bool l64, bool l32, const SortScratch& sc, uint32_t err_bit, Side& sd, const Slots& sl,
                     hipStream_t s) {
   sd.n_src = n;
   sd.ra = ra;
   sd.dec = dec;
+  sd.n_cap = halo ? 2 * n : n;
+  if (sd.plan.K) {
+    const unsigned int* none = &dev.cnt->sort_over;
+    const KeygenSample ks{sd.plan.direct ? nullptr : sd.bws.fine, bucket_sample_mask(n, sd.plan), fine_mul(g)};
+    launch_keygen(ra, dec, n, g, halo, err_bit, sc.keys_alt, sc.vals_alt, dev.cnt, s, nullptr, nullptr, true, &ks);
+    mark(dev, sl.keygen, s);
+    sd.cnt = halo ? DevCount{n, 2 * n, &dev.cnt->n_halo, none} : DevCount{n, n, nullptr, none};
+    return;
+  }
   // an odd number of radix passes ends in the scratch pair unless it starts there
   const bool from_alt = (radix_passes(key_bits(g), sort_lo(g)) & 1) != 0;
   uint32_t* kk = from_alt ? sc.keys_alt : sd.keys;
   uint32_t* vv = from_alt ? sc.vals_alt : sd.vals;
-  sd.n_cap = halo ? 2 * n : n;
   // the keygen also counts the first radix pass's digits of the tiles it alone fills
   const KeygenHist kh{sc.counts, sd.n_cap, sort_lo(g)};
   launch_keygen(ra, dec, n, g, halo, err_bit, kk, vv, dev.cnt, s, sd.srcrad, &kh, iota_values(g, sd));
@@ -37,6 +50,16 @@ void partition_keys(Device& dev, const double* ra, const double* dec, uint32_t n
 
 int partition_sort(Device& dev, const Geom& g, bool l64, bool l32, const SortScratch& sc, Side& sd,
                    const Slots& sl, hipStream_t s, hipEvent_t sorted_ev) {
+  if (sd.plan.K) {
+    mark(dev, sl.sort_begin, s);
+    const BucketIn in{sc.keys_alt, sc.vals_alt, sd.ra, sd.dec, sd.n_src, sd.cnt, nullptr, nullptr, nullptr, nullptr};
+    const BucketOut out{sd.keys, sd.vals, sd.r64, sd.r32, sd.radec};
+    launch_bucket_sort(sd.plan, in, out, sd.bws, fine_mul(g), dev.cnt, s);
+    mark(dev, sl.sort, s);
+    if (sorted_ev) HLC_TRY(hipEventRecord(sorted_ev, s));
+    mark(dev, sl.layout, s);
+    return HLC_OK;
+  }
   const int bits = key_bits(g);
   const bool from_alt = (radix_passes(bits, sort_lo(g)) & 1) != 0;
   mark(dev, sl.sort_begin, s);
@@ -226,6 +249,13 @@ void carve_side(Carve& c, Side& sd, uint32_t cap, bool l64, bool l32, uint32_t n
   sd.vals = c.take<uint32_t>(cap);
   sd.r64 = (l64 && layout) ? c.take<Rec64>(cap) : nullptr;
   sd.r32 = (l32 && layout) ? c.take<CellRec32>(cap) : nullptr;
+  if (sd.plan.K) {
+    // the bucket sort carries (ra, dec): kept sorted where the filter computes
+    // its records from them and for the FP32 certification
+    sd.radec = (l32 || !layout) ? c.take<double2>(cap) : nullptr;
+    sd.srcrad = nullptr;
+    return;
+  }
   const bool sorted = l32 && layout && sorted_radec;
   sd.radec = sorted ? c.take<double2>(cap) : nullptr;
   // the one per-source record: (ra, dec), 16 B, written by the keygen; the
@@ -233,6 +263,23 @@ void carve_side(Carve& c, Side& sd, uint32_t cap, bool l64, bool l32, uint32_t n
   // side read in place, and the certification reads it for B's positions
   // (unless they are sorted too)
   sd.srcrad = ((l64 || l32) && n_src) ? c.take<double2>(n_src) : nullptr;
+}
+
+void carve_sort(Carve& c, SortScratch& sc, uint32_t nmax, Side& sd) {
+  if (!sd.plan.K) return carve_sort(c, sc, nmax);
+  nmax = std::max(nmax, 1u);
+  sc.keys_alt = c.take<uint32_t>(nmax);
+  sc.vals_alt = c.take<uint32_t>(nmax);
+  sc.counts = sc.digit_totals = nullptr;
+  sd.bws = BucketWs{};
+  if (sd.plan.direct) return;
+  sd.bws.fine = c.take<uint32_t>(BS_FINE);
+  sd.bws.map = c.take<uint16_t>(BS_FINE);
+  sd.bws.counts = c.take<uint32_t>((size_t)sd.plan.chunks * sd.plan.K);
+  sd.bws.totals = c.take<uint32_t>(sd.plan.K);
+  sd.bws.starts = c.take<uint32_t>((size_t)sd.plan.K + 1);
+  sd.bws.kv = c.take<uint2>(nmax);
+  sd.bws.rd = c.take<double2>(nmax);
 }
 
 void carve_sort(Carve& c, SortScratch& sc, uint32_t nmax) {

@@ -170,13 +170,14 @@ Frame frame_around(const Box& b, double r_arcsec) {
 int slab_match(Device& dev, const double* a_ra, const double* a_dec, uint32_t m, const Side& B,
                uint32_t* zstartB, const Geom& g, double r_arcsec, bool fp32, Caps& caps, hlc_pair* rp,
                double* rs, int64_t cap, int64_t* found, const hlc_opts* o, hipStream_t s) {
-  for (int attempt = 0; attempt < 3; ++attempt) {
+  for (int attempt = 0; attempt < 4; ++attempt) {
     Side A;
+    A.plan = plan_sort(m, caps.digit_sort);
     SortScratch scA;
     MatchWs w;
     auto lay = [&](Carve& c) {
       carve_side(c, A, m, !fp32, fp32, m, false);
-      carve_sort(c, scA, m);
+      carve_sort(c, scA, m, A);
       carve_match_ws(c, w, m, g, caps, false);
     };
     Carve sizing{nullptr};
@@ -185,7 +186,7 @@ int slab_match(Device& dev, const double* a_ra, const double* a_dec, uint32_t m,
     Carve c{(char*)dev.ws};
     lay(c);
     w.zstartB = zstartB;
-    launch_zero_counters(dev.cnt, s);
+    launch_zero_counters(dev.cnt, s, A.bws.fine);
     partition_keys(dev, a_ra, a_dec, m, g, false, !fp32, fp32, scA, 1u, A, NO_SLOTS, s);
     HLC_CHECK(partition_sort(dev, g, !fp32, fp32, scA, A, NO_SLOTS, s));
     match(dev, A, B, g, r_arcsec, fp32, false, false, Radii{nullptr, nullptr, 0.0}, w, rp,
@@ -193,6 +194,10 @@ int slab_match(Device& dev, const double* a_ra, const double* a_dec, uint32_t m,
     HLC_CHECK(read_counters(dev, s, false));
     const Counters& h = *dev.cnt_host;
     if (h.err) return HLC_E_INVAL;
+    if (h.sort_over) {
+      caps.digit_sort = true;  // (the call's later slabs too)
+      continue;
+    }
     if (regrow(dev, h, (uint64_t)cap, caps)) continue;
     *found = (int64_t)h.n_pairs;
     return h.n_pairs > (unsigned long long)cap ? HLC_E_OVERFLOW : HLC_OK;

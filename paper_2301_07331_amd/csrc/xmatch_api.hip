@@ -33,21 +33,26 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   Geom g = make_geom(r_arcsec, tuned_height(o), na, nb, tuned_bins(o), Frame{});
   // (set before A's speculative keygen: the number of radix passes decides
   // which buffer that keygen writes)
-  g.frac_sorted = tuned_fraction_sort(o) || dev->last_crowded ? 1 : 0;
   Side A, B;
+  A.plan = plan_sort(na, caps.digit_sort);
+  B.plan = plan_sort(nb, caps.digit_sort);
+  // B's windows are cut at sub-bin resolution when its sort orders those bits
+  // too: the bucket sort always does
+  auto sub_bins = [&](bool crowded) { return B.plan.K || crowded || tuned_fraction_sort(o) ? 1 : 0; };
+  g.frac_sorted = sub_bins(dev->last_crowded);
   SortScratch sc, scA;
   MatchWs w;
   // FP32: B in the sorted certification layout when the last FP32 call on
   // this device had that many candidates per B entry
-  const bool sorted_b = fp32 && dev->cand_per_b >= SORTED_RADEC_MIN;
+  const bool sorted_b = fp32 && !B.plan.K && dev->cand_per_b >= SORTED_RADEC_MIN;
   auto lay = [&](Carve& c) {
     // A is read in place: the filter gathers its records itself
     if (!self) {
       carve_side(c, A, nA, !fp32, fp32, nA, false);
-      carve_sort(c, scA, nA);
+      carve_sort(c, scA, nA, A);
     }
     carve_side(c, B, 2 * nB, !fp32, fp32, nB, true, sorted_b);
-    carve_sort(c, sc, 2 * nB);
+    carve_sort(c, sc, 2 * nB, B);
     carve_match_ws(c, w, nA, g, caps, true);
   };
   // While the host waits for the sample, A's and B's keys under the
@@ -61,23 +66,24 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
     lay(sizing);
     spec = sizing.off + 256 <= dev->ws_bytes;
   }
+  const bool crowd = !B.plan.K && std::max(na, nb) >= CROWD_MIN;
   FrameQuery fq;
   if (spec) {
     Carve c{(char*)dev->ws};
     lay(c);
     if (prof) HLC_TRY(hipEventRecord(dev->ev[14], s));
-    launch_zero_counters(dev->cnt, s);
+    launch_zero_counters(dev->cnt, s, A.bws.fine, B.bws.fine);
     // B's on the caller's stream, launched first (B's chain is the longer
     // one); the sample and A's keygen beside it on the side stream, where A's
     // sort follows (the places of B's buffers do not depend on the frame
     // either)
     HLC_TRY(hipEventRecord(dev->fork, s));
     HLC_TRY(hipStreamWaitEvent(dev->side, dev->fork, 0));
-    fq = frame_begin(*dev, a_ra, a_dec, na_frame, b_ra, b_dec, nb, dev->side);
+    fq = frame_begin(*dev, a_ra, a_dec, na_frame, b_ra, b_dec, nb, crowd, dev->side);
     partition_keys(*dev, b_ra, b_dec, nB, g, true, !fp32, fp32, sc, 2u, B, slB, s);
     partition_keys(*dev, a_ra, a_dec, nA, g, false, !fp32, fp32, scA, 1u, A, slA, dev->side);
   } else {
-    fq = frame_begin(*dev, a_ra, a_dec, na_frame, b_ra, b_dec, nb, s);
+    fq = frame_begin(*dev, a_ra, a_dec, na_frame, b_ra, b_dec, nb, crowd, s);
   }
   Frame f;
   bool crowded = false;
@@ -86,7 +92,7 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   const int spec_frac = g.frac_sorted;
   dev->last_crowded = crowded;
   g = make_geom(r_arcsec, tuned_height(o), na, nb, tuned_bins(o), f);
-  g.frac_sorted = tuned_fraction_sort(o) || crowded ? 1 : 0;
+  g.frac_sorted = sub_bins(crowded);
   const bool keep = spec && dev->last_full && g.frac_sorted == spec_frac;  // the speculative keys stand
   Carve sizing{nullptr};
   lay(sizing);
@@ -102,7 +108,7 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
       HLC_TRY(hipStreamWaitEvent(s, dev->prepped, 0));
     }
     if (prof) HLC_TRY(hipEventRecord(dev->ev[14], s));
-    launch_zero_counters(dev->cnt, s);
+    launch_zero_counters(dev->cnt, s, A.bws.fine, B.bws.fine);
   }
   // A's partition on the side stream, B's on the caller's, the two keygens
   // side by side; the ranges run on the side stream once both are sorted,
@@ -136,6 +142,12 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
     *o->n_pairs = 0;
     return HLC_E_INVAL;
   }
+  if (h.sort_over) {
+    dev->digit_calls = DIGIT_CALLS;
+    caps.digit_sort = true;
+    *again = true;
+    return HLC_OK;
+  }
   if (regrow(*dev, h, (uint64_t)o->capacity, caps)) {
     *again = true;
     return HLC_OK;
@@ -155,7 +167,11 @@ int xmatch_core(const double* a_ra, const double* a_dec, int64_t na, const doubl
   Device* dev = nullptr;
   HLC_CHECK(get_device(&dev));
   Caps caps = initial_caps(*dev, (uint64_t)(na + nb), (uint64_t)o->capacity, true, false);
-  for (int attempt = 0; attempt < 3; ++attempt) {
+  if (dev->digit_calls > 0) {
+    --dev->digit_calls;
+    caps.digit_sort = true;
+  }
+  for (int attempt = 0; attempt < 4; ++attempt) {
     bool again = false;
     int st = xmatch_impl(a_ra, a_dec, na, b_ra, b_dec, nb, r_arcsec, out_pairs, out_sep, o, caps, &again, rad);
     if (!again) return st;
