@@ -5,7 +5,7 @@
 // their (ra, dec), and each bucket is then ordered in LDS by one block, which
 // writes the sorted keys, indices and working records. The digit sort is nine
 // to twelve launches and a layout that fetches each record from a random
-// line; this is five, or one for a catalogue that one block takes, all 32 bits
+// line; this is four, or one for a catalogue that one block takes, all 32 bits
 // are sorted at no extra cost (the bins' RA fractions included), and the
 // filter reads A's positions along memory. It is bound by its launches and by
 // each block's chain of barriers up to about a million sources. Beyond, the
@@ -16,8 +16,8 @@
 // 2.0M 389 and 395, 2.8M 474 and 505.
 //   k_keygen       keys; every 2^k-th source is counted by which of 8,192 equal
 //                  parts of the key space it lies in
-//   k_bs_map       part -> bucket, about equally filled (one block)
-//   k_bs_count     entries per bucket and chunk, exactly; scanned over chunks
+//   k_bs_count     part -> bucket, about equally filled; entries per bucket and
+//                  chunk, exactly, which are then scanned over the chunks
 //   k_bs_scatter   tiles grouped by bucket in LDS, runs written out
 //   k_bs_bucket    the order in LDS and the output
 // A catalogue that fits one block (8,192 sources) goes straight from its keys
@@ -63,38 +63,39 @@ __device__ inline uint32_t scan_block(uint32_t v, uint32_t* total, uint32_t* s_w
   return base + x - v;
 }
 
-// Bucket of each part of the key space: the sample's running share, times K. An empty sample (no valid source) puts everything into bucket 0.
-__global__ __launch_bounds__(BS_THREADS) void k_bs_map(const uint32_t* __restrict__ fine, uint32_t K,
-                                                       uint16_t* __restrict__ map) {
-  constexpr uint32_t PER = BS_FINE / BS_THREADS;
-  __shared__ uint32_t s_w[BS_THREADS / 64];
-  const uint32_t t = threadIdx.x;
-  uint32_t c[PER], sum = 0u, all;
-#pragma unroll
-  for (uint32_t k = 0; k < PER; ++k) {
-    c[k] = fine[t * PER + k];
-    sum += c[k];
-  }
-  uint32_t run = scan_block<BS_THREADS / 64>(sum, &all, s_w);
-  const double share = all ? (double)K / (double)all : 0.0;
-#pragma unroll
-  for (uint32_t k = 0; k < PER; ++k) {
-    map[t * PER + k] = (uint16_t)min((uint32_t)((double)run * share), K - 1u);
-    run += c[k];
-  }
-}
-
+// Entries per bucket and chunk. Each block first makes the map from parts of
+// the key space to buckets, the sample's running share times K (an empty
+// sample, no valid source, puts everything into bucket 0); block 0 keeps it for
+// the scatter.
 __device__ inline uint32_t chunk_of(uint32_t n) { return (n + gridDim.x - 1u) / gridDim.x; }
 
 __global__ __launch_bounds__(BS_THREADS) void k_bs_count(const uint32_t* __restrict__ keys, DevCount nc,
-                                                         unsigned long long fmul, const uint16_t* __restrict__ map,
-                                                         uint32_t K,
+                                                         unsigned long long fmul, const uint32_t* __restrict__ fine,
+                                                         uint32_t K, uint16_t* __restrict__ map,
                                                          uint32_t* __restrict__ counts) {
+  constexpr uint32_t PER = BS_FINE / BS_THREADS;
   __shared__ uint32_t s_c[BS_BUCKETS];
   __shared__ uint16_t s_map[BS_FINE];
+  __shared__ uint32_t s_w[BS_THREADS / 64];
   const uint32_t t = threadIdx.x, n = nc.get(), chunk = chunk_of(n);
   for (uint32_t d = t; d < K; d += BS_THREADS) s_c[d] = 0u;
-  for (uint32_t f = t; f < BS_FINE; f += BS_THREADS) s_map[f] = map[f];
+  {
+    uint32_t c[PER], sum = 0u, all;
+#pragma unroll
+    for (uint32_t k = 0; k < PER; ++k) {
+      c[k] = fine[t * PER + k];
+      sum += c[k];
+    }
+    uint32_t run = scan_block<BS_THREADS / 64>(sum, &all, s_w);
+    const float share = all ? (float)K / (float)all : 0.0f;
+#pragma unroll
+    for (uint32_t k = 0; k < PER; ++k) {
+      const uint16_t b = (uint16_t)min((uint32_t)((float)run * share), K - 1u);
+      s_map[t * PER + k] = b;
+      if (blockIdx.x == 0) map[t * PER + k] = b;
+      run += c[k];
+    }
+  }
   __syncthreads();
   const uint32_t b0 = min(n, blockIdx.x * chunk), b1 = min(n, b0 + chunk);
 #pragma unroll 8
@@ -449,8 +450,7 @@ void launch_bucket_sort(const BucketPlan& p, const BucketIn& in0, const BucketOu
     else k_bs_bucket<16384, 1024, true><<<1, 1024, 0, s>>>(in, out);
     return;
   }
-  k_bs_map<<<1, BS_THREADS, 0, s>>>(w.fine, p.K, w.map);
-  k_bs_count<<<p.chunks, BS_THREADS, 0, s>>>(in.keys, in.cnt, fine_mul, w.map, p.K, w.counts);
+  k_bs_count<<<p.chunks, BS_THREADS, 0, s>>>(in.keys, in.cnt, fine_mul, w.fine, p.K, w.map, w.counts);
   launch_bucket_scan(w.counts, p.chunks, p.K, w.totals, s);
   k_bs_scatter<<<p.chunks, BS_THREADS, 0, s>>>(in.keys, in.vals, in.ra, in.dec, in.n_src, in.cnt, fine_mul, w.map, p.K,
                                                p.cap, w.counts, w.totals, w.starts, w.kv, w.rd, cnt);

@@ -10,8 +10,11 @@ namespace hlc {
 
 // ---- partition.hip ---------------------------------------------------------
 void launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t s);
-// (and up to two bucket-sort samples of BS_FINE words)
-void launch_zero_counters(Counters* c, hipStream_t s, uint32_t* fine1 = nullptr, uint32_t* fine2 = nullptr);
+// the counters zeroed, and with them up to two bucket-sort samples of BS_FINE
+// words and the counts of a call's regions
+struct Regions;
+void launch_zero_counters(Counters* c, hipStream_t s, uint32_t* fine1 = nullptr, uint32_t* fine2 = nullptr,
+                          const Regions* reg = nullptr);
 struct SortScratch {
   uint32_t* keys_alt;
   uint32_t* vals_alt;
@@ -91,12 +94,6 @@ uint32_t launch_extent(const double* ra1, const double* dec1, uint32_t n1, const
 void launch_zone_tables(const Geom& g, int32_t* zmarg, double* zdelta, hipStream_t s);
 void launch_zone_starts(const uint32_t* keys, const DevCount& n, const Geom& g, uint32_t* zstart,
                         hipStream_t s);
-// the same read from the key index (requires rb + fb >= shift: every zone's
-// first key is then a multiple of the index step); with zmarg, also the zone
-// tables of launch_zone_tables
-void launch_zone_starts_index(const uint32_t* idx, int shift, uint32_t T, const DevCount& n, const Geom& g,
-                              uint32_t* zstart, hipStream_t s, int32_t* zmarg = nullptr,
-                              double* zdelta = nullptr);
 // sorted working records of a side: each entry's source position read from
 // il (the keygen's (ra, dec) records) when given, else from ra and dec
 void launch_layout64(const uint32_t* vals, const DevCount& n, const double* ra, const double* dec,
@@ -111,9 +108,12 @@ void launch_layout_both(const uint32_t* vals, const DevCount& n, const double2* 
 size_t merge_splits_len(uint64_t na_cap, uint64_t nb_cap);
 void launch_merge_lb(const uint32_t* keysA, const DevCount& na, const uint32_t* keysB,
                      const DevCount& nb, uint32_t* splits, uint32_t* lb, hipStream_t s);
-// idx[i] = first position of the sorted keys with key >= i << shift, i < T
-void launch_key_index(const uint32_t* keys, const DevCount& n, int shift, uint32_t T, uint32_t* idx,
-                      hipStream_t s);
+// idx[i] = first position of the sorted keys with key >= i << shift, i < T;
+// with zmarg (requires rb + fb >= shift: every zone's first key is then a
+// multiple of the index step) also the zone tables, and with zstart the zone
+// starts
+void launch_key_index(const uint32_t* keys, const DevCount& n, int shift, uint32_t T, uint32_t* idx, const Geom& g,
+                      uint32_t* zstart, int32_t* zmarg, double* zdelta, hipStream_t s);
 void launch_ranges(const uint32_t* keysA, const DevCount& na, const uint32_t* kidx, int kshift, uint32_t kT,
                    const uint32_t* keysB, const uint32_t* zstartB, const int32_t* zmarg, const double* zdelta,
                    const Geom& g, GroupRanges* out, hipStream_t s);

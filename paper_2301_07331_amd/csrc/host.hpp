@@ -347,6 +347,7 @@ struct MatchWs {
   uint2* band;
   uint64_t band_cap;
   Regions reg;
+  OutArgs out{};  // what the match wrote to (for a band list's decision)
 };
 
 // Sizes of the spill-prone work buffers of a call: the band list, the pair
@@ -377,8 +378,10 @@ OutArgs out_args(hlc_pair* pairs, double* sep, uint64_t cap, uint2* band, uint64
 // events, PROF_FILTER the filter's two events, PROF_ALL every stage's.
 constexpr int PROF_FILTER = 1, PROF_ALL = 2;
 void match(Device& dev, const Side& A, const Side& B, const Geom& g, double r_arcsec, bool fp32,
-           bool skip_halo_a, bool self_only, const Radii& rad, const MatchWs& w, hlc_pair* out_pairs,
+           bool skip_halo_a, bool self_only, const Radii& rad, MatchWs& w, hlc_pair* out_pairs,
            double* out_sep, uint64_t cap, int prof, int filter_items, hipStream_t s, hipStream_t ps = nullptr);
+int finish_match(Device& dev, const Side& A, const Side& B, double r_arcsec, const Radii& rad, const MatchWs& w,
+                 bool prof, hipStream_t s);
 // the profiling level of a call's flags
 inline int prof_level(uint32_t flags) {
   return (flags & HLC_PROFILE) ? PROF_ALL : ((flags & HLC_TIME_FILTER) ? PROF_FILTER : 0);

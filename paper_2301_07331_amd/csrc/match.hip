@@ -248,13 +248,58 @@ __device__ inline void emit_block(const Decision (&v)[ITEMS], const OutArgs& o, 
   }
 }
 
-template <bool F32, bool HP, int ITEMS>
+// The regions' exclusive prefix by a block of its own (k_cand_prefix's, from
+// the counts; block 0 also writes the totals): small calls spare the launch.
+__device__ inline void block_prefix(const Regions& reg, Counters* cnt, unsigned long long* s_pre) {
+  __shared__ unsigned long long s_w[2][NREG / 64];
+  __shared__ unsigned long long s_max[NREG / 64];
+  const uint32_t t = threadIdx.x, lane = t & 63u, w = t >> 6;
+  const unsigned long long f = reg.cfill[t * REG_STRIDE];
+  const unsigned long long v = f < reg.Sc ? f : reg.Sc;
+  unsigned long long x = v, all = f, mx = f;
+  for (int off = 1; off < 64; off <<= 1) {
+    const unsigned long long y = __shfl_up(x, off);
+    if (lane >= (uint32_t)off) x += y;
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    all += __shfl_xor(all, off);
+    const unsigned long long o = __shfl_xor(mx, off);
+    mx = o > mx ? o : mx;
+  }
+  if (lane == 63u) s_w[0][w] = x;
+  if (lane == 0u) {
+    s_w[1][w] = all;
+    s_max[w] = mx;
+  }
+  __syncthreads();
+  for (uint32_t k = 0; k < w; ++k) x += s_w[0][k];
+  s_pre[t + 1] = x;
+  if (t == 0) {
+    s_pre[0] = 0ull;
+    if (blockIdx.x == 0) {
+      unsigned long long tot = 0, m = 0;
+      for (uint32_t k = 0; k < NREG / 64; ++k) {
+        tot += s_w[1][k];
+        m = s_max[k] > m ? s_max[k] : m;
+      }
+      cnt->n_cand = tot;
+      cnt->cand_max = m;
+    }
+  }
+}
+
+template <bool F32, bool HP, int ITEMS, bool PREFIX = false>
 __global__ __launch_bounds__(256) void k_cand(MatchArgs a, OutArgs o) {
   __shared__ unsigned long long s_pre[NREG + 1];
   __shared__ uint32_t s_wc[2][256 / 64];
   __shared__ unsigned long long s_base[2];
   const uint32_t t = threadIdx.x;
-  for (uint32_t k = t; k <= NREG; k += blockDim.x) s_pre[k] = o.reg.cpre[k];
+  if constexpr (PREFIX) {
+    static_assert(NREG == 256, "a thread per region");
+    block_prefix(o.reg, o.cnt, s_pre);
+  } else {
+    for (uint32_t k = t; k <= NREG; k += blockDim.x) s_pre[k] = o.reg.cpre[k];
+  }
   __syncthreads();
   const unsigned long long total = s_pre[NREG];
   const unsigned long long tile = (unsigned long long)ITEMS * blockDim.x;
@@ -765,8 +810,17 @@ void launch_cand(const MatchArgs& a, const OutArgs& o, bool fp32, hipStream_t s)
   // one candidate per thread when the staging is full; the walk is
   // grid-stride beyond that
   const unsigned long long slots = (unsigned long long)NREG * o.reg.Sc;
-  const uint32_t blocks = (uint32_t)std::min<unsigned long long>(
+  uint32_t blocks = (uint32_t)std::min<unsigned long long>(
       CAND_BLOCKS_MAX, std::max(1ull, (slots + 256 * CAND_ITEMS - 1) / (256 * CAND_ITEMS)));
+  // Up to 2M A entries each block makes the regions' prefix itself (2 us of
+  // every block, against a launch of 5 us and its gap); and a small call's
+  // staging is far larger than its candidates.
+  if (o.direct && a.na.cap <= (1u << 21)) {
+    blocks = std::min(blocks, std::max(64u, a.na.cap / 256u));
+    if (fp32) k_cand<true, false, CAND_ITEMS, true><<<blocks, 256, 0, s>>>(a, o);
+    else k_cand<false, false, CAND_ITEMS, true><<<blocks, 256, 0, s>>>(a, o);
+    return;
+  }
   k_cand_prefix<<<1, NREG, 0, s>>>(o.reg, o.direct ? o.cnt : nullptr);
   if (fp32) k_cand<true, false, CAND_ITEMS><<<blocks, 256, 0, s>>>(a, o);
   else if (a.hp_order >= 0) k_cand<false, true, 1><<<blocks, 256, 0, s>>>(a, o);

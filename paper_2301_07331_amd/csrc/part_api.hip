@@ -173,12 +173,12 @@ int hlc_xmatch_part(const struct hlc_part* A, const struct hlc_part* B, double r
       carve_match_ws(c, w, A->side.cnt.cap, g, caps, false);
       w.zstartB = B->zstart;
       if (prof) HLC_TRY(hipEventRecord(dev->ev[0], s));
-      launch_zero_counters(dev->cnt, s);
+      launch_zero_counters(dev->cnt, s, nullptr, nullptr, &w.reg);
       match(*dev, A->side, B->side, g, r_arcsec, fp32, true, false, Radii{nullptr, nullptr, 0.0}, w,
             out_pairs,
             (opts->flags & HLC_NO_SEP) ? nullptr : out_sep_arcsec, (uint64_t)opts->capacity, prof_level(opts->flags),
             tuned_items(opts), s);
-      HLC_CHECK(read_counters(*dev, s, prof));
+      HLC_CHECK(finish_match(*dev, A->side, B->side, r_arcsec, Radii{nullptr, nullptr, 0.0}, w, prof, s));
       const Counters& h = *dev->cnt_host;
       if (regrow(*dev, h, (uint64_t)opts->capacity, caps)) continue;
       fill_stats(h, A->side.n_src, B->side.n_src, B->side.cnt.cap, g);

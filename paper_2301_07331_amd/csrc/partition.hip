@@ -52,9 +52,12 @@ __global__ void k_copy_pairs(const uint32_t* __restrict__ ks, const uint32_t* __
   }
 }
 
-__global__ __launch_bounds__(1024) void k_zero_counters(Counters* c, uint32_t* f1, uint32_t* f2) {
+__global__ __launch_bounds__(1024) void k_zero_counters(Counters* c, uint32_t* f1, uint32_t* f2,
+                                                        unsigned long long* fill, unsigned long long* cfill) {
   uint32_t* p = reinterpret_cast<uint32_t*>(c);
   for (uint32_t i = threadIdx.x; i < sizeof(Counters) / 4; i += blockDim.x) p[i] = 0u;
+  if (fill)
+    for (uint32_t i = threadIdx.x; i < (uint32_t)NREG; i += blockDim.x) fill[i * REG_STRIDE] = cfill[i * REG_STRIDE] = 0ull;
   for (uint32_t* f : {f1, f2})
     if (f)
       for (uint32_t i = threadIdx.x; i < BS_FINE / 4; i += blockDim.x)
@@ -476,21 +479,6 @@ __global__ void k_zone_starts(const uint32_t* __restrict__ keys, DevCount nc, Ge
   zstart[z] = lower_bound_u32(keys, 0, n, make_key(g, z, 0u));
 }
 
-// The same from the coarse key index when a zone's first key is a multiple
-// of the index's step (idx[i] = first position with key >= i << shift).
-// With zmarg, the zone tables as well (one launch for both).
-__global__ void k_zone_starts_index(const uint32_t* __restrict__ idx, int shift, uint32_t T, DevCount nc, Geom g,
-                                    uint32_t* __restrict__ zstart, int32_t* __restrict__ zmarg,
-                                    double* __restrict__ zdelta) {
-  const uint32_t n = nc.get();
-  uint32_t z = blockIdx.x * blockDim.x + threadIdx.x;
-  if (z > (uint32_t)g.nz) return;
-  if (z == (uint32_t)g.nz) { zstart[z] = n; return; }
-  if (zmarg) zone_table_entry(g, (int32_t)z, zmarg, zdelta);
-  const uint32_t i = make_key(g, (int32_t)z, 0u) >> shift;
-  zstart[z] = i < T ? idx[i] : n;
-}
-
 // ---------------------------------------------------------------------------
 // working layouts
 // ---------------------------------------------------------------------------
@@ -710,8 +698,13 @@ __device__ inline uint32_t wave_lower(const uint32_t* __restrict__ keys, uint32_
   return m ? l + (uint32_t)__builtin_ctzll(m) : r;
 }
 
+// With zmarg (a zone's first key is then a multiple of the index's step), the
+// thread of a zone's first slot also writes that zone's tables and, with
+// zstart, its first position (zstart[nz] = n: no key lies there or beyond).
 __global__ __launch_bounds__(KI_THREADS) void k_key_index(const uint32_t* __restrict__ keys, DevCount nc, int shift,
-                                                          uint32_t T, uint32_t* __restrict__ idx) {
+                                                          uint32_t T, uint32_t* __restrict__ idx, Geom g,
+                                                          uint32_t* __restrict__ zstart, int32_t* __restrict__ zmarg,
+                                                          double* __restrict__ zdelta) {
   __shared__ uint32_t s_end[2];
   const uint32_t n = nc.get();
   const uint32_t i0 = blockIdx.x * KI_THREADS, w = threadIdx.x >> 6;
@@ -728,6 +721,14 @@ __global__ __launch_bounds__(KI_THREADS) void k_key_index(const uint32_t* __rest
     if ((keys[mid] >> shift) < i) l = mid + 1u; else r = mid;
   }
   idx[i] = l;
+  if (zmarg) {
+    const int zs = g.rb + g.fb - shift;  // log2 of the slots per zone
+    const uint32_t z = i >> zs;
+    if ((z << zs) == i && z <= (uint32_t)g.nz) {
+      if (zstart) zstart[z] = l;
+      if (z < (uint32_t)g.nz) zone_table_entry(g, (int32_t)z, zmarg, zdelta);
+    }
+  }
 }
 
 // First position in [lo, hi) whose key is >= K (hi if none), searched only
@@ -1301,8 +1302,9 @@ void launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t s) {
   k_fill_u32<<<blocks, 256, 0, s>>>(p, v, n);
 }
 
-void launch_zero_counters(Counters* c, hipStream_t s, uint32_t* fine1, uint32_t* fine2) {
-  k_zero_counters<<<1, fine1 || fine2 ? 1024 : 64, 0, s>>>(c, fine1, fine2);
+void launch_zero_counters(Counters* c, hipStream_t s, uint32_t* fine1, uint32_t* fine2, const Regions* reg) {
+  k_zero_counters<<<1, fine1 || fine2 ? 1024 : 256, 0, s>>>(c, fine1, fine2, reg ? reg->fill : nullptr,
+                                                            reg ? reg->cfill : nullptr);
 }
 
 void launch_keygen(const double* ra, const double* dec, uint32_t n, const Geom& g, bool halo,
@@ -1408,11 +1410,6 @@ void launch_zone_tables(const Geom& g, int32_t* zmarg, double* zdelta, hipStream
   k_zone_tables<<<cdiv((uint32_t)g.nz, 256), 256, 0, s>>>(g, zmarg, zdelta);
 }
 
-void launch_zone_starts_index(const uint32_t* idx, int shift, uint32_t T, const DevCount& n, const Geom& g,
-                              uint32_t* zstart, hipStream_t s, int32_t* zmarg, double* zdelta) {
-  k_zone_starts_index<<<cdiv((uint32_t)g.nz + 1, 256), 256, 0, s>>>(idx, shift, T, n, g, zstart, zmarg, zdelta);
-}
-
 void launch_zone_starts(const uint32_t* keys, const DevCount& n, const Geom& g, uint32_t* zstart,
                         hipStream_t s) {
   k_zone_starts<<<cdiv((uint32_t)g.nz + 1, 256), 256, 0, s>>>(keys, n, g, zstart);
@@ -1446,9 +1443,9 @@ void launch_merge_lb(const uint32_t* keysA, const DevCount& na, const uint32_t* 
   k_merge_lb<<<blocks, MP_THREADS, 0, s>>>(keysA, na, keysB, nb, splits, lb);
 }
 
-void launch_key_index(const uint32_t* keys, const DevCount& n, int shift, uint32_t T, uint32_t* idx,
-                      hipStream_t s) {
-  k_key_index<<<cdiv(T, KI_THREADS), KI_THREADS, 0, s>>>(keys, n, shift, T, idx);
+void launch_key_index(const uint32_t* keys, const DevCount& n, int shift, uint32_t T, uint32_t* idx, const Geom& g,
+                      uint32_t* zstart, int32_t* zmarg, double* zdelta, hipStream_t s) {
+  k_key_index<<<cdiv(T, KI_THREADS), KI_THREADS, 0, s>>>(keys, n, shift, T, idx, g, zstart, zmarg, zdelta);
 }
 
 void launch_ranges(const uint32_t* keysA, const DevCount& na, const uint32_t* kidx, int kshift, uint32_t kT,

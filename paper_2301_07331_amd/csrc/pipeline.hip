@@ -149,7 +149,7 @@ OutArgs out_args(hlc_pair* pairs, double* sep, uint64_t cap, uint2* band, uint64
 
 // Everything after the partition: ranges, match, certification.
 void match(Device& dev, const Side& A, const Side& B, const Geom& g, double r_arcsec, bool fp32,
-           bool skip_halo_a, bool self_only, const Radii& rad, const MatchWs& w,
+           bool skip_halo_a, bool self_only, const Radii& rad, MatchWs& w,
            hlc_pair* out_pairs, double* out_sep, uint64_t cap, int prof, int filter_items, hipStream_t s,
            hipStream_t ps) {
   // zone tables, key index and ranges need only the sorted keys: on ps
@@ -157,33 +157,30 @@ void match(Device& dev, const Side& A, const Side& B, const Geom& g, double r_ar
   if (!ps) ps = s;
   Thresholds th = thresholds(r_arcsec);
   const KeyIndex ki = key_index_dims(g);
-  launch_key_index(B.keys, B.cnt, ki.shift, ki.T, w.kidx, ps);
   const uint32_t* zstart = w.zstartB;
-  // zone starts from the index when zone boundaries fall on its entries (with
-  // the zone tables in the same launch), else searched
-  const bool from_index = !zstart && g.rb + g.fb >= ki.shift;
-  if (from_index) {
-    launch_zone_starts_index(w.kidx, ki.shift, ki.T, B.cnt, g, w.zstart_buf, ps, w.zmarg, w.zdelta);
+  // zone tables (and starts, unless the side keeps them) with the index when
+  // zone boundaries fall on its entries, else by kernels of their own
+  if (g.rb + g.fb >= ki.shift) {
+    launch_key_index(B.keys, B.cnt, ki.shift, ki.T, w.kidx, g, zstart ? nullptr : w.zstart_buf, w.zmarg, w.zdelta, ps);
   } else {
+    launch_key_index(B.keys, B.cnt, ki.shift, ki.T, w.kidx, g, nullptr, nullptr, nullptr, ps);
     launch_zone_tables(g, w.zmarg, w.zdelta, ps);
     if (!zstart) launch_zone_starts(B.keys, B.cnt, g, w.zstart_buf, ps);
   }
   if (!zstart) zstart = w.zstart_buf;
   launch_ranges(A.keys, A.cnt, w.kidx, ki.shift, ki.T, B.keys, zstart, w.zmarg, w.zdelta, g, w.ranges, ps);
   if (prof >= PROF_ALL) (void)hipEventRecord(dev.ev[8], ps);
-  // the candidate regions are cleared before the join, beside the ranges
   // certified pairs go straight into the caller's buffer (no pair regions)
   OutArgs oa = out_args(out_pairs, out_sep, cap, w.band, w.band_cap, w.reg, dev.cnt);
   oa.direct = 1;
-  launch_regions_reset(oa, s);
   // The filter and what follows run on ps after the ranges, once B's records
   // are gathered on s (that event is usually complete by then, so the join
-  // costs no latency); the caller reads the counters on ps.
-  hipStream_t ts = s;
-  if (ps != s) {
+  // costs no latency); the caller reads the counters on ps. (The bucket sort
+  // leaves B's records with its keys: ps waited for them already.)
+  hipStream_t ts = ps;
+  if (ps != s && !B.plan.K) {
     (void)hipEventRecord(dev.prepped, s);
     (void)hipStreamWaitEvent(ps, dev.prepped, 0);
-    ts = ps;
   }
   if (prof) (void)hipEventRecord(dev.ev[13], ts);
   MatchArgs ma{};
@@ -219,14 +216,30 @@ void match(Device& dev, const Side& A, const Side& B, const Geom& g, double r_ar
   launch_filter(ma, oa, fp32, filter_items, ts);
   if (prof) (void)hipEventRecord(dev.ev[9], ts);
   launch_cand(ma, oa, fp32, ts);
-  launch_certify(A.ra, A.dec, B.ra, B.dec, r_arcsec, th.H_lo, th.H_hi, rad, oa, ts);
   if (prof >= PROF_ALL) (void)hipEventRecord(dev.ev[10], ts);
+  w.out = oa;
+}
+
+// The counters of a call whose match ended on s. A band list (pairs within
+// rounding of the radius: rare) is decided first, and the counters read again.
+int finish_match(Device& dev, const Side& A, const Side& B, double r_arcsec, const Radii& rad, const MatchWs& w,
+                 bool prof, hipStream_t s) {
+  HLC_CHECK(read_counters(dev, s, prof));
+  if (dev.cnt_host->n_band == 0) return HLC_OK;
+  const Thresholds th = thresholds(r_arcsec);
+  launch_certify(A.ra, A.dec, B.ra, B.dec, r_arcsec, th.H_lo, th.H_hi, rad, w.out, s);
+  if (prof) (void)hipEventRecord(dev.ev[10], s);
+  return read_counters(dev, s, prof);
 }
 
 size_t carve_match_ws(Carve& c, MatchWs& w, uint32_t na_entries, const Geom& g, const Caps& caps,
                       bool need_zstart) {
   const uint64_t band_cap = caps.band;
   const uint32_t nA = std::max(na_entries, 1u);
+  // first what does not depend on the frame
+  w.band = c.take<uint2>(band_cap);
+  w.band_cap = band_cap;
+  carve_regions(c, w.reg, caps, true);
   w.lb = c.take<uint32_t>(nA);
   w.ranges = c.take<GroupRanges>((nA + GROUP - 1) / GROUP);
   w.zmarg = c.take<int32_t>((size_t)g.nz);
@@ -234,9 +247,6 @@ size_t carve_match_ws(Carve& c, MatchWs& w, uint32_t na_entries, const Geom& g, 
   w.zdelta = c.take<double>((size_t)g.nz);
   w.zstart_buf = need_zstart ? c.take<uint32_t>((size_t)g.nz + 1) : nullptr;
   w.zstartB = nullptr;
-  w.band = c.take<uint2>(band_cap);
-  w.band_cap = band_cap;
-  carve_regions(c, w.reg, caps, true);
   return c.off;
 }
 

@@ -186,12 +186,12 @@ int slab_match(Device& dev, const double* a_ra, const double* a_dec, uint32_t m,
     Carve c{(char*)dev.ws};
     lay(c);
     w.zstartB = zstartB;
-    launch_zero_counters(dev.cnt, s, A.bws.fine);
+    launch_zero_counters(dev.cnt, s, A.bws.fine, nullptr, &w.reg);
     partition_keys(dev, a_ra, a_dec, m, g, false, !fp32, fp32, scA, 1u, A, NO_SLOTS, s);
     HLC_CHECK(partition_sort(dev, g, !fp32, fp32, scA, A, NO_SLOTS, s));
     match(dev, A, B, g, r_arcsec, fp32, false, false, Radii{nullptr, nullptr, 0.0}, w, rp,
           (o->flags & HLC_NO_SEP) ? nullptr : rs, (uint64_t)cap, false, tuned_items(o), s);
-    HLC_CHECK(read_counters(dev, s, false));
+    HLC_CHECK(finish_match(dev, A, B, r_arcsec, Radii{nullptr, nullptr, 0.0}, w, false, s));
     const Counters& h = *dev.cnt_host;
     if (h.err) return HLC_E_INVAL;
     if (h.sort_over) {

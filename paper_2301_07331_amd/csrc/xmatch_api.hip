@@ -61,18 +61,26 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   // buffers do not depend on the frame). They are kept if the sample
   // confirms the frame, else computed again.
   bool spec = false;
-  if (!self && dev->last_full) {
-    Carve sizing{nullptr};
-    lay(sizing);
-    spec = sizing.off + 256 <= dev->ws_bytes;
-  }
+  Carve guess{nullptr};
+  lay(guess);
+  const bool fits = guess.off + 256 <= dev->ws_bytes;
+  if (!self && dev->last_full) spec = fits;
+  // what the counters' clearing reaches: places that depend on the workspace
+  // and the sizes, not on the frame
+  struct Cleared {
+    void* at[4];
+    bool operator==(const Cleared& o) const { return std::memcmp(at, o.at, sizeof at) == 0; }
+  };
+  auto cleared = [&]() { return Cleared{{dev->ws, A.bws.fine, B.bws.fine, w.reg.cfill}}; };
+  auto clear = [&]() { launch_zero_counters(dev->cnt, s, A.bws.fine, B.bws.fine, &w.reg); };
+  Cleared early{};
   const bool crowd = !B.plan.K && std::max(na, nb) >= CROWD_MIN;
   FrameQuery fq;
   if (spec) {
     Carve c{(char*)dev->ws};
     lay(c);
     if (prof) HLC_TRY(hipEventRecord(dev->ev[14], s));
-    launch_zero_counters(dev->cnt, s, A.bws.fine, B.bws.fine);
+    clear();
     // B's on the caller's stream, launched first (B's chain is the longer
     // one); the sample and A's keygen beside it on the side stream, where A's
     // sort follows (the places of B's buffers do not depend on the frame
@@ -84,6 +92,13 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
     partition_keys(*dev, a_ra, a_dec, nA, g, false, !fp32, fp32, scA, 1u, A, slA, dev->side);
   } else {
     fq = frame_begin(*dev, a_ra, a_dec, na_frame, b_ra, b_dec, nb, crowd, s);
+    if (fits && !prof) {
+      // cleared while the host waits for the frame
+      Carve c{(char*)dev->ws};
+      lay(c);
+      early = cleared();
+      clear();
+    }
   }
   Frame f;
   bool crowded = false;
@@ -108,7 +123,7 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
       HLC_TRY(hipStreamWaitEvent(s, dev->prepped, 0));
     }
     if (prof) HLC_TRY(hipEventRecord(dev->ev[14], s));
-    launch_zero_counters(dev->cnt, s, A.bws.fine, B.bws.fine);
+    if (spec || !(early == cleared())) clear();
   }
   // A's partition on the side stream, B's on the caller's, the two keygens
   // side by side; the ranges run on the side stream once both are sorted,
@@ -135,7 +150,7 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   match(*dev, A, B, g, r_arcsec, fp32, self, self, rad, w, out_pairs,
         (o->flags & HLC_NO_SEP) ? nullptr : out_sep, (uint64_t)o->capacity, plevel, tuned_items(o), s, dev->side);
   // the match ended on the side stream (after every kernel of the call on s)
-  HLC_CHECK(read_counters(*dev, dev->side, prof));
+  HLC_CHECK(finish_match(*dev, A, B, r_arcsec, rad, w, prof, dev->side));
 
   const Counters& h = *dev->cnt_host;
   if (h.err) {
