@@ -67,17 +67,22 @@ __device__ inline uint32_t scan_block(uint32_t v, uint32_t* total, uint32_t* s_w
 // the key space to buckets, the sample's running share times K (an empty
 // sample, no valid source, puts everything into bucket 0); block 0 keeps it for
 // the scatter.
-__device__ inline uint32_t chunk_of(uint32_t n) { return (n + gridDim.x - 1u) / gridDim.x; }
-
-__global__ __launch_bounds__(BS_THREADS) void k_bs_count(const uint32_t* __restrict__ keys, DevCount nc,
-                                                         unsigned long long fmul, const uint32_t* __restrict__ fine,
-                                                         uint32_t K, uint16_t* __restrict__ map,
-                                                         uint32_t* __restrict__ counts) {
+// The kernels take one side or two, the second's blocks after the first's.
+__global__ __launch_bounds__(BS_THREADS) void k_bs_count(BucketSide first, BucketSide second,
+                                                         unsigned long long fmul) {
+  const bool other = blockIdx.x >= first.p.chunks;
+  const BucketSide& S = other ? second : first;
+  const uint32_t blk = other ? blockIdx.x - first.p.chunks : blockIdx.x;
+  const uint32_t* __restrict__ keys = S.in.keys;
+  const uint32_t* __restrict__ fine = S.w.fine;
+  uint16_t* __restrict__ map = S.w.map;
+  uint32_t* __restrict__ counts = S.w.counts;
+  const uint32_t K = S.p.K;
   constexpr uint32_t PER = BS_FINE / BS_THREADS;
   __shared__ uint32_t s_c[BS_BUCKETS];
   __shared__ uint16_t s_map[BS_FINE];
   __shared__ uint32_t s_w[BS_THREADS / 64];
-  const uint32_t t = threadIdx.x, n = nc.get(), chunk = chunk_of(n);
+  const uint32_t t = threadIdx.x, n = S.in.cnt.get(), chunk = (n + S.p.chunks - 1u) / S.p.chunks;
   for (uint32_t d = t; d < K; d += BS_THREADS) s_c[d] = 0u;
   {
     uint32_t c[PER], sum = 0u, all;
@@ -92,16 +97,16 @@ __global__ __launch_bounds__(BS_THREADS) void k_bs_count(const uint32_t* __restr
     for (uint32_t k = 0; k < PER; ++k) {
       const uint16_t b = (uint16_t)min((uint32_t)((float)run * share), K - 1u);
       s_map[t * PER + k] = b;
-      if (blockIdx.x == 0) map[t * PER + k] = b;
+      if (blk == 0) map[t * PER + k] = b;
       run += c[k];
     }
   }
   __syncthreads();
-  const uint32_t b0 = min(n, blockIdx.x * chunk), b1 = min(n, b0 + chunk);
+  const uint32_t b0 = min(n, blk * chunk), b1 = min(n, b0 + chunk);
 #pragma unroll 8
   for (uint32_t i = b0 + t; i < b1; i += BS_THREADS) atomicAdd(&s_c[s_map[bucket_fine(keys[i], fmul)]], 1u);
   __syncthreads();
-  for (uint32_t d = t; d < K; d += BS_THREADS) counts[(size_t)blockIdx.x * K + d] = s_c[d];
+  for (uint32_t d = t; d < K; d += BS_THREADS) counts[(size_t)blk * K + d] = s_c[d];
 }
 
 // A chunk's entries into their buckets, a tile at a time, as (key, index) and
@@ -110,11 +115,22 @@ __global__ __launch_bounds__(BS_THREADS) void k_bs_count(const uint32_t* __restr
 // words) and written out in runs. Entries from n_src on are Dec-halo copies:
 // their index is in vals, their position read by it. starts[0..K] are the
 // buckets' first places.
-__global__ __launch_bounds__(BS_THREADS) void k_bs_scatter(
-    const uint32_t* __restrict__ keys, const uint32_t* __restrict__ vals, const double* __restrict__ ra,
-    const double* __restrict__ dec, uint32_t n_src, DevCount nc, unsigned long long fmul, const uint16_t* __restrict__ map,
-    uint32_t K, uint32_t cap, const uint32_t* __restrict__ counts, const uint32_t* __restrict__ totals,
-    uint32_t* __restrict__ starts, uint2* __restrict__ kv, double2* __restrict__ rd, Counters* cnt) {
+__global__ __launch_bounds__(BS_THREADS) void k_bs_scatter(BucketSide first, BucketSide second,
+                                                           unsigned long long fmul, Counters* cnt) {
+  const bool other = blockIdx.x >= first.p.chunks;
+  const BucketSide& S = other ? second : first;
+  const uint32_t blk = other ? blockIdx.x - first.p.chunks : blockIdx.x;
+  const uint32_t* __restrict__ keys = S.in.keys;
+  const uint32_t* __restrict__ vals = S.in.vals;
+  const double* __restrict__ ra = S.in.ra;
+  const double* __restrict__ dec = S.in.dec;
+  const uint16_t* __restrict__ map = S.w.map;
+  const uint32_t* __restrict__ counts = S.w.counts;
+  const uint32_t* __restrict__ totals = S.w.totals;
+  uint32_t* __restrict__ starts = S.w.starts;
+  uint2* __restrict__ kv = S.w.kv;
+  double2* __restrict__ rd = S.w.rd;
+  const uint32_t n_src = S.in.n_src, K = S.p.K, cap = S.p.cap;
   constexpr uint32_t NW = BS_THREADS / 64, PER = BS_TILE / BS_THREADS, BPT = BS_BUCKETS / BS_THREADS;
   __shared__ double2 s_rd[BS_TILE];
   __shared__ uint16_t s_map[BS_FINE];
@@ -124,7 +140,7 @@ __global__ __launch_bounds__(BS_THREADS) void k_bs_scatter(
   __shared__ uint16_t s_start[BS_BUCKETS];
   __shared__ uint32_t s_w[NW];
   uint2* s_kv = reinterpret_cast<uint2*>(s_rd);
-  const uint32_t t = threadIdx.x, n = nc.get(), chunk = chunk_of(n);
+  const uint32_t t = threadIdx.x, n = S.in.cnt.get(), chunk = (n + S.p.chunks - 1u) / S.p.chunks;
   // thread t's buckets are t BPT .. t BPT + BPT - 1
   auto scan_buckets = [&](const uint32_t (&c)[BPT], uint32_t (&st)[BPT]) {
     uint32_t sum = 0u, all;
@@ -153,16 +169,16 @@ __global__ __launch_bounds__(BS_THREADS) void k_bs_scatter(
     for (uint32_t u = 0; u < BPT; ++u) {
       const uint32_t d = t * BPT + u;
       if (d < K) {
-        s_goff[d] = st[u] + counts[(size_t)blockIdx.x * K + d];
-        if (blockIdx.x == 0) starts[d] = st[u];
+        s_goff[d] = st[u] + counts[(size_t)blk * K + d];
+        if (blk == 0) starts[d] = st[u];
       }
     }
-    if (blockIdx.x == 0) {
+    if (blk == 0) {
       if (over) atomicOr(&cnt->sort_over, 1u);
       if (t == 0) starts[K] = n;
     }
   }
-  const uint32_t b0 = min(n, blockIdx.x * chunk), b1 = min(n, b0 + chunk);
+  const uint32_t b0 = min(n, blk * chunk), b1 = min(n, b0 + chunk);
   uint32_t key[PER], val[PER];
   double pa[PER], pd[PER];
   auto load = [&](uint32_t base) {
@@ -229,14 +245,18 @@ __global__ __launch_bounds__(BS_THREADS) void k_bs_scatter(
   }
 }
 
-// Bucket blockIdx.x in order. The keys are binned in BINS bins evenly between
+// A bucket in order. The keys are binned in BINS bins evenly between
 // the smallest and the largest; where a bin holds more than BIN_FULL, each of
 // those again in as many bins evenly as it holds keys, so that a clump, which
 // fills few of the first, is spread over the second. A key's rank is its bin's
 // start and the number of smaller keys in the bin. Keys, indices and places pass through LDS
 // to leave in whole lines; the (ra, dec) are read from the bucket's stretch.
 template <uint32_t CAP, uint32_t T, bool DIRECT>
-__global__ __launch_bounds__(T, CAP <= 4096 ? 8 : 4) void k_bs_bucket(BucketIn in, BucketOut out) {
+__global__ __launch_bounds__(T, CAP <= 4096 ? 8 : 4) void k_bs_bucket(BucketSide first, BucketSide second) {
+  const bool other = blockIdx.x >= first.p.K;
+  const BucketIn& in = other ? second.in : first.in;
+  const BucketOut& out = other ? second.out : first.out;
+  const uint32_t blk = other ? blockIdx.x - first.p.K : blockIdx.x;
   constexpr uint32_t PER = CAP / T, BINS = CAP > 4096 ? 4096 : 2048, NW = T / 64;
   __shared__ uint32_t s_key[CAP];
   __shared__ uint32_t s_c1[BINS + 1];
@@ -250,8 +270,8 @@ __global__ __launch_bounds__(T, CAP <= 4096 ? 8 : 4) void k_bs_bucket(BucketIn i
     m = in.cnt.get();
   } else {
     if (in.over && *in.over) return;
-    s0 = in.starts[blockIdx.x];
-    m = in.starts[blockIdx.x + 1] - s0;
+    s0 = in.starts[blk];
+    m = in.starts[blk + 1] - s0;
   }
   if (m == 0u || m > CAP) return;
   uint32_t key[PER], val[PER];
@@ -442,23 +462,26 @@ uint32_t bucket_sample_mask(uint32_t n, const BucketPlan& p) {
   return stride - 1u;
 }
 
-void launch_bucket_sort(const BucketPlan& p, const BucketIn& in0, const BucketOut& out, const BucketWs& w,
-                        unsigned long long fine_mul, Counters* cnt, hipStream_t s) {
-  BucketIn in = in0;
-  if (p.direct) {
-    if (p.cap == 4096u) k_bs_bucket<4096, 1024, true><<<1, 1024, 0, s>>>(in, out);
-    else k_bs_bucket<16384, 1024, true><<<1, 1024, 0, s>>>(in, out);
+void launch_bucket_sort(const BucketSide& a, const BucketSide* b, unsigned long long fine_mul, Counters* cnt,
+                        hipStream_t s) {
+  BucketSide first = a, second = b ? *b : BucketSide{};
+  for (BucketSide* x : {&first, &second}) {
+    x->in.starts = x->w.starts;
+    x->in.kv = x->w.kv;
+    x->in.rd = x->w.rd;
+    x->in.over = &cnt->sort_over;
+  }
+  const uint32_t K = first.p.K + second.p.K, chunks = first.p.chunks + second.p.chunks;
+  if (first.p.direct) {
+    if (first.p.cap == 4096u) k_bs_bucket<4096, 1024, true><<<K, 1024, 0, s>>>(first, second);
+    else k_bs_bucket<16384, 1024, true><<<K, 1024, 0, s>>>(first, second);
     return;
   }
-  k_bs_count<<<p.chunks, BS_THREADS, 0, s>>>(in.keys, in.cnt, fine_mul, w.fine, p.K, w.map, w.counts);
-  launch_bucket_scan(w.counts, p.chunks, p.K, w.totals, s);
-  k_bs_scatter<<<p.chunks, BS_THREADS, 0, s>>>(in.keys, in.vals, in.ra, in.dec, in.n_src, in.cnt, fine_mul, w.map, p.K,
-                                               p.cap, w.counts, w.totals, w.starts, w.kv, w.rd, cnt);
-  in.starts = w.starts;
-  in.kv = w.kv;
-  in.rd = w.rd;
-  in.over = &cnt->sort_over;
-  k_bs_bucket<BS_CAP, 512, false><<<p.K, 512, 0, s>>>(in, out);
+  k_bs_count<<<chunks, BS_THREADS, 0, s>>>(first, second, fine_mul);
+  launch_bucket_scan(BucketScan{first.w.counts, first.p.chunks, first.p.K, first.w.totals},
+                     BucketScan{second.w.counts, second.p.chunks, second.p.K, second.w.totals}, s);
+  k_bs_scatter<<<chunks, BS_THREADS, 0, s>>>(first, second, fine_mul, cnt);
+  k_bs_bucket<BS_CAP, 512, false><<<K, 512, 0, s>>>(first, second);
 }
 
 }  // namespace hlc

@@ -48,6 +48,17 @@ void launch_keygen(const double* ra, const double* dec, uint32_t n, const Geom& 
                    uint32_t err_bit, uint32_t* keys, uint32_t* vals, Counters* cnt, hipStream_t s,
                    double2* radec = nullptr, const KeygenHist* kh = nullptr, bool iota_vals = false,
                    const KeygenSample* ks = nullptr);
+// both sides of a call by one kernel, ahead of the bucket sort: both with a
+// sample or neither (indices are left to the sort, no (ra, dec) records)
+struct KeygenSide {
+  const double *ra, *dec;
+  uint32_t n;
+  int halo;
+  uint32_t err_bit;
+  uint32_t *keys, *vals;
+  KeygenSample ks;
+};
+void launch_keygen_both(const KeygenSide& a, const KeygenSide& b, const Geom& g, Counters* cnt, hipStream_t s);
 // tiles of the first pass whose counts a keygen of n sources fills
 uint32_t keygen_hist_tiles(uint32_t n);
 
@@ -162,11 +173,27 @@ struct BucketOut {
   CellRec32* r32;
   double2* radec;
 };
-void launch_bucket_sort(const BucketPlan& p, const BucketIn& in, const BucketOut& out, const BucketWs& w,
-                        unsigned long long fine_mul, Counters* cnt, hipStream_t s);
+struct BucketSide {
+  BucketPlan p;
+  BucketIn in;
+  BucketOut out;
+  BucketWs w;
+};
+// one side, or both of the same form (b not null) in the same launches
+inline bool same_form(const BucketPlan& a, const BucketPlan& b) {
+  return a.K && b.K && a.direct == b.direct && a.cap == b.cap;
+}
+void launch_bucket_sort(const BucketSide& a, const BucketSide* b, unsigned long long fine_mul, Counters* cnt,
+                        hipStream_t s);
 // per bucket of K, the exclusive scan of counts[chunk * K + bucket] over the
-// chunks (at most 256), in place, and the totals (pair_order.hip)
-void launch_bucket_scan(uint32_t* counts, uint32_t chunks, uint32_t K, uint32_t* totals, hipStream_t s);
+// chunks (at most 256), in place, and the totals, for one table or two
+// (pair_order.hip)
+struct BucketScan {
+  uint32_t* counts;
+  uint32_t chunks, K;
+  uint32_t* totals;
+};
+void launch_bucket_scan(const BucketScan& a, const BucketScan& b, hipStream_t s);
 
 // ---- pair_order.hip --------------------------------------------------------
 // pairs (and separations, if sep) ordered by (a, b), a < na

@@ -309,6 +309,13 @@ inline void mark(Device& dev, int slot, hipStream_t s) {
 void partition_keys(Device& dev, const double* ra, const double* dec, uint32_t n, const Geom& g, bool halo,
                     bool l64, bool l32, const SortScratch& sc, uint32_t err_bit, Side& sd, const Slots& sl,
                     hipStream_t s);
+// Both sides of a call whose bucket sorts have the same form, in the same
+// launches: their keys, then their order.
+void partition_keys_both(Device& dev, const double* a_ra, const double* a_dec, uint32_t na, const SortScratch& scA,
+                         Side& A, const double* b_ra, const double* b_dec, uint32_t nb, const SortScratch& scB,
+                         Side& B, const Geom& g, hipStream_t s);
+void partition_sort_both(Device& dev, const Geom& g, const SortScratch& scA, Side& A, const SortScratch& scB, Side& B,
+                         hipStream_t s);
 int partition_sort(Device& dev, const Geom& g, bool l64, bool l32, const SortScratch& sc, Side& sd,
                    const Slots& sl, hipStream_t s, hipEvent_t sorted_ev = nullptr);
 int partition(Device& dev, const double* ra, const double* dec, uint32_t n, const Geom& g, bool halo,

@@ -141,10 +141,15 @@ int noalloc_impl(const double* a_ra, const double* a_dec, int64_t na, const doub
     Carve c{static_cast<char*>(ctx.ws)};
     lay(c);
     launch_zero_counters(ctx.cnt, s, A.bws.fine, B.bws.fine, &w.reg);
-    partition_keys(ctx, a_ra, a_dec, nA, g, false, !fp32, fp32, scA, 1u, A, NO_SLOTS, s);
-    partition_keys(ctx, b_ra, b_dec, nB, g, true, !fp32, fp32, scB, 2u, B, NO_SLOTS, s);
-    HLC_CHECK(partition_sort(ctx, g, !fp32, fp32, scA, A, NO_SLOTS, s));
-    HLC_CHECK(partition_sort(ctx, g, !fp32, fp32, scB, B, NO_SLOTS, s));
+    if (same_form(A.plan, B.plan)) {
+      partition_keys_both(ctx, a_ra, a_dec, nA, scA, A, b_ra, b_dec, nB, scB, B, g, s);
+      partition_sort_both(ctx, g, scA, A, scB, B, s);
+    } else {
+      partition_keys(ctx, a_ra, a_dec, nA, g, false, !fp32, fp32, scA, 1u, A, NO_SLOTS, s);
+      partition_keys(ctx, b_ra, b_dec, nB, g, true, !fp32, fp32, scB, 2u, B, NO_SLOTS, s);
+      HLC_CHECK(partition_sort(ctx, g, !fp32, fp32, scA, A, NO_SLOTS, s));
+      HLC_CHECK(partition_sort(ctx, g, !fp32, fp32, scB, B, NO_SLOTS, s));
+    }
     match(ctx, A, B, g, r_arcsec, fp32, false, false, Radii{nullptr, nullptr, 0.0}, w, out_pairs, sep,
           (uint64_t)o->capacity, false, tuned_items(o), s);
     HLC_CHECK(finish_match(ctx, A, B, r_arcsec, Radii{nullptr, nullptr, 0.0}, w, false, s));

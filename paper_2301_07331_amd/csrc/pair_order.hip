@@ -283,12 +283,17 @@ __global__ __launch_bounds__(PO_CHUNK_THREADS) void k_po_count(const uint2* __re
 // Per bucket, the exclusive scan over the chunks (in place) and the total.
 // A block takes 64 buckets: 16 rows of threads, each summing a sixteenth of
 // the chunks, all loads in flight at once.
-__global__ __launch_bounds__(PO_CHUNK_THREADS) void k_po_scan(uint32_t* __restrict__ counts, uint32_t nchunks,
-                                                              uint32_t K, uint32_t* __restrict__ totals) {
+// (Two tables' blocks follow each other.)
+__global__ __launch_bounds__(PO_CHUNK_THREADS) void k_po_scan(BucketScan first, BucketScan second) {
   constexpr uint32_t ROWS = PO_CHUNK_THREADS / 64, PER = PO_CHUNKS / ROWS;
   __shared__ uint32_t s_sum[ROWS][64];
   const uint32_t l = threadIdx.x & 63u, row = threadIdx.x >> 6;
-  const uint32_t d = blockIdx.x * 64u + l;
+  const uint32_t nfirst = (first.K + 63u) / 64u;
+  const bool other = blockIdx.x >= nfirst;
+  uint32_t* const counts = other ? second.counts : first.counts;
+  uint32_t* const totals = other ? second.totals : first.totals;
+  const uint32_t K = other ? second.K : first.K, nchunks = other ? second.chunks : first.chunks;
+  const uint32_t d = (blockIdx.x - (other ? nfirst : 0u)) * 64u + l;
   uint32_t c[PER], sum = 0u;
 #pragma unroll
   for (uint32_t k = 0; k < PER; ++k) {
@@ -577,8 +582,8 @@ uint32_t block_cap(uint32_t n, const PairOrderSizes& z) {
 
 }  // namespace
 
-void launch_bucket_scan(uint32_t* counts, uint32_t chunks, uint32_t K, uint32_t* totals, hipStream_t s) {
-  k_po_scan<<<(K + 63) / 64, PO_CHUNK_THREADS, 0, s>>>(counts, chunks, K, totals);
+void launch_bucket_scan(const BucketScan& a, const BucketScan& b, hipStream_t s) {
+  k_po_scan<<<(a.K + 63) / 64 + (b.K + 63) / 64, PO_CHUNK_THREADS, 0, s>>>(a, b);
 }
 
 PairOrderSizes pair_order_sizes(uint32_t n, uint64_t na) {
@@ -599,7 +604,7 @@ void launch_pair_order(uint2* pairs, double* sep, uint32_t n, uint64_t na, const
   const uint64_t mul = ((uint64_t)z.K << 32) / na;
   const uint32_t chunk = (n + z.chunks - 1) / z.chunks;
   k_po_count<<<z.chunks, PO_CHUNK_THREADS, 0, s>>>(pairs, n, chunk, mul, z.K, w.counts);
-  launch_bucket_scan(w.counts, z.chunks, z.K, w.totals, s);
+  launch_bucket_scan(BucketScan{w.counts, z.chunks, z.K, w.totals}, BucketScan{}, s);
   k_po_scatter<<<z.chunks, PO_CHUNK_THREADS, 0, s>>>(pairs, sep, n, chunk, mul, z.K, block_cap(n, z), w.counts,
                                                      w.totals, w.starts, w.rec, over);
   switch (block_cap(n, z)) {

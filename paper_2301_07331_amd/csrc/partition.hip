@@ -110,14 +110,11 @@ constexpr uint32_t KG_HASH = 512;  // sampled parts of the key space per block
 // computes the sorted working record from it; a side that the filter reads
 // in place is read once per entry there, the filter computing the record.
 template <bool SAMPLE, int ITEMS>
-__global__ __launch_bounds__(KG_THREADS) void k_keygen(const double* __restrict__ ra,
-                                                const double* __restrict__ dec, uint32_t n,
-                                                Geom g, int halo, uint32_t err_bit,
-                                                uint32_t* __restrict__ keys,
-                                                uint32_t* __restrict__ vals, Counters* cnt,
-                                                double2* __restrict__ radec, uint32_t* __restrict__ hist,
-                                                uint32_t hist_tiles, int hist_shift, uint32_t hist_full,
-                                                int iota_vals, KeygenSample ks) {
+__device__ inline void keygen_block(uint32_t blk, const double* __restrict__ ra, const double* __restrict__ dec,
+                                    uint32_t n, const Geom& g, int halo, uint32_t err_bit,
+                                    uint32_t* __restrict__ keys, uint32_t* __restrict__ vals, Counters* cnt,
+                                    double2* __restrict__ radec, uint32_t* __restrict__ hist, uint32_t hist_tiles,
+                                    int hist_shift, uint32_t hist_full, int iota_vals, const KeygenSample& ks) {
   constexpr int NW = KG_THREADS / 64;
   constexpr uint32_t TILE = ITEMS * KG_THREADS;
   __shared__ uint32_t s_w[NW];
@@ -147,11 +144,11 @@ __global__ __launch_bounds__(KG_THREADS) void k_keygen(const double* __restrict_
   // tile), stored whole when the tile holds keygen entries only (tiles below
   // hist_full; the others, which may mix in halo copies, are counted by the
   // pass's own histogram kernel)
-  const uint32_t rtile = blockIdx.x;
+  const uint32_t rtile = blk;
   const bool count = hist && rtile < hist_full;
   if (count && t < (uint32_t)RS_BINS) s_h[t] = 0u;
   __syncthreads();
-  const uint32_t base = blockIdx.x * TILE;
+  const uint32_t base = blk * TILE;
   uint32_t hkey[ITEMS];
   uint32_t need = 0;  // bit j: item j has a halo copy
   bool bad = false;
@@ -231,6 +228,30 @@ __global__ __launch_bounds__(KG_THREADS) void k_keygen(const double* __restrict_
       ++pos;
     }
   }
+}
+
+template <bool SAMPLE, int ITEMS>
+__global__ __launch_bounds__(KG_THREADS) void k_keygen(const double* __restrict__ ra,
+                                                const double* __restrict__ dec, uint32_t n,
+                                                Geom g, int halo, uint32_t err_bit,
+                                                uint32_t* __restrict__ keys,
+                                                uint32_t* __restrict__ vals, Counters* cnt,
+                                                double2* __restrict__ radec, uint32_t* __restrict__ hist,
+                                                uint32_t hist_tiles, int hist_shift, uint32_t hist_full,
+                                                int iota_vals, KeygenSample ks) {
+  keygen_block<SAMPLE, ITEMS>(blockIdx.x, ra, dec, n, g, halo, err_bit, keys, vals, cnt, radec, hist, hist_tiles,
+                              hist_shift, hist_full, iota_vals, ks);
+}
+
+// Both sides of a call in one launch (before the bucket sort): A's blocks, then
+// B's.
+template <bool SAMPLE, int ITEMS>
+__global__ __launch_bounds__(KG_THREADS) void k_keygen_both(KeygenSide a, KeygenSide b, uint32_t a_blocks, Geom g,
+                                                            Counters* cnt) {
+  const bool second = blockIdx.x >= a_blocks;
+  const KeygenSide& k = second ? b : a;
+  keygen_block<SAMPLE, ITEMS>(second ? blockIdx.x - a_blocks : blockIdx.x, k.ra, k.dec, k.n, g, k.halo, k.err_bit,
+                              k.keys, k.vals, cnt, nullptr, nullptr, 0u, 0, 0u, 1, k.ks);
 }
 
 // ---------------------------------------------------------------------------
@@ -1328,6 +1349,13 @@ void launch_keygen(const double* ra, const double* dec, uint32_t n, const Geom& 
   if (!ks) run(k_keygen<false, KG_DIGIT>, KG_DIGIT, KeygenSample{});
   else if (ks->fine) run(k_keygen<true, KG_BUCKET>, KG_BUCKET, *ks);
   else run(k_keygen<false, KG_BLOCK>, KG_BLOCK, *ks);
+}
+
+void launch_keygen_both(const KeygenSide& a, const KeygenSide& b, const Geom& g, Counters* cnt, hipStream_t s) {
+  const uint32_t per = (a.ks.fine ? KG_BUCKET : KG_BLOCK) * KG_THREADS;
+  const uint32_t ab = cdiv(a.n, per), bb = cdiv(b.n, per);
+  if (a.ks.fine) k_keygen_both<true, KG_BUCKET><<<ab + bb, KG_THREADS, 0, s>>>(a, b, ab, g, cnt);
+  else k_keygen_both<false, KG_BLOCK><<<ab + bb, KG_THREADS, 0, s>>>(a, b, ab, g, cnt);
 }
 
 size_t sort_counts_len(uint32_t n) { return (size_t)RS_BINS * std::max<uint32_t>(1, cdiv(n, RS_TILE)); }

@@ -22,6 +22,44 @@ static unsigned long long fine_mul(const Geom& g) {
   return bucket_fine_mul((unsigned long long)g.nz << (g.rb + g.fb));
 }
 
+static KeygenSample keygen_sample(const Side& sd, const Geom& g) {
+  return KeygenSample{sd.plan.direct ? nullptr : sd.bws.fine, bucket_sample_mask(sd.n_src, sd.plan), fine_mul(g)};
+}
+// entries of a bucket-sorted side: none if a bucket outgrew its block
+static DevCount sort_count(Device& dev, uint32_t n, bool halo) {
+  const unsigned int* none = &dev.cnt->sort_over;
+  return halo ? DevCount{n, 2 * n, &dev.cnt->n_halo, none} : DevCount{n, n, nullptr, none};
+}
+static BucketSide bucket_side(const Side& sd, const SortScratch& sc) {
+  return BucketSide{sd.plan,
+                    BucketIn{sc.keys_alt, sc.vals_alt, sd.ra, sd.dec, sd.n_src, sd.cnt, nullptr, nullptr, nullptr,
+                             nullptr},
+                    BucketOut{sd.keys, sd.vals, sd.r64, sd.r32, sd.radec}, sd.bws};
+}
+
+void partition_keys_both(Device& dev, const double* a_ra, const double* a_dec, uint32_t na, const SortScratch& scA,
+                         Side& A, const double* b_ra, const double* b_dec, uint32_t nb, const SortScratch& scB,
+                         Side& B, const Geom& g, hipStream_t s) {
+  A.n_src = A.n_cap = na;
+  A.ra = a_ra;
+  A.dec = a_dec;
+  A.cnt = sort_count(dev, na, false);
+  B.n_src = nb;
+  B.n_cap = 2 * nb;
+  B.ra = b_ra;
+  B.dec = b_dec;
+  B.cnt = sort_count(dev, nb, true);
+  launch_keygen_both(KeygenSide{a_ra, a_dec, na, 0, 1u, scA.keys_alt, scA.vals_alt, keygen_sample(A, g)},
+                     KeygenSide{b_ra, b_dec, nb, 1, 2u, scB.keys_alt, scB.vals_alt, keygen_sample(B, g)}, g, dev.cnt,
+                     s);
+}
+
+void partition_sort_both(Device& dev, const Geom& g, const SortScratch& scA, Side& A, const SortScratch& scB, Side& B,
+                         hipStream_t s) {
+  const BucketSide b = bucket_side(B, scB);
+  launch_bucket_sort(bucket_side(A, scA), &b, fine_mul(g), dev.cnt, s);
+}
+
 void partition_keys(Device& dev, const double* ra, const double* dec, uint32_t n, const Geom& g, bool halo,
                     bool l64, bool l32, const SortScratch& sc, uint32_t err_bit, Side& sd, const Slots& sl,
                     hipStream_t s) {
@@ -30,11 +68,10 @@ void partition_keys(Device& dev, const double* ra, const double* dec, uint32_t n
   sd.dec = dec;
   sd.n_cap = halo ? 2 * n : n;
   if (sd.plan.K) {
-    const unsigned int* none = &dev.cnt->sort_over;
-    const KeygenSample ks{sd.plan.direct ? nullptr : sd.bws.fine, bucket_sample_mask(n, sd.plan), fine_mul(g)};
+    const KeygenSample ks = keygen_sample(sd, g);
     launch_keygen(ra, dec, n, g, halo, err_bit, sc.keys_alt, sc.vals_alt, dev.cnt, s, nullptr, nullptr, true, &ks);
     mark(dev, sl.keygen, s);
-    sd.cnt = halo ? DevCount{n, 2 * n, &dev.cnt->n_halo, none} : DevCount{n, n, nullptr, none};
+    sd.cnt = sort_count(dev, n, halo);
     return;
   }
   // an odd number of radix passes ends in the scratch pair unless it starts there
@@ -52,9 +89,7 @@ int partition_sort(Device& dev, const Geom& g, bool l64, bool l32, const SortScr
                    const Slots& sl, hipStream_t s, hipEvent_t sorted_ev) {
   if (sd.plan.K) {
     mark(dev, sl.sort_begin, s);
-    const BucketIn in{sc.keys_alt, sc.vals_alt, sd.ra, sd.dec, sd.n_src, sd.cnt, nullptr, nullptr, nullptr, nullptr};
-    const BucketOut out{sd.keys, sd.vals, sd.r64, sd.r32, sd.radec};
-    launch_bucket_sort(sd.plan, in, out, sd.bws, fine_mul(g), dev.cnt, s);
+    launch_bucket_sort(bucket_side(sd, sc), nullptr, fine_mul(g), dev.cnt, s);
     mark(dev, sl.sort, s);
     if (sorted_ev) HLC_TRY(hipEventRecord(sorted_ev, s));
     mark(dev, sl.layout, s);

@@ -45,6 +45,11 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   // FP32: B in the sorted certification layout when the last FP32 call on
   // this device had that many candidates per B entry
   const bool sorted_b = fp32 && !B.plan.K && dev->cand_per_b >= SORTED_RADEC_MIN;
+  // both sides through the bucket sort in the same form: in the same launches,
+  // all on the caller's stream (two streams' events cost more than running side
+  // by side gains: 2,000 a side 99 us against 137, 300k 201 against 213, 1.4M
+  // the same)
+  const bool both = !self && !prof && same_form(A.plan, B.plan);
   auto lay = [&](Carve& c) {
     // A is read in place: the filter gathers its records itself
     if (!self) {
@@ -68,10 +73,13 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   // what the counters' clearing reaches: places that depend on the workspace
   // and the sizes, not on the frame
   struct Cleared {
+    size_t ws_bytes;
     void* at[4];
-    bool operator==(const Cleared& o) const { return std::memcmp(at, o.at, sizeof at) == 0; }
+    bool operator==(const Cleared& o) const {
+      return ws_bytes == o.ws_bytes && std::memcmp(at, o.at, sizeof at) == 0;
+    }
   };
-  auto cleared = [&]() { return Cleared{{dev->ws, A.bws.fine, B.bws.fine, w.reg.cfill}}; };
+  auto cleared = [&]() { return Cleared{dev->ws_bytes, {dev->ws, A.bws.fine, B.bws.fine, w.reg.cfill}}; };
   auto clear = [&]() { launch_zero_counters(dev->cnt, s, A.bws.fine, B.bws.fine, &w.reg); };
   Cleared early{};
   const bool crowd = !B.plan.K && std::max(na, nb) >= CROWD_MIN;
@@ -88,8 +96,12 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
     HLC_TRY(hipEventRecord(dev->fork, s));
     HLC_TRY(hipStreamWaitEvent(dev->side, dev->fork, 0));
     fq = frame_begin(*dev, a_ra, a_dec, na_frame, b_ra, b_dec, nb, crowd, dev->side);
-    partition_keys(*dev, b_ra, b_dec, nB, g, true, !fp32, fp32, sc, 2u, B, slB, s);
-    partition_keys(*dev, a_ra, a_dec, nA, g, false, !fp32, fp32, scA, 1u, A, slA, dev->side);
+    if (both) {
+      partition_keys_both(*dev, a_ra, a_dec, nA, scA, A, b_ra, b_dec, nB, sc, B, g, s);
+    } else {
+      partition_keys(*dev, b_ra, b_dec, nB, g, true, !fp32, fp32, sc, 2u, B, slB, s);
+      partition_keys(*dev, a_ra, a_dec, nA, g, false, !fp32, fp32, scA, 1u, A, slA, dev->side);
+    }
   } else {
     fq = frame_begin(*dev, a_ra, a_dec, na_frame, b_ra, b_dec, nb, crowd, s);
     if (fits && !prof) {
@@ -129,28 +141,35 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   // side by side; the ranges run on the side stream once both are sorted,
   // beside B's gather (separate sort scratch, disjoint counter fields)
   // (B's keygen launched first: B's chain is the longer one)
-  if (!keep) {
-    if (!self) HLC_TRY(hipEventRecord(dev->fork, s));
-    partition_keys(*dev, b_ra, b_dec, nB, g, true, !fp32, fp32, sc, 2u, B, slB, s);
-    if (!self) {
-      HLC_TRY(hipStreamWaitEvent(dev->side, dev->fork, 0));
-      partition_keys(*dev, a_ra, a_dec, nA, g, false, !fp32, fp32, scA, 1u, A, slA, dev->side);
+  hipStream_t ms = s;  // the stream that the match runs and ends on
+  if (both) {
+    if (!keep) partition_keys_both(*dev, a_ra, a_dec, nA, scA, A, b_ra, b_dec, nB, sc, B, g, s);
+    partition_sort_both(*dev, g, scA, A, sc, B, s);
+  } else {
+    if (!keep) {
+      if (!self) HLC_TRY(hipEventRecord(dev->fork, s));
+      partition_keys(*dev, b_ra, b_dec, nB, g, true, !fp32, fp32, sc, 2u, B, slB, s);
+      if (!self) {
+        HLC_TRY(hipStreamWaitEvent(dev->side, dev->fork, 0));
+        partition_keys(*dev, a_ra, a_dec, nA, g, false, !fp32, fp32, scA, 1u, A, slA, dev->side);
+      }
     }
+    if (self) mark(*dev, slA.keygen, s);
+    if (!self) HLC_CHECK(partition_sort(*dev, g, !fp32, fp32, scA, A, slA, dev->side));
+    HLC_CHECK(partition_sort(*dev, g, !fp32, fp32, sc, B, slB, s, dev->bsorted));
+    if (self) {
+      // one partition serves both roles; its halo copies are skipped as A
+      for (int k : {slA.sort, slA.layout}) mark(*dev, k, s);
+      A = B;
+    }
+    HLC_TRY(hipStreamWaitEvent(dev->side, dev->bsorted, 0));
+    mark(*dev, prof ? 12 : -1, dev->side);
+    ms = dev->side;
   }
-  if (self) mark(*dev, slA.keygen, s);
-  if (!self) HLC_CHECK(partition_sort(*dev, g, !fp32, fp32, scA, A, slA, dev->side));
-  HLC_CHECK(partition_sort(*dev, g, !fp32, fp32, sc, B, slB, s, dev->bsorted));
-  if (self) {
-    // one partition serves both roles; its halo copies are skipped as A
-    for (int k : {slA.sort, slA.layout}) mark(*dev, k, s);
-    A = B;
-  }
-  HLC_TRY(hipStreamWaitEvent(dev->side, dev->bsorted, 0));
-  mark(*dev, prof ? 12 : -1, dev->side);
   match(*dev, A, B, g, r_arcsec, fp32, self, self, rad, w, out_pairs,
-        (o->flags & HLC_NO_SEP) ? nullptr : out_sep, (uint64_t)o->capacity, plevel, tuned_items(o), s, dev->side);
-  // the match ended on the side stream (after every kernel of the call on s)
-  HLC_CHECK(finish_match(*dev, A, B, r_arcsec, rad, w, prof, dev->side));
+        (o->flags & HLC_NO_SEP) ? nullptr : out_sep, (uint64_t)o->capacity, plevel, tuned_items(o), s, ms);
+  // (on the side stream: after every kernel of the call on s)
+  HLC_CHECK(finish_match(*dev, A, B, r_arcsec, rad, w, prof, ms));
 
   const Counters& h = *dev->cnt_host;
   if (h.err) {
