@@ -4,6 +4,7 @@
 // shutdown).
 #include <hip/hip_runtime.h>
 
+#include <chrono>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -180,7 +181,25 @@ void fill_times(Device& dev, bool with_partition) {
   g_stats.t_total_ms = el(0, 11);
 }
 
+// The counters as of the work enqueued on s. Unless stage times are wanted (or
+// the context has no mapped memory), a kernel writes them to host memory, where
+// the host polls for the call's number: no copy and no stream round trip.
 int read_counters(Device& dev, hipStream_t s, bool prof) {
+  if (dev.msg_dev && !prof) {
+    const unsigned long long seq = ++dev.fseq;
+    launch_report(dev.cnt, &dev.msg_dev->cnt, &dev.msg_dev->cnt_seq, seq, s);
+    HLC_TRY(hipGetLastError());
+    const auto t0 = std::chrono::steady_clock::now();
+    while (__atomic_load_n(&dev.msg->cnt_seq, __ATOMIC_ACQUIRE) != seq) {
+      if (std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(50)) {
+        HLC_TRY(hipStreamSynchronize(s));
+        HLC_TRY(hipGetLastError());
+        if (__atomic_load_n(&dev.msg->cnt_seq, __ATOMIC_ACQUIRE) != seq) return HLC_E_DEVICE;
+      }
+    }
+    *dev.cnt_host = dev.msg->cnt;
+    return HLC_OK;
+  }
   HLC_TRY(hipMemcpyAsync(dev.cnt_host, dev.cnt, sizeof(Counters), hipMemcpyDeviceToHost, s));
   if (prof) HLC_TRY(hipEventRecord(dev.ev[11], s));
   HLC_TRY(hipStreamSynchronize(s));

@@ -15,6 +15,8 @@ void launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t s);
 struct Regions;
 void launch_zero_counters(Counters* c, hipStream_t s, uint32_t* fine1 = nullptr, uint32_t* fine2 = nullptr,
                           const Regions* reg = nullptr);
+// the counters into mapped host memory, then seq at *at
+void launch_report(const Counters* c, Counters* out, unsigned long long* at, unsigned long long seq, hipStream_t s);
 struct SortScratch {
   uint32_t* keys_alt;
   uint32_t* vals_alt;
@@ -221,6 +223,21 @@ bool pair_order_fits(uint32_t n, const PairOrderSizes& z);
 constexpr unsigned long long PAIR_ORDER_NONE = 1, PAIR_ORDER_ROUNDS = 2;
 void launch_pair_order(uint2* pairs, double* sep, uint32_t n, uint64_t na, const PairOrderSizes& z,
                        const PairOrderWs& w, unsigned long long* over, hipStream_t s);
+// The same enqueued before the host knows the count (it is in cnt->n_pairs), in
+// grids for `most` pairs: with `block` at most PAIR_ORDER_LDS pairs are
+// ordered, else through the bucket pass more than that and up to `most`
+// (*over: PAIR_ORDER_NONE when the pairs were left alone). ws for `most`.
+struct PairOrderAhead {
+  bool block;
+  uint64_t most;  // 0: not ahead
+  PairOrderWs w;
+  unsigned long long* over;
+};
+constexpr uint64_t PAIR_AHEAD_MAX = 1000000;
+uint32_t pair_order_ahead_buckets(uint64_t most);
+uint32_t pair_order_ahead_chunks(uint64_t most);
+void launch_pair_order_ahead(uint2* pairs, double* sep, uint64_t capacity, uint64_t na, const PairOrderAhead& o,
+                             const Counters* cnt, hipStream_t s);
 void launch_pair_order_rounds(uint2* pairs, double* sep, uint32_t n, const PairOrderSizes& z, const PairOrderWs& w,
                               hipStream_t s);
 

@@ -35,6 +35,8 @@ struct HostMsg {
   ExtentSlot sample;                         // the sample's (polled); pad_[0]: its shared cells
   unsigned long long err[2 * EXTENT_SLOTS];  // the largest error radii
   unsigned long long order;                  // what the pair ordering left to do
+  Counters cnt;                              // a call's counters,
+  unsigned long long cnt_seq;                // once this is its number (polled)
 };
 
 // Memory of freed partitions, kept for the next one: hipFree wipes what it
@@ -87,6 +89,7 @@ struct Device {
   // mapped host memory: what kernels tell the host without a copy
   HostMsg* msg = nullptr;
   HostMsg* msg_dev = nullptr;  // its device address
+  bool ordered = false;  // the call's output is in order already (sort_output has nothing left to do)
   unsigned long long fseq = 0;
 };
 
@@ -354,6 +357,8 @@ struct MatchWs {
   uint2* band;
   uint64_t band_cap;
   Regions reg;
+  uint64_t ahead_na = 0;
+  PairOrderAhead ahead{};  // HLC_SORTED: the ordering enqueued behind the match
   OutArgs out{};  // what the match wrote to (for a band list's decision)
 };
 
@@ -387,6 +392,11 @@ constexpr int PROF_FILTER = 1, PROF_ALL = 2;
 void match(Device& dev, const Side& A, const Side& B, const Geom& g, double r_arcsec, bool fp32,
            bool skip_halo_a, bool self_only, const Radii& rad, MatchWs& w, hlc_pair* out_pairs,
            double* out_sep, uint64_t cap, int prof, int filter_items, hipStream_t s, hipStream_t ps = nullptr);
+// The ordering of a call's output enqueued behind its match, where the number
+// of pairs can be expected to suit (carved with the match's workspace); whether
+// it was done, and if not quite, its last step.
+void carve_order_ahead(Carve& c, MatchWs& w, Device& dev, const hlc_opts* o, int64_t na, int64_t nb);
+int finish_order_ahead(Device& dev, const MatchWs& w, uint64_t n, int64_t na, hipStream_t s);
 int finish_match(Device& dev, const Side& A, const Side& B, double r_arcsec, const Radii& rad, const MatchWs& w,
                  bool prof, hipStream_t s);
 // the profiling level of a call's flags

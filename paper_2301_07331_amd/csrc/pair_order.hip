@@ -52,6 +52,61 @@ __device__ inline uint32_t bucket_of(uint32_t a, u64 mul, uint32_t K) {
   return min((uint32_t)(((u64)a * mul) >> 32), K - 1u);
 }
 
+__host__ __device__ inline uint32_t bucket_count(uint32_t n, uint64_t na) {
+  uint64_t k = n / PO_MEAN;
+  if (k > PO_RUNS) {
+    k = n / PO_MEAN_L;
+    k = k > PO_BUCKETS ? PO_BUCKETS : k;
+    k = k < PO_RUNS ? PO_RUNS : k;
+  }
+  k = k > na ? na : k;
+  return k < 1 ? 1u : (uint32_t)k;
+}
+__host__ __device__ inline uint32_t chunk_count(uint32_t n) {
+  const uint32_t c = (n + PO_CHUNK_MIN - 1) / PO_CHUNK_MIN;
+  return c > PO_CHUNKS ? PO_CHUNKS : c < 1 ? 1u : c;
+}
+
+// What the kernels of a bucket pass work on. With cnt the pairs are not
+// counted on the host yet: the kernels take the count and the plan from it, in
+// grids for the most, and leave the pairs alone (K = 0) when they are few
+// enough for one block, more than `most` or the buffer, or crowded.
+struct PairRun {
+  uint2* pairs;
+  double* sep;
+  u64 na;
+  PairOrderWs w;
+  u64* over;
+  uint32_t cap;  // pairs that an ordering block takes
+  uint32_t n, K, chunks, chunk;
+  u64 mul;
+  const Counters* cnt;
+  u64 most;
+};
+struct PairPlan {
+  uint32_t n, K, chunks, chunk;
+  u64 mul;
+};
+__host__ __device__ inline PairPlan pair_plan(uint32_t n, u64 na) {
+  PairPlan p;
+  p.n = n;
+  p.K = bucket_count(n, na);
+  p.chunks = chunk_count(n);
+  p.chunk = (n + p.chunks - 1) / p.chunks;
+  p.mul = ((u64)p.K << 32) / na;
+  return p;
+}
+__device__ inline PairPlan plan_of(const PairRun& r) {
+  if (!r.cnt) return PairPlan{r.n, r.K, r.chunks, r.chunk, r.mul};
+  const u64 n = r.cnt->n_pairs;
+  PairPlan p{0u, 0u, 0u, 0u, 0ull};
+  if (n > PAIR_ORDER_LDS && n <= r.most) {
+    p = pair_plan((uint32_t)n, r.na);
+    if (p.n / p.K > PO_MEAN_S) p = PairPlan{0u, 0u, 0u, 0u, 0ull};
+  }
+  return p;
+}
+
 // Exclusive scan of one value per thread over a block of NW waves.
 template <int NW>
 __device__ inline uint32_t scan_block(uint32_t v, uint32_t* total, uint32_t* s_w) {
@@ -250,7 +305,14 @@ __device__ inline void order_pairs(OrderLds<CAP, T>& L, const u64 (&key)[CAP / T
 // n <= PAIR_ORDER_LDS pairs in place, one block: everything is read before
 // anything is written.
 constexpr uint32_t PO_THREADS_1 = 1024;
-__global__ __launch_bounds__(PO_THREADS_1) void k_po_block(uint2* pairs, double* sep, uint32_t n) {
+// (With cnt the count is taken from there: more than `most` are left alone.)
+__global__ __launch_bounds__(PO_THREADS_1) void k_po_block(uint2* pairs, double* sep, uint32_t n, const Counters* cnt,
+                                                           u64 most) {
+  if (cnt) {
+    const u64 found = cnt->n_pairs;
+    if (found > most || found < 2ull) return;
+    n = (uint32_t)found;
+  }
   __shared__ OrderLds<PAIR_ORDER_LDS, PO_THREADS_1> L;
   constexpr uint32_t PER = PAIR_ORDER_LDS / PO_THREADS_1;
   u64 key[PER];
@@ -267,9 +329,13 @@ __global__ __launch_bounds__(PO_THREADS_1) void k_po_block(uint2* pairs, double*
 }
 
 // chunk c's pairs per bucket: counts[c * K + d]
-__global__ __launch_bounds__(PO_CHUNK_THREADS) void k_po_count(const uint2* __restrict__ pairs, uint32_t n,
-                                                               uint32_t chunk, u64 mul, uint32_t K,
-                                                               uint32_t* __restrict__ counts) {
+__global__ __launch_bounds__(PO_CHUNK_THREADS) void k_po_count(PairRun run) {
+  const PairPlan p = plan_of(run);
+  if (blockIdx.x >= p.chunks) return;
+  const uint2* __restrict__ pairs = run.pairs;
+  uint32_t* __restrict__ counts = run.w.counts;
+  const uint32_t n = p.n, K = p.K, chunk = p.chunk;
+  const u64 mul = p.mul;
   __shared__ uint32_t s_c[PO_BUCKETS];
   for (uint32_t d = threadIdx.x; d < K; d += PO_CHUNK_THREADS) s_c[d] = 0u;
   __syncthreads();
@@ -284,7 +350,7 @@ __global__ __launch_bounds__(PO_CHUNK_THREADS) void k_po_count(const uint2* __re
 // A block takes 64 buckets: 16 rows of threads, each summing a sixteenth of
 // the chunks, all loads in flight at once.
 // (Two tables' blocks follow each other.)
-__global__ __launch_bounds__(PO_CHUNK_THREADS) void k_po_scan(BucketScan first, BucketScan second) {
+__device__ inline void scan_tables(const BucketScan& first, const BucketScan& second) {
   constexpr uint32_t ROWS = PO_CHUNK_THREADS / 64, PER = PO_CHUNKS / ROWS;
   __shared__ uint32_t s_sum[ROWS][64];
   const uint32_t l = threadIdx.x & 63u, row = threadIdx.x >> 6;
@@ -315,6 +381,14 @@ __global__ __launch_bounds__(PO_CHUNK_THREADS) void k_po_scan(BucketScan first, 
   }
   if (row == ROWS - 1u) totals[d] = run;
 }
+__global__ __launch_bounds__(PO_CHUNK_THREADS) void k_po_scan(BucketScan first, BucketScan second) {
+  scan_tables(first, second);
+}
+__global__ __launch_bounds__(PO_CHUNK_THREADS) void k_po_scan_ahead(PairRun run) {
+  const PairPlan p = plan_of(run);
+  if (blockIdx.x * 64u >= p.K) return;
+  scan_tables(BucketScan{run.w.counts, p.chunks, p.K, run.w.totals}, BucketScan{});
+}
 
 // A chunk's pairs as 16-B records into their buckets, a tile at a time: each
 // record's rank in its bucket from an LDS counter, the tile grouped by bucket
@@ -322,13 +396,21 @@ __global__ __launch_bounds__(PO_CHUNK_THREADS) void k_po_scan(BucketScan first, 
 // starts[0..K] are the buckets' first places. *over (in host memory) becomes
 // PAIR_ORDER_ROUNDS when a bucket holds more than `cap` pairs, and
 // PAIR_ORDER_NONE, nothing being moved, when one holds more than PO_OVER.
-__global__ __launch_bounds__(PO_CHUNK_THREADS) void k_po_scatter(const uint2* __restrict__ pairs,
-                                                                 const double* __restrict__ sep, uint32_t n,
-                                                                 uint32_t chunk, u64 mul, uint32_t K, uint32_t cap,
-                                                                 const uint32_t* __restrict__ counts,
-                                                                 const uint32_t* __restrict__ totals,
-                                                                 uint32_t* __restrict__ starts,
-                                                                 PairRec* __restrict__ rec, u64* over) {
+__global__ __launch_bounds__(PO_CHUNK_THREADS) void k_po_scatter(PairRun run) {
+  const PairPlan plan = plan_of(run);
+  u64* const over = run.over;
+  if (blockIdx.x >= plan.chunks) {
+    if (plan.chunks == 0u && blockIdx.x == 0 && threadIdx.x == 0) *over = PAIR_ORDER_NONE;
+    return;
+  }
+  const uint2* __restrict__ pairs = run.pairs;
+  const double* __restrict__ sep = run.sep;
+  const uint32_t* __restrict__ counts = run.w.counts;
+  const uint32_t* __restrict__ totals = run.w.totals;
+  uint32_t* __restrict__ starts = run.w.starts;
+  PairRec* __restrict__ rec = run.w.rec;
+  const uint32_t n = plan.n, K = plan.K, chunk = plan.chunk, cap = run.cap;
+  const u64 mul = plan.mul;
   constexpr uint32_t NW = PO_CHUNK_THREADS / 64, PER = PO_TILE / PO_CHUNK_THREADS;
   constexpr uint32_t BPT = PO_BUCKETS / PO_CHUNK_THREADS;  // buckets per thread
   __shared__ PairRec s_rec[PO_TILE];
@@ -429,10 +511,13 @@ __global__ __launch_bounds__(PO_CHUNK_THREADS) void k_po_scatter(const uint2* __
 // fits LDS (a kernel of its own: with the rounds below in it the registers of
 // both spill: 138 us against 39 us for 4.07M pairs).
 template <uint32_t CAP, uint32_t T>
-__global__ __launch_bounds__(T, CAP <= PO_CAP_M ? 8 : 4) void k_po_bucket(const PairRec* __restrict__ rec,
-                                                                          const uint32_t* __restrict__ starts,
-                                                                          uint32_t K, uint2* __restrict__ pairs,
-                                                                          double* __restrict__ sep) {
+__global__ __launch_bounds__(T, CAP <= PO_CAP_M ? 8 : 4) void k_po_bucket(PairRun run) {
+  const uint32_t K = plan_of(run).K;
+  if (blockIdx.x >= K) return;
+  const PairRec* __restrict__ rec = run.w.rec;
+  const uint32_t* __restrict__ starts = run.w.starts;
+  uint2* __restrict__ pairs = run.pairs;
+  double* __restrict__ sep = run.sep;
   __shared__ OrderLds<CAP, T> L;
   if (starts[K] == 0xffffffffu) return;  // nothing was moved
   const uint32_t t = threadIdx.x;
@@ -568,12 +653,6 @@ __global__ __launch_bounds__(T) void k_po_rounds(const PairRec* __restrict__ rec
   }
 }
 
-uint32_t bucket_count(uint32_t n, uint64_t na) {
-  uint64_t k = n / PO_MEAN;
-  if (k > PO_RUNS) k = std::max<uint64_t>(PO_RUNS, std::min<uint64_t>(PO_BUCKETS, n / PO_MEAN_L));
-  return (uint32_t)std::max<uint64_t>(1, std::min(k, na));
-}
-
 // pairs that the ordering blocks of a call take
 uint32_t block_cap(uint32_t n, const PairOrderSizes& z) {
   const uint32_t mean = n / z.K;
@@ -587,37 +666,59 @@ void launch_bucket_scan(const BucketScan& a, const BucketScan& b, hipStream_t s)
 }
 
 PairOrderSizes pair_order_sizes(uint32_t n, uint64_t na) {
-  PairOrderSizes z{};
-  z.K = bucket_count(n, na);
-  z.chunks = std::min(PO_CHUNKS, std::max(1u, (n + PO_CHUNK_MIN - 1) / PO_CHUNK_MIN));
-  return z;
+  const PairPlan p = pair_plan(n, na);
+  return PairOrderSizes{p.K, p.chunks};
 }
 
 void launch_pair_order_block(uint2* pairs, double* sep, uint32_t n, hipStream_t s) {
-  k_po_block<<<1, PO_THREADS_1, 0, s>>>(pairs, sep, n);
+  k_po_block<<<1, PO_THREADS_1, 0, s>>>(pairs, sep, n, nullptr, 0ull);
 }
 
 bool pair_order_fits(uint32_t n, const PairOrderSizes& z) { return n / z.K <= 2u * PO_CAP_L - PO_CAP_L / 8u; }
 
 void launch_pair_order(uint2* pairs, double* sep, uint32_t n, uint64_t na, const PairOrderSizes& z,
                        const PairOrderWs& w, unsigned long long* over, hipStream_t s) {
-  const uint64_t mul = ((uint64_t)z.K << 32) / na;
-  const uint32_t chunk = (n + z.chunks - 1) / z.chunks;
-  k_po_count<<<z.chunks, PO_CHUNK_THREADS, 0, s>>>(pairs, n, chunk, mul, z.K, w.counts);
+  const PairPlan p = pair_plan(n, na);
+  const PairRun run{pairs, sep, na, w, over, block_cap(n, z), p.n, p.K, p.chunks, p.chunk, p.mul, nullptr, 0ull};
+  k_po_count<<<z.chunks, PO_CHUNK_THREADS, 0, s>>>(run);
   launch_bucket_scan(BucketScan{w.counts, z.chunks, z.K, w.totals}, BucketScan{}, s);
-  k_po_scatter<<<z.chunks, PO_CHUNK_THREADS, 0, s>>>(pairs, sep, n, chunk, mul, z.K, block_cap(n, z), w.counts,
-                                                     w.totals, w.starts, w.rec, over);
-  switch (block_cap(n, z)) {
+  k_po_scatter<<<z.chunks, PO_CHUNK_THREADS, 0, s>>>(run);
+  switch (run.cap) {
     case PO_CAP_S:
-      k_po_bucket<PO_CAP_S, PO_THREADS_S><<<z.K, PO_THREADS_S, 0, s>>>(w.rec, w.starts, z.K, pairs, sep);
+      k_po_bucket<PO_CAP_S, PO_THREADS_S><<<z.K, PO_THREADS_S, 0, s>>>(run);
       break;
     case PO_CAP_M:
-      k_po_bucket<PO_CAP_M, PO_THREADS_L><<<z.K, PO_THREADS_L, 0, s>>>(w.rec, w.starts, z.K, pairs, sep);
+      k_po_bucket<PO_CAP_M, PO_THREADS_L><<<z.K, PO_THREADS_L, 0, s>>>(run);
       break;
     default:
-      k_po_bucket<PO_CAP_L, PO_THREADS_L><<<z.K, PO_THREADS_L, 0, s>>>(w.rec, w.starts, z.K, pairs, sep);
+      k_po_bucket<PO_CAP_L, PO_THREADS_L><<<z.K, PO_THREADS_L, 0, s>>>(run);
   }
 }
+
+void launch_pair_order_ahead(uint2* pairs, double* sep, uint64_t capacity, uint64_t na, const PairOrderAhead& o,
+                             const Counters* cnt, hipStream_t s) {
+  if (o.block) {
+    k_po_block<<<1, PO_THREADS_1, 0, s>>>(pairs, sep, 0u, cnt, std::min<u64>(capacity, PAIR_ORDER_LDS));
+    return;
+  }
+  PairRun run{};
+  run.pairs = pairs;
+  run.sep = sep;
+  run.na = na;
+  run.w = o.w;
+  run.over = o.over;
+  run.cap = PO_CAP_S;
+  run.cnt = cnt;
+  run.most = std::min<u64>(capacity, o.most);
+  const uint32_t chunks = chunk_count((uint32_t)o.most), K = pair_order_ahead_buckets(o.most);
+  k_po_count<<<chunks, PO_CHUNK_THREADS, 0, s>>>(run);
+  k_po_scan_ahead<<<(K + 63) / 64, PO_CHUNK_THREADS, 0, s>>>(run);
+  k_po_scatter<<<chunks, PO_CHUNK_THREADS, 0, s>>>(run);
+  k_po_bucket<PO_CAP_S, PO_THREADS_S><<<K, PO_THREADS_S, 0, s>>>(run);
+}
+
+uint32_t pair_order_ahead_buckets(uint64_t most) { return bucket_count((uint32_t)most, ~0ull); }
+uint32_t pair_order_ahead_chunks(uint64_t most) { return chunk_count((uint32_t)most); }
 
 void launch_pair_order_rounds(uint2* pairs, double* sep, uint32_t n, const PairOrderSizes& z, const PairOrderWs& w,
                               hipStream_t s) {

@@ -166,11 +166,16 @@ int hlc_xmatch_part(const struct hlc_part* A, const struct hlc_part* B, double r
                              false);
     for (int attempt = 0; attempt < 3; ++attempt) {
       MatchWs w;
+      auto lay = [&](Carve& c) {
+        carve_order_ahead(c, w, *dev, opts, A->side.n_src, B->side.n_src);
+        carve_match_ws(c, w, A->side.cnt.cap, g, caps, false);
+      };
       Carve sizing{nullptr};
-      carve_match_ws(sizing, w, A->side.cnt.cap, g, caps, false);
+      lay(sizing);
       HLC_CHECK(ensure_ws(*dev, sizing.off + 256));
       Carve c{(char*)dev->ws};
-      carve_match_ws(c, w, A->side.cnt.cap, g, caps, false);
+      lay(c);
+      dev->ordered = false;
       w.zstartB = B->zstart;
       if (prof) HLC_TRY(hipEventRecord(dev->ev[0], s));
       launch_zero_counters(dev->cnt, s, nullptr, nullptr, &w.reg);
@@ -185,6 +190,7 @@ int hlc_xmatch_part(const struct hlc_part* A, const struct hlc_part* B, double r
       if (prof) fill_times(*dev, false);
       else if (prof_level(opts->flags) == PROF_FILTER) g_stats.t_match_ms = elapsed(dev->ev[13], dev->ev[9]);
       *opts->n_pairs = (int64_t)h.n_pairs;
+      HLC_CHECK(finish_order_ahead(*dev, w, h.n_pairs, A->side.n_src, s));
       return sort_output(h.n_pairs > (unsigned long long)opts->capacity ? HLC_E_OVERFLOW : HLC_OK, out_pairs,
                          out_sep_arcsec, opts, A->side.n_src, B->side.n_src);
     }

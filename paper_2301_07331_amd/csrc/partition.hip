@@ -64,6 +64,18 @@ __global__ __launch_bounds__(1024) void k_zero_counters(Counters* c, uint32_t* f
         reinterpret_cast<uint4*>(f)[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
+// the counters into mapped host memory, then the call's number
+__global__ __launch_bounds__(64) void k_report(const Counters* c, Counters* out, unsigned long long* at,
+                                               unsigned long long seq) {
+  static_assert(sizeof(Counters) % 8 == 0 && sizeof(Counters) <= 512, "a word per lane");
+  const uint32_t t = threadIdx.x;
+  if (t < sizeof(Counters) / 8)
+    reinterpret_cast<unsigned long long*>(out)[t] = reinterpret_cast<const unsigned long long*>(c)[t];
+  __threadfence_system();
+  __syncthreads();
+  if (t == 0) *(volatile unsigned long long*)at = seq;
+}
+
 // ---------------------------------------------------------------------------
 // keygen
 // ---------------------------------------------------------------------------
@@ -1326,6 +1338,10 @@ void launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t s) {
 void launch_zero_counters(Counters* c, hipStream_t s, uint32_t* fine1, uint32_t* fine2, const Regions* reg) {
   k_zero_counters<<<1, fine1 || fine2 ? 1024 : 256, 0, s>>>(c, fine1, fine2, reg ? reg->fill : nullptr,
                                                             reg ? reg->cfill : nullptr);
+}
+
+void launch_report(const Counters* c, Counters* out, unsigned long long* at, unsigned long long seq, hipStream_t s) {
+  k_report<<<1, 64, 0, s>>>(c, out, at, seq);
 }
 
 void launch_keygen(const double* ra, const double* dec, uint32_t n, const Geom& g, bool halo,

@@ -22,6 +22,7 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   const int plevel = prof_level(o->flags);
   const bool fp32 = o->precision == HLC_FP32_RECHECK;
   const bool self = (o->flags & HLC_SELF) != 0;
+  dev->ordered = false;
   if (prof) HLC_TRY(hipEventRecord(dev->ev[0], s));
   const int64_t na_frame = self ? 0 : na;
   const uint32_t nB = (uint32_t)nb;
@@ -58,6 +59,7 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
     }
     carve_side(c, B, 2 * nB, !fp32, fp32, nB, true, sorted_b);
     carve_sort(c, sc, 2 * nB, B);
+    carve_order_ahead(c, w, *dev, o, na, nb);
     carve_match_ws(c, w, nA, g, caps, true);
   };
   // While the host waits for the sample, A's and B's keys under the
@@ -189,6 +191,7 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   fill_stats(h, na, nb, nb + (int64_t)h.n_halo, g);
   if (prof) fill_times(*dev, true);
   else if (plevel == PROF_FILTER) g_stats.t_match_ms = elapsed(dev->ev[13], dev->ev[9]);
+  HLC_CHECK(finish_order_ahead(*dev, w, (uint64_t)h.n_pairs, na, ms));
   if (fp32) dev->cand_per_b = (double)h.n_cand / (double)std::max<unsigned long long>(1, nb + h.n_halo);
   *o->n_pairs = (int64_t)h.n_pairs;
   return h.n_pairs > (unsigned long long)o->capacity ? HLC_E_OVERFLOW : HLC_OK;
