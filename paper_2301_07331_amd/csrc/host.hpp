@@ -173,7 +173,8 @@ struct Frame {
 
 // Partition geometry: zone height h_as (arcsec; <= 0 = automatic from the
 // data density), radius r (halo and windows), frame f.
-Geom make_geom(double r_arcsec, double h_as, int64_t na, int64_t nb, int ra_bits, const Frame& f = Frame{});
+Geom make_geom(double r_arcsec, double h_as, int64_t na, int64_t nb, int ra_bits, const Frame& f = Frame{},
+               bool crowded = false);
 
 inline double ext_value(unsigned long long code) {
   double v;

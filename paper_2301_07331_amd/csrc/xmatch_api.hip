@@ -31,7 +31,7 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   const Slots slB = prof ? Slots{1, 2, 3, 4} : NO_SLOTS;
   const Slots slA = prof ? Slots{5, -1, 6, 7} : NO_SLOTS;
 
-  Geom g = make_geom(r_arcsec, tuned_height(o), na, nb, tuned_bins(o), Frame{});
+  Geom g = make_geom(r_arcsec, tuned_height(o), na, nb, tuned_bins(o), Frame{}, dev->last_crowded);
   // (set before A's speculative keygen: the number of radix passes decides
   // which buffer that keygen writes)
   Side A, B;
@@ -71,7 +71,7 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   Carve guess{nullptr};
   lay(guess);
   const bool fits = guess.off + 256 <= dev->ws_bytes;
-  if (!self && dev->last_full) spec = fits;
+  if (dev->last_full) spec = fits;
   // what the counters' clearing reaches: places that depend on the workspace
   // and the sizes, not on the frame
   struct Cleared {
@@ -102,7 +102,7 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
       partition_keys_both(*dev, a_ra, a_dec, nA, scA, A, b_ra, b_dec, nB, sc, B, g, s);
     } else {
       partition_keys(*dev, b_ra, b_dec, nB, g, true, !fp32, fp32, sc, 2u, B, slB, s);
-      partition_keys(*dev, a_ra, a_dec, nA, g, false, !fp32, fp32, scA, 1u, A, slA, dev->side);
+      if (!self) partition_keys(*dev, a_ra, a_dec, nA, g, false, !fp32, fp32, scA, 1u, A, slA, dev->side);
     }
   } else {
     fq = frame_begin(*dev, a_ra, a_dec, na_frame, b_ra, b_dec, nb, crowd, s);
@@ -118,11 +118,11 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   bool crowded = false;
   HLC_CHECK(frame_finish(*dev, fq, a_ra, a_dec, na_frame, b_ra, b_dec, nb, s, spec ? dev->side : s, &f, &crowded));
   dev->last_full = is_full(f);
-  const int spec_frac = g.frac_sorted;
+  const bool same_crowd = crowded == dev->last_crowded;
   dev->last_crowded = crowded;
-  g = make_geom(r_arcsec, tuned_height(o), na, nb, tuned_bins(o), f);
+  g = make_geom(r_arcsec, tuned_height(o), na, nb, tuned_bins(o), f, crowded);
   g.frac_sorted = sub_bins(crowded);
-  const bool keep = spec && dev->last_full && g.frac_sorted == spec_frac;  // the speculative keys stand
+  const bool keep = spec && dev->last_full && same_crowd;  // the speculative keys stand
   Carve sizing{nullptr};
   lay(sizing);
   HLC_CHECK(ensure_ws(*dev, sizing.off + 256));
