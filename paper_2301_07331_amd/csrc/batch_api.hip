@@ -24,7 +24,35 @@ struct BatchPlan {
   uint32_t ztotal = 0;
   std::vector<BatchJob> jobs;
   std::vector<BatchTile> tA, tB;
+  uint32_t order_cap = 0;  // entries a block orders (k_job_order); 0: the digit sort
+  std::vector<BatchPiece> pA, pB;
 };
+
+// When the jobs are ordered one by one (k_job_order) rather than all together
+// by the digit sort. A job shared by np blocks is read np times: up to
+// JOB_ORDER_READS reads of an entry on average (300 jobs of 30,000, 11 reads:
+// 1,390 us a call against 1,630; 100 of 100,000, 35 reads: 2,220 against
+// 2,000), and no job beyond JOB_ORDER_MAX, whose blocks would run on alone. A
+// block of a few entries is mostly barriers, so that jobs are large enough
+// (20,000 of 64 sources: 890 us either way; of 128: 960 and 1,050; 60,000 of
+// 30: 1,980 and 1,790) or so few that the launches count more (100 of 30: 225
+// and 335). Blocks of 1,024 entries below a mean of 700 (10,000 of 512: 930 us,
+// 1,180 by digits).
+constexpr int64_t JOB_ORDER_MAX = 1 << 18;
+constexpr uint64_t JOB_ORDER_READS = 20, JOB_ORDER_MEAN_MIN = 64, JOB_ORDER_MEAN_SMALL = 700;
+constexpr int32_t JOB_ORDER_FEW = 4096;
+
+// The blocks that order a job of n sources on one side: one where the sources
+// and a few halo copies fit it, else with room for a third more than an even
+// share (a cone is 4/pi times denser along its middle than on average).
+uint32_t job_blocks(int64_t n, uint32_t cap) {
+  const uint32_t share = cap - cap * 3 / 10;
+  return n == 0 ? 0u : n <= (int64_t)(cap - cap / 8) ? 1u : (uint32_t)((n + share - 1) / share);
+}
+
+void push_pieces(std::vector<BatchPiece>& v, uint32_t job, uint32_t np) {
+  for (uint32_t k = 0; k < np; ++k) v.push_back({job, k, np});
+}
 
 // 64-bit hash of a byte range, eight bytes per step (multiply and xor-shift
 // mixing of each word into the state).
@@ -93,6 +121,21 @@ int build_plan(const hlc_job* jobs, int32_t njobs, int tile, BatchPlan& P) {
     if (ea >= (uint64_t(1) << 30) || eb >= (uint64_t(1) << 30) || zo >= (uint64_t(1) << 31))
       return HLC_E_INVAL;
   }
+  const uint64_t mean = (ea + eb) / std::max(2 * (uint64_t)njobs, (uint64_t)1);
+  if (mean >= JOB_ORDER_MEAN_MIN || njobs <= JOB_ORDER_FEW) {
+    P.order_cap = mean < JOB_ORDER_MEAN_SMALL ? JOB_ORDER_CAP_SMALL : JOB_ORDER_CAP;
+    uint64_t reads = 0;
+    int64_t most = 0;
+    for (const BatchJob& J : P.jobs) {
+      reads += J.na * (uint64_t)job_blocks(J.na, P.order_cap) + J.nb * (uint64_t)job_blocks(J.nb, P.order_cap);
+      most = std::max({most, J.na, J.nb});
+    }
+    if (most > JOB_ORDER_MAX || reads > JOB_ORDER_READS * (ea + eb)) P.order_cap = 0;
+  }
+  for (int32_t j = 0; P.order_cap && j < njobs; ++j) {
+    push_pieces(P.pA, (uint32_t)j, job_blocks(jobs[j].na, P.order_cap));
+    push_pieces(P.pB, (uint32_t)j, job_blocks(jobs[j].nb, P.order_cap));
+  }
   P.NA = ea;
   P.NB = eb;
   P.ztotal = (uint32_t)zo;
@@ -105,6 +148,7 @@ struct BatchState {  // per device
   uint64_t tables_hash = 0;
   BatchJob* d_jobs = nullptr;
   BatchTile *d_tA = nullptr, *d_tB = nullptr;
+  BatchPiece *d_pA = nullptr, *d_pB = nullptr;
   hipStream_t st = nullptr;
   hipStream_t st2 = nullptr;  // A's chain, beside B's
   hipEvent_t ev_in = nullptr, ev_out = nullptr, ev_t0 = nullptr, ev_t1 = nullptr;
@@ -133,7 +177,7 @@ void drop_graph(BatchState& B) {
 struct BatchBufs {
   unsigned long long* bounds;
   JobGeom* geo;
-  uint32_t *kA, *vA, *kB, *vB, *lb, *msplit, *zstart, *ckey, *cval;
+  uint32_t *kA, *vA, *kB, *vB, *lb, *msplit, *zstart, *ckey, *cval, *hcount, *hbase;
   int32_t* zmarg;
   GroupRanges* ranges;
   Rec64 *rA64, *rB64;
@@ -153,6 +197,11 @@ void carve_batch(Carve& c, BatchBufs& b, const BatchPlan& P, bool fp32, const Ca
   const uint32_t ng = (NA + GROUP - 1) / GROUP;
   b.bounds = c.take<unsigned long long>(4 * (size_t)std::max(P.njobs, 1));
   b.geo = c.take<JobGeom>(std::max(P.njobs, 1));
+  b.hcount = b.hbase = nullptr;
+  if (P.order_cap) {
+    b.hcount = c.take<uint32_t>(std::max(P.njobs, 1));
+    b.hbase = c.take<uint32_t>(std::max(P.njobs, 1));
+  }
   b.kA = c.take<uint32_t>(NA);
   b.vA = c.take<uint32_t>(NA);
   b.kB = c.take<uint32_t>(NB2);
@@ -218,7 +267,7 @@ void batch_enqueue(Device& dev, BatchState& BS, const BatchPlan& P, const BatchB
   };
   launch_zero_counters(dev.cnt, s);
   launch_zero_u64(jcount, (uint32_t)P.njobs, s);
-  launch_job_bounds_init(b.bounds, P.njobs, s);
+  launch_job_bounds_init(b.bounds, P.njobs, b.hcount, s);
   fork(0);
   launch_job_bounds(BS.d_tA, (uint32_t)P.tA.size(), P.tile, BS.d_jobs, a_ra, b_ra, a_ra, a_dec, false, b.bounds,
                     dev.cnt, s2);
@@ -229,14 +278,39 @@ void batch_enqueue(Device& dev, BatchState& BS, const BatchPlan& P, const BatchB
   const DevCount cA{NA, NA, nullptr};
   const DevCount cB{NB, 2 * NB, &dev.cnt->n_halo};
   fork(1);
-  launch_batch_keygen(BS.d_tA, (uint32_t)P.tA.size(), P.tile, b.geo, a_ra, a_dec, P.lb_bits, false, NA, b.kA, b.vA,
-                      dev.cnt, s2);
-  radix_sort(b.kA, b.vA, cA, 32, b.scA, s2);
+  const bool by_job = P.order_cap != 0;
+  auto order = [&](bool side_b, hipStream_t q) {
+    JobOrder o{};
+    o.pieces = side_b ? BS.d_pB : BS.d_pA;
+    o.npieces = (uint32_t)(side_b ? P.pB : P.pA).size();
+    o.cap = P.order_cap;
+    o.jobs = BS.d_jobs;
+    o.geo = b.geo;
+    o.lb_bits = P.lb_bits;
+    o.side_b = side_b;
+    o.n_total = side_b ? NB : NA;
+    o.keys_in = (side_b ? b.sc : b.scA).keys_alt;
+    o.vals_in = (side_b ? b.sc : b.scA).vals_alt;
+    o.hcount = side_b ? b.hcount : nullptr;
+    o.hbase = side_b ? b.hbase : nullptr;
+    o.keys = side_b ? b.kB : b.kA;
+    o.vals = side_b ? b.vB : b.vA;
+    launch_job_order(o, q);
+  };
+  launch_batch_keygen(BS.d_tA, (uint32_t)P.tA.size(), P.tile, b.geo, a_ra, a_dec, P.lb_bits, false, by_job, NA,
+                      by_job ? b.scA.keys_alt : b.kA, by_job ? b.scA.vals_alt : b.vA, BS.d_jobs, nullptr, dev.cnt, s2);
+  if (by_job) order(false, s2);
+  else radix_sort(b.kA, b.vA, cA, 32, b.scA, s2);
   if (fp32) launch_batch_layout32(b.kA, b.vA, cA, a_ra, a_dec, b.geo, P.lb_bits, b.rA32, b.radecA, s2);
   else launch_layout64(b.vA, cA, a_ra, a_dec, b.rA64, s2);
-  launch_batch_keygen(BS.d_tB, (uint32_t)P.tB.size(), P.tile, b.geo, b_ra, b_dec, P.lb_bits, true, NB, b.kB, b.vB,
-                      dev.cnt, s);
-  radix_sort(b.kB, b.vB, cB, 32, b.sc, s);
+  launch_batch_keygen(BS.d_tB, (uint32_t)P.tB.size(), P.tile, b.geo, b_ra, b_dec, P.lb_bits, true, by_job, NB,
+                      by_job ? b.sc.keys_alt : b.kB, by_job ? b.sc.vals_alt : b.vB, BS.d_jobs, b.hcount, dev.cnt, s);
+  if (by_job) {
+    launch_job_halo_scan(b.hcount, P.njobs, b.hbase, dev.cnt, s);
+    order(true, s);
+  } else {
+    radix_sort(b.kB, b.vB, cB, 32, b.sc, s);
+  }
   if (fp32) launch_batch_layout32(b.kB, b.vB, cB, b_ra, b_dec, b.geo, P.lb_bits, b.rB32, b.radecB, s);
   else launch_layout64(b.vB, cB, b_ra, b_dec, b.rB64, s);
   launch_batch_zone_tables(b.geo, P.njobs, BS.d_jobs, P.ztotal, P.lb_bits, b.kB, cB, b.zmarg, b.zstart, s);
@@ -303,6 +377,8 @@ int ensure_tables(BatchState& BS, hipStream_t s) {
   sz.take<BatchJob>(P.jobs.size());
   sz.take<BatchTile>(std::max<size_t>(P.tA.size(), 1));
   sz.take<BatchTile>(std::max<size_t>(P.tB.size(), 1));
+  sz.take<BatchPiece>(std::max<size_t>(P.pA.size(), 1));
+  sz.take<BatchPiece>(std::max<size_t>(P.pB.size(), 1));
   if (sz.off + 256 > BS.tables_bytes) {
     if (BS.tables) {
       (void)hipDeviceSynchronize();
@@ -317,9 +393,15 @@ int ensure_tables(BatchState& BS, hipStream_t s) {
   BS.d_jobs = c.take<BatchJob>(P.jobs.size());
   BS.d_tA = c.take<BatchTile>(std::max<size_t>(P.tA.size(), 1));
   BS.d_tB = c.take<BatchTile>(std::max<size_t>(P.tB.size(), 1));
+  BS.d_pA = c.take<BatchPiece>(std::max<size_t>(P.pA.size(), 1));
+  BS.d_pB = c.take<BatchPiece>(std::max<size_t>(P.pB.size(), 1));
   HLC_TRY(hipMemcpyAsync(BS.d_jobs, P.jobs.data(), P.jobs.size() * sizeof(BatchJob), hipMemcpyHostToDevice, s));
   HLC_TRY(hipMemcpyAsync(BS.d_tA, P.tA.data(), P.tA.size() * sizeof(BatchTile), hipMemcpyHostToDevice, s));
   HLC_TRY(hipMemcpyAsync(BS.d_tB, P.tB.data(), P.tB.size() * sizeof(BatchTile), hipMemcpyHostToDevice, s));
+  if (P.order_cap) {
+    HLC_TRY(hipMemcpyAsync(BS.d_pA, P.pA.data(), P.pA.size() * sizeof(BatchPiece), hipMemcpyHostToDevice, s));
+    HLC_TRY(hipMemcpyAsync(BS.d_pB, P.pB.data(), P.pB.size() * sizeof(BatchPiece), hipMemcpyHostToDevice, s));
+  }
   HLC_TRY(hipStreamSynchronize(s));
   BS.tables_hash = BS.plan_gen;
   return HLC_OK;

@@ -26,6 +26,7 @@
 // and the call runs again with the digit sort.
 #include <hip/hip_runtime.h>
 
+#include "bucket_order.hpp"
 #include "hlc_kernels.hpp"
 
 namespace hlc {
@@ -37,31 +38,6 @@ constexpr uint32_t BS_THREADS = 1024;
 constexpr uint32_t BS_CHUNKS = 256;     // counted and scattered by a block each
 constexpr uint32_t BS_CHUNK_MIN = 2048;
 constexpr uint32_t BS_CAP = 4096;       // entries of an ordering block
-constexpr uint32_t BIN_FULL = 12;       // keys in a bin of an ordering block
-
-// Exclusive scan of one value per thread over a block of NW waves.
-template <int NW>
-__device__ inline uint32_t scan_block(uint32_t v, uint32_t* total, uint32_t* s_w) {
-  const uint32_t t = threadIdx.x, lane = t & 63u, w = t >> 6;
-  uint32_t x = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(x, off);
-    if (lane >= (uint32_t)off) x += y;
-  }
-  if (lane == 63u) s_w[w] = x;
-  __syncthreads();
-  uint32_t base = 0, tot = 0;
-#pragma unroll
-  for (int k = 0; k < NW; ++k) {
-    const uint32_t s = s_w[k];
-    if ((uint32_t)k < w) base += s;
-    tot += s;
-  }
-  __syncthreads();
-  *total = tot;
-  return base + x - v;
-}
 
 // Entries per bucket and chunk. Each block first makes the map from parts of
 // the key space to buckets, the sample's running share times K (an empty
@@ -245,25 +221,16 @@ __global__ __launch_bounds__(BS_THREADS) void k_bs_scatter(BucketSide first, Buc
   }
 }
 
-// A bucket in order. The keys are binned in BINS bins evenly between
-// the smallest and the largest; where a bin holds more than BIN_FULL, each of
-// those again in as many bins evenly as it holds keys, so that a clump, which
-// fills few of the first, is spread over the second. A key's rank is its bin's
-// start and the number of smaller keys in the bin. Keys, indices and places pass through LDS
-// to leave in whole lines; the (ra, dec) are read from the bucket's stretch.
+// A bucket in order. Keys, indices and places pass through LDS to leave in
+// whole lines; the (ra, dec) are read from the bucket's stretch.
 template <uint32_t CAP, uint32_t T, bool DIRECT>
 __global__ __launch_bounds__(T, CAP <= 4096 ? 8 : 4) void k_bs_bucket(BucketSide first, BucketSide second) {
   const bool other = blockIdx.x >= first.p.K;
   const BucketIn& in = other ? second.in : first.in;
   const BucketOut& out = other ? second.out : first.out;
   const uint32_t blk = other ? blockIdx.x - first.p.K : blockIdx.x;
-  constexpr uint32_t PER = CAP / T, BINS = CAP > 4096 ? 4096 : 2048, NW = T / 64;
-  __shared__ uint32_t s_key[CAP];
-  __shared__ uint32_t s_c1[BINS + 1];
-  __shared__ uint32_t s_c2[CAP / 2];  // 16-bit counts, two a word
-  __shared__ uint32_t s_red[2][NW];
-  __shared__ uint32_t s_w[NW];
-  __shared__ uint32_t s_most;
+  constexpr uint32_t PER = CAP / T;
+  __shared__ OrderLds<CAP, T> L;
   const uint32_t t = threadIdx.x;
   uint32_t s0 = 0u, m;
   if constexpr (DIRECT) {
@@ -287,130 +254,16 @@ __global__ __launch_bounds__(T, CAP <= 4096 ? 8 : 4) void k_bs_bucket(BucketSide
       val[j] = e.y;
     }
   }
-  if (t == 0) s_most = 0u;
-  for (uint32_t i = t; i <= BINS; i += T) s_c1[i] = 0u;
-  for (uint32_t i = t; i < CAP / 2; i += T) s_c2[i] = 0u;
-  uint32_t lo = ~0u, hi = 0u;
-#pragma unroll
-  for (uint32_t j = 0; j < PER; ++j)
-    if (t + j * T < m) {
-      lo = min(lo, key[j]);
-      hi = max(hi, key[j]);
-    }
-  for (int d = 32; d > 0; d >>= 1) {
-    lo = min(lo, (uint32_t)__shfl_xor((int)lo, d));
-    hi = max(hi, (uint32_t)__shfl_xor((int)hi, d));
-  }
-  if ((t & 63u) == 0u) {
-    s_red[0][t >> 6] = lo;
-    s_red[1][t >> 6] = hi;
-  }
-  __syncthreads();
-  for (uint32_t k = 0; k < NW; ++k) {
-    lo = min(lo, s_red[0][k]);
-    hi = max(hi, s_red[1][k]);
-  }
-  // (key - lo) scale / 2^32 in [0, BINS): scale rounded down far enough
-  const unsigned long long scale =
-      (unsigned long long)((double)BINS * 4294967296.0 / ((double)(hi - lo) + 1.0) * (1.0 - 0x1p-40));
-  auto first_bin = [&](uint32_t k, uint32_t& frac) {
-    const unsigned long long x = (unsigned long long)(k - lo) * scale;
-    frac = (uint32_t)x;
-    return (uint32_t)(x >> 32);
-  };
-#pragma unroll
-  for (uint32_t j = 0; j < PER; ++j)
-    if (t + j * T < m) {
-      uint32_t f;
-      atomicAdd(&s_c1[first_bin(key[j], f)], 1u);
-    }
-  __syncthreads();
-  {
-    constexpr uint32_t PB = BINS / T;
-    uint32_t c[PB], sum = 0u, most = 0u, tot;
-#pragma unroll
-    for (uint32_t k = 0; k < PB; ++k) {
-      c[k] = s_c1[t * PB + k];
-      sum += c[k];
-      most = max(most, c[k]);
-    }
-    if (__any(most > BIN_FULL) && (t & 63u) == 0u) s_most = 1u;
-    uint32_t run = scan_block<NW>(sum, &tot, s_w);
-#pragma unroll
-    for (uint32_t k = 0; k < PB; ++k) {
-      s_c1[t * PB + k] = run;
-      run += c[k];
-    }
-    if (t == 0) s_c1[BINS] = tot;
-  }
-  __syncthreads();
-  uint32_t at[PER];   // the key's bin, then its place, then its rank
-  uint32_t bin[PER];
-  const bool twice = s_most != 0u;
-  if (!twice) {
-#pragma unroll
-    for (uint32_t j = 0; j < PER; ++j)
-      if (t + j * T < m) {
-        uint32_t f;
-        bin[j] = first_bin(key[j], f);
-        at[j] = atomicAdd(&s_c1[bin[j]], 1u);
-        s_key[at[j]] = key[j];
-      }
-  } else {
-#pragma unroll
-    for (uint32_t j = 0; j < PER; ++j)
-      if (t + j * T < m) {
-        uint32_t f;
-        const uint32_t b = first_bin(key[j], f), p = s_c1[b];
-        bin[j] = p + __umulhi(f, s_c1[b + 1u] - p);
-        atomicAdd(&s_c2[bin[j] >> 1], 1u << ((bin[j] & 1u) * 16u));
-      }
-    __syncthreads();
-    constexpr uint32_t PW = CAP / 2 / T;
-    uint32_t c[PW], sum = 0u, tot;
-#pragma unroll
-    for (uint32_t k = 0; k < PW; ++k) {
-      c[k] = s_c2[t * PW + k];
-      sum += (c[k] & 0xffffu) + (c[k] >> 16);
-    }
-    uint32_t run = scan_block<NW>(sum, &tot, s_w);
-#pragma unroll
-    for (uint32_t k = 0; k < PW; ++k) {
-      const uint32_t mid = run + (c[k] & 0xffffu);
-      s_c2[t * PW + k] = run | (mid << 16);
-      run = mid + (c[k] >> 16);
-    }
-    __syncthreads();
-#pragma unroll
-    for (uint32_t j = 0; j < PER; ++j)
-      if (t + j * T < m) {
-        const uint32_t sh = (bin[j] & 1u) * 16u;
-        at[j] = (atomicAdd(&s_c2[bin[j] >> 1], 1u << sh) >> sh) & 0xffffu;
-        s_key[at[j]] = key[j];
-      }
-  }
-  __syncthreads();
-  // a bin's word is now its end, the start of the next
-  auto end_of = [&](uint32_t b) { return twice ? (s_c2[b >> 1] >> ((b & 1u) * 16u)) & 0xffffu : s_c1[b]; };
-#pragma unroll
-  for (uint32_t j = 0; j < PER; ++j)
-    if (t + j * T < m) {
-      const uint32_t b0 = bin[j] ? end_of(bin[j] - 1u) : 0u, b1 = end_of(bin[j]);
-      uint32_t r = b0;
-      for (uint32_t q = b0; q < b1; ++q) {
-        const uint32_t o = s_key[q];
-        r += (o < key[j] || (o == key[j] && q < at[j])) ? 1u : 0u;
-      }
-      at[j] = r;
-    }
+  uint32_t at[PER];
+  order_block<CAP, T>(L, key, at, m);
   auto through_lds = [&](auto value, auto put) {
     __syncthreads();
 #pragma unroll
     for (uint32_t j = 0; j < PER; ++j)
-      if (t + j * T < m) s_key[at[j]] = value(j);
+      if (t + j * T < m) L.key[at[j]] = value(j);
     __syncthreads();
 #pragma unroll 4
-    for (uint32_t p = t; p < m; p += T) put(p, s_key[p]);
+    for (uint32_t p = t; p < m; p += T) put(p, L.key[p]);
   };
   through_lds([&](uint32_t j) { return key[j]; }, [&](uint32_t p, uint32_t v) { out.keys[s0 + p] = v; });
   auto record = [&](uint32_t p, uint32_t v, double2 q) {

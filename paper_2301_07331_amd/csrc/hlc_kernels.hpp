@@ -443,6 +443,9 @@ inline bool batch_tile_ok(int t) { return t == 256 || t == 512 || t == 1024 || t
 struct BatchTile {         // <= tile consecutive sources of one job and one side
   uint32_t job, entry, src, count;
 };
+struct BatchPiece {        // one block's share of a job's order: piece k of np even parts of its key range
+  uint32_t job, k, np;
+};
 struct JobGeom {           // the job's local frame (computed on the device)
   double d0, h_deg, inv_h, ra0, ra_span, bin_scale, r_deg, rpad_deg;
   double c_r, t_lo64, t_hi64, H_lo, H_hi;
@@ -469,7 +472,8 @@ struct BatchMatchArgs {
   unsigned long long* job_count;
 };
 
-void launch_job_bounds_init(unsigned long long* bounds, int32_t njobs, hipStream_t s);
+// hcount (the jobs' halo copies) cleared as well, unless null
+void launch_job_bounds_init(unsigned long long* bounds, int32_t njobs, uint32_t* hcount, hipStream_t s);
 void launch_job_bounds(const BatchTile* tiles, uint32_t ntiles, int tile, const BatchJob* jobs,
                        const double* a_ra, const double* b_ra, const double* ra, const double* dec, bool side_b,
                        unsigned long long* bounds, Counters* cnt, hipStream_t s);
@@ -477,8 +481,25 @@ void launch_job_frames(const BatchJob* jobs, int32_t njobs, const double* a_ra, 
                        const unsigned long long* bounds, int32_t lb_bits, double h_factor, JobGeom* geo,
                        hipStream_t s);
 void launch_batch_keygen(const BatchTile* tiles, uint32_t ntiles, int tile, const JobGeom* geo, const double* ra,
-                         const double* dec, int32_t lb_bits, bool halo, uint32_t n_total, uint32_t* keys,
-                         uint32_t* vals, Counters* cnt, hipStream_t s);
+                         const double* dec, int32_t lb_bits, bool halo, bool by_job, uint32_t n_total, uint32_t* keys,
+                         uint32_t* vals, const BatchJob* jobs, uint32_t* hcount, Counters* cnt, hipStream_t s);
+// hbase[j] = halo copies of the jobs before j; cnt->n_halo = all
+void launch_job_halo_scan(const uint32_t* hcount, int32_t njobs, uint32_t* hbase, Counters* cnt, hipStream_t s);
+// Each job's entries, as the keygen left them by job, in key order and packed;
+// cap: JOB_ORDER_CAP or JOB_ORDER_CAP_SMALL entries a block
+constexpr uint32_t JOB_ORDER_CAP = 4096, JOB_ORDER_CAP_SMALL = 1024;
+struct JobOrder {
+  const BatchPiece* pieces;
+  uint32_t npieces, cap;
+  const BatchJob* jobs;
+  const JobGeom* geo;
+  int32_t lb_bits;
+  bool side_b;
+  uint32_t n_total;                          // the side's sources: the first halo copy's place
+  const uint32_t *keys_in, *vals_in, *hcount, *hbase;  // (vals_in of the halo copies only)
+  uint32_t *keys, *vals;
+};
+void launch_job_order(const JobOrder& o, hipStream_t s);
 void launch_batch_layout32(const uint32_t* keys, const uint32_t* vals, const DevCount& n, const double* ra,
                            const double* dec, const JobGeom* geo, int32_t lb_bits, Rec32* rec,
                            double2* radec, hipStream_t s);
