@@ -17,6 +17,8 @@
 // covers the FP32 rounding of offsets up to the box's extent E_j.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "bucket_order.hpp"
 #include "hlc_kernels.hpp"
 
@@ -338,6 +340,18 @@ __global__ __launch_bounds__(FT) void k_batch_keygen(const BatchTile* __restrict
   }
 }
 
+__device__ inline Rec32 job_record(const JobGeom& G, double ra, double dec, uint32_t v) {
+  double sd, cd, sa, ca;
+  sincos_deg(dec, &sd, &cd);
+  sincos_deg(ra, &sa, &ca);
+  Rec32 r;
+  r.x = (float)(cd * ca - G.cx);
+  r.y = (float)(cd * sa - G.cy);
+  r.z = (float)(sd - G.cz);
+  r.idx = v;
+  return r;
+}
+
 // hbase = exclusive prefix of hcount (one block, njobs <= 65,536); the total to
 // cnt->n_halo
 constexpr uint32_t HS_THREADS = 1024;
@@ -363,14 +377,21 @@ __global__ __launch_bounds__(HS_THREADS) void k_job_halo_scan(const uint32_t* __
 // an entry, from the cache after the first block), keeps its own and counts the
 // lower ones, which gives its place without a pass of counts before. A
 // part that holds more than CAP is taken in halves that don't, and a single key
-// that more than CAP entries share is written as it comes. Bound by each
-// block's chain of LDS steps and barriers: 66 million entries in 1,020 us
-// where the four passes of both sides took 2,200 (10,000 cones of about 3,300
-// sources a side; the call 6,100 -> 5,200 us).
-template <uint32_t CAP, uint32_t T>
-__global__ __launch_bounds__(T, 8) void k_job_order(JobOrder o) {
-  constexpr uint32_t PER = CAP / T;
-  __shared__ OrderLds<CAP, T> L;
+// that more than CAP entries share is written as it comes.
+// The working records are made here too: a block's sources are read in input
+// order, along memory, and pass through LDS into key order, where a layout
+// after the sort fetches every (ra, dec) from a line of its own. Two blocks of
+// 512 threads a CU with the registers that the records want: four, with
+// spills, took 13 % longer, and blocks of 2,048 entries as much or up to 25 %
+// longer where jobs are large.
+// Bound by each block's chain of LDS steps and barriers. 10,000 cones of about
+// 3,300 sources a side: four digit passes of both sides 2,200 us and the
+// layouts 1,350, the order alone 1,020, both together 1,530
+// (the call 6,100 us, 5,250, 4,650).
+template <uint32_t CAP, uint32_t T, bool FP32>
+__global__ __launch_bounds__(T, 4) void k_job_order(JobOrder o) {
+  constexpr uint32_t PER = CAP / T, Q = CAP / 4;
+  __shared__ __align__(16) OrderLds<CAP, T> L;
   __shared__ uint32_t s_n, s_less;
   static_assert(sizeof(L.c) >= CAP * sizeof(uint32_t), "places pass through the counts' memory");
   // the blocks of one job on one XCD: its keys come from one L2
@@ -387,6 +408,16 @@ __global__ __launch_bounds__(T, 8) void k_job_order(JobOrder o) {
   auto key_at = [&](uint32_t i) { return i < own ? kin[i] : khalo[i - own]; };
   auto val_at = [&](uint32_t i) { return i < own ? src + i : vhalo[i - own]; };
   const JobGeom& G = o.geo[P.job];
+  auto record = [&](uint32_t p, uint32_t v, double2 q) {
+    if constexpr (FP32) {
+      o.radec[p] = q;
+      o.r32[p] = job_record(G, q.x, q.y, v);
+    } else {
+      double x, y, z;
+      unit_vector(q.x, q.y, x, y, z);
+      o.r64[p] = Rec64{x, y, z, v, 0u};
+    }
+  };
   const uint64_t span = (uint64_t)G.nz << G.rb, jb = (uint64_t)P.job << o.lb_bits;
   uint32_t lo = (uint32_t)(jb + span * P.k / P.np);
   const uint32_t end = (uint32_t)(jb + span * (P.k + 1u) / P.np - 1u);
@@ -440,6 +471,8 @@ __global__ __launch_bounds__(T, 8) void k_job_order(JobOrder o) {
     out += s_less;
   }
   while (true) {
+    uint32_t t = threadIdx.x;
+    asm volatile("" : "+v"(t));  // (nothing made of t is kept in registers round the loop)
     while (m > CAP && hi > lo) {
       hi = lo + (hi - lo) / 2u;
       m = select(lo, hi);
@@ -462,12 +495,23 @@ __global__ __launch_bounds__(T, 8) void k_job_order(JobOrder o) {
 #pragma unroll 4
       for (uint32_t p = t; p < m; p += T) o.keys[out + p] = L.key[p];
       __syncthreads();
+      double2 q[PER];
 #pragma unroll
       for (uint32_t j = 0; j < PER; ++j)
-        if (t + j * T < m) L.key[at[j]] = place[j];
-      __syncthreads();
-#pragma unroll 4
-      for (uint32_t p = t; p < m; p += T) o.vals[out + p] = val_at(L.key[p]);
+        if (t + j * T < m) {
+          const uint32_t v = val_at(place[j]), i = v & IDX_MASK;
+          L.key[at[j]] = v;
+          q[j] = make_double2(o.ra[i], o.dec[i]);
+        }
+      double2* const s_q = reinterpret_cast<double2*>(L.c);
+      for (uint32_t h = 0; h < m; h += Q) {
+        __syncthreads();
+#pragma unroll
+        for (uint32_t j = 0; j < PER; ++j)
+          if (t + j * T < m && at[j] - h < Q) s_q[at[j] - h] = q[j];
+        __syncthreads();
+        for (uint32_t p = t; p < min(Q, m - h); p += T) record(out + h + p, L.key[h + p], s_q[p]);
+      }
     } else {  // one key
       __syncthreads();
       if (t == 0) s_n = 0u;
@@ -475,8 +519,9 @@ __global__ __launch_bounds__(T, 8) void k_job_order(JobOrder o) {
       for (uint32_t i = t; i < total; i += T)
         if (key_at(i) == lo) {
           const uint32_t q = out + atomicAdd(&s_n, 1u);
+          const uint32_t v = val_at(i), k = v & IDX_MASK;
           o.keys[q] = lo;
-          o.vals[q] = val_at(i);
+          record(q, v, make_double2(o.ra[k], o.dec[k]));
         }
     }
     out += m;
@@ -504,15 +549,7 @@ __global__ __launch_bounds__(256) void k_batch_layout32(const uint32_t* __restri
   const uint32_t v = vals[p], i = v & IDX_MASK;
   const JobGeom& G = geo[keys[p] >> lb_bits];
   const double a = ra[i], d = dec[i];
-  double sd, cd, sa, ca;
-  sincos_deg(d, &sd, &cd);
-  sincos_deg(a, &sa, &ca);
-  Rec32 r;
-  r.x = (float)(cd * ca - G.cx);
-  r.y = (float)(cd * sa - G.cy);
-  r.z = (float)(sd - G.cz);
-  r.idx = v;
-  rec[p] = r;
+  rec[p] = job_record(G, a, d, v);
   radec[p] = make_double2(a, d);
 }
 
@@ -915,8 +952,13 @@ void launch_job_halo_scan(const uint32_t* hcount, int32_t njobs, uint32_t* hbase
 
 void launch_job_order(const JobOrder& o, hipStream_t s) {
   if (o.npieces == 0) return;
-  if (o.cap == JOB_ORDER_CAP) k_job_order<JOB_ORDER_CAP, 512><<<o.npieces, 512, 0, s>>>(o);
-  else k_job_order<JOB_ORDER_CAP_SMALL, 256><<<o.npieces, 256, 0, s>>>(o);
+  auto go = [&](auto fp32) {
+    constexpr bool F = decltype(fp32)::value;
+    if (o.cap == JOB_ORDER_CAP) k_job_order<JOB_ORDER_CAP, 512, F><<<o.npieces, 512, 0, s>>>(o);
+    else k_job_order<JOB_ORDER_CAP_SMALL, 256, F><<<o.npieces, 256, 0, s>>>(o);
+  };
+  if (o.r32) go(std::true_type{});
+  else go(std::false_type{});
 }
 
 void launch_job_bounds(const BatchTile* tiles, uint32_t ntiles, int tile, const BatchJob* jobs,

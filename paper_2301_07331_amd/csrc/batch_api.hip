@@ -203,9 +203,9 @@ void carve_batch(Carve& c, BatchBufs& b, const BatchPlan& P, bool fp32, const Ca
     b.hbase = c.take<uint32_t>(std::max(P.njobs, 1));
   }
   b.kA = c.take<uint32_t>(NA);
-  b.vA = c.take<uint32_t>(NA);
+  b.vA = P.order_cap ? nullptr : c.take<uint32_t>(NA);
   b.kB = c.take<uint32_t>(NB2);
-  b.vB = c.take<uint32_t>(NB2);
+  b.vB = P.order_cap ? nullptr : c.take<uint32_t>(NB2);
   carve_sort(c, b.sc, std::max(NB2, ng));
   carve_sort(c, b.scA, NA);
   if (fp32) {
@@ -294,15 +294,22 @@ void batch_enqueue(Device& dev, BatchState& BS, const BatchPlan& P, const BatchB
     o.hcount = side_b ? b.hcount : nullptr;
     o.hbase = side_b ? b.hbase : nullptr;
     o.keys = side_b ? b.kB : b.kA;
-    o.vals = side_b ? b.vB : b.vA;
+    o.ra = side_b ? b_ra : a_ra;
+    o.dec = side_b ? b_dec : a_dec;
+    o.r64 = side_b ? b.rB64 : b.rA64;
+    o.r32 = side_b ? b.rB32 : b.rA32;
+    o.radec = side_b ? b.radecB : b.radecA;
     launch_job_order(o, q);
   };
   launch_batch_keygen(BS.d_tA, (uint32_t)P.tA.size(), P.tile, b.geo, a_ra, a_dec, P.lb_bits, false, by_job, NA,
                       by_job ? b.scA.keys_alt : b.kA, by_job ? b.scA.vals_alt : b.vA, BS.d_jobs, nullptr, dev.cnt, s2);
-  if (by_job) order(false, s2);
-  else radix_sort(b.kA, b.vA, cA, 32, b.scA, s2);
-  if (fp32) launch_batch_layout32(b.kA, b.vA, cA, a_ra, a_dec, b.geo, P.lb_bits, b.rA32, b.radecA, s2);
-  else launch_layout64(b.vA, cA, a_ra, a_dec, b.rA64, s2);
+  if (by_job) {
+    order(false, s2);
+  } else {
+    radix_sort(b.kA, b.vA, cA, 32, b.scA, s2);
+    if (fp32) launch_batch_layout32(b.kA, b.vA, cA, a_ra, a_dec, b.geo, P.lb_bits, b.rA32, b.radecA, s2);
+    else launch_layout64(b.vA, cA, a_ra, a_dec, b.rA64, s2);
+  }
   launch_batch_keygen(BS.d_tB, (uint32_t)P.tB.size(), P.tile, b.geo, b_ra, b_dec, P.lb_bits, true, by_job, NB,
                       by_job ? b.sc.keys_alt : b.kB, by_job ? b.sc.vals_alt : b.vB, BS.d_jobs, b.hcount, dev.cnt, s);
   if (by_job) {
@@ -310,9 +317,9 @@ void batch_enqueue(Device& dev, BatchState& BS, const BatchPlan& P, const BatchB
     order(true, s);
   } else {
     radix_sort(b.kB, b.vB, cB, 32, b.sc, s);
+    if (fp32) launch_batch_layout32(b.kB, b.vB, cB, b_ra, b_dec, b.geo, P.lb_bits, b.rB32, b.radecB, s);
+    else launch_layout64(b.vB, cB, b_ra, b_dec, b.rB64, s);
   }
-  if (fp32) launch_batch_layout32(b.kB, b.vB, cB, b_ra, b_dec, b.geo, P.lb_bits, b.rB32, b.radecB, s);
-  else launch_layout64(b.vB, cB, b_ra, b_dec, b.rB64, s);
   launch_batch_zone_tables(b.geo, P.njobs, BS.d_jobs, P.ztotal, P.lb_bits, b.kB, cB, b.zmarg, b.zstart, s);
   join(1);
   launch_merge_lb(b.kA, cA, b.kB, cB, b.msplit, b.lb, s);

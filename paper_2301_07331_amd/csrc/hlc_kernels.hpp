@@ -485,7 +485,8 @@ void launch_batch_keygen(const BatchTile* tiles, uint32_t ntiles, int tile, cons
                          uint32_t* vals, const BatchJob* jobs, uint32_t* hcount, Counters* cnt, hipStream_t s);
 // hbase[j] = halo copies of the jobs before j; cnt->n_halo = all
 void launch_job_halo_scan(const uint32_t* hcount, int32_t njobs, uint32_t* hbase, Counters* cnt, hipStream_t s);
-// Each job's entries, as the keygen left them by job, in key order and packed;
+// Each job's entries, as the keygen left them by job, in key order, packed and
+// with their working records;
 // cap: JOB_ORDER_CAP or JOB_ORDER_CAP_SMALL entries a block
 constexpr uint32_t JOB_ORDER_CAP = 4096, JOB_ORDER_CAP_SMALL = 1024;
 struct JobOrder {
@@ -497,7 +498,11 @@ struct JobOrder {
   bool side_b;
   uint32_t n_total;                          // the side's sources: the first halo copy's place
   const uint32_t *keys_in, *vals_in, *hcount, *hbase;  // (vals_in of the halo copies only)
-  uint32_t *keys, *vals;
+  const double *ra, *dec;
+  uint32_t* keys;
+  Rec64* r64;                                // this or the two below
+  Rec32* r32;
+  double2* radec;
 };
 void launch_job_order(const JobOrder& o, hipStream_t s);
 void launch_batch_layout32(const uint32_t* keys, const uint32_t* vals, const DevCount& n, const double* ra,
