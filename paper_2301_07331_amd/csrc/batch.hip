@@ -652,12 +652,7 @@ __global__ __launch_bounds__(256) void k_batch_ranges(const uint32_t* __restrict
   const uint32_t na = nac.get();
   const uint32_t ngroups = (na + GROUP - 1) / GROUP;
   const uint32_t grp = blockIdx.x * blockDim.x + threadIdx.x;
-  if (grp >= (nac.cap + GROUP - 1) / GROUP) return;
-  if (grp >= ngroups) {  // padding of the LPT order: sorts last, never processed
-    cost_key[grp] = 0xffffffffu;
-    cost_val[grp] = grp;
-    return;
-  }
+  if (grp >= ngroups) return;
   const uint32_t p0 = grp * GROUP;
   const uint32_t cnt = min((uint32_t)GROUP, na - p0);
   RangeList L;
@@ -710,30 +705,45 @@ __global__ __launch_bounds__(256) void k_batch_ranges(const uint32_t* __restrict
   R.count = (uint32_t)n;
   R.pad_[0] = R.pad_[1] = R.pad_[2] = 0u;
   out[grp] = R;
-  // LPT order: most B work first (ascending sort of the complement)
-  cost_key[grp] = 0xfffffffeu - min(work + 1u, 0xfffffffeu);
-  cost_val[grp] = grp;
+  if (cost_key) {  // most B work first (ascending sort of the complement)
+    cost_key[grp] = 0xfffffffeu - min(work + 1u, 0xfffffffeu);
+    cost_val[grp] = grp;
+  }
 }
 
 // ---------------------------------------------------------------------------
-// persistent match kernel over LPT-ordered groups
+// persistent match kernel over the groups
 // ---------------------------------------------------------------------------
 constexpr int MT = 256;
 constexpr int WAVES = MT / 64;
 constexpr int QCAP = 64 * (GROUP + 1);
 
+// A wave's pairs of the job it is in, added to the job's count when the job
+// changes: the waves of a large job run side by side, and an atomic a flush on
+// its one counter held them up (11 ns each, one after the other).
+struct JobTally {
+  int32_t job = -1;
+  uint32_t n = 0u;
+  __device__ void put(unsigned long long* job_count) const {
+    if (n && lane_id() == 0u) atomicAdd(&job_count[job], (unsigned long long)n);
+  }
+};
+
 __device__ inline void bemit(bool in, uint32_t ia, uint32_t ib, double sep, int32_t job,
-                             const OutArgs& o, unsigned long long* job_count) {
+                             const OutArgs& o, unsigned long long* job_count, JobTally& tally) {
   emit_wave(in, ia, ib, sep, o);
   if (!job_count) return;
-  // one atomic per distinct job among the wave's pairs (the four groups of
-  // a wave seldom span more than two jobs)
   uint64_t rem = __ballot(in);
   while (rem) {
     const uint32_t leader = (uint32_t)__builtin_ctzll(rem);
     const int32_t j0 = __shfl(job, (int)leader);
     const uint64_t same = __ballot(in && job == j0);
-    if (lane_id() == leader) atomicAdd(&job_count[j0], (unsigned long long)__popcll(same));
+    if (j0 != tally.job || tally.n > 0x7fffffffu) {
+      tally.put(job_count);
+      tally.job = j0;
+      tally.n = 0u;
+    }
+    tally.n += (uint32_t)__popcll(same);
     rem &= ~same;
   }
 }
@@ -755,7 +765,7 @@ __device__ inline void bband(bool band, uint32_t ia, uint32_t ib, int32_t job, c
 }
 
 template <bool FP32>
-__device__ void bflush(const BatchMatchArgs& a, const OutArgs& o, const uint2* q, uint32_t qn) {
+__device__ void bflush(const BatchMatchArgs& a, const OutArgs& o, const uint2* q, uint32_t qn, JobTally& tally) {
   const uint32_t lane = lane_id();
   count_candidates(qn, o);
   for (uint32_t b0 = 0; b0 < qn; b0 += 64) {
@@ -789,7 +799,7 @@ __device__ void bflush(const BatchMatchArgs& a, const OutArgs& o, const uint2* q
         if (in) sep = 2.0 * asin(0.5 * sqrt(d2)) * RAD2ARCSEC;
       }
     }
-    bemit(in, ia, ib, sep, job, o, a.job_count);
+    bemit(in, ia, ib, sep, job, o, a.job_count, tally);
     bband(band, ia, ib, job, o);
   }
 }
@@ -825,17 +835,17 @@ __global__ __launch_bounds__(MT) void k_batch_match(BatchMatchArgs a, OutArgs o)
   const uint32_t row = lane >> 4, l16 = lane & 15u;
   uint2* q = s_q[w];
   uint32_t qn = 0;
+  JobTally tally;
   const uint32_t na = a.na.get();
   const uint32_t ngroups = (na + GROUP - 1) / GROUP;
-  // persistent: wave w of W takes the four groups at LPT positions
-  // 4 (w + i W), i = 0, 1, ... (largest first, dealt round-robin; no queue
-  // atomics); every wave leaves after its last item
-  const uint32_t W = gridDim.x * WAVES;
-  const uint32_t wid = blockIdx.x * WAVES + w;
+  // persistent: wave w of W takes the four groups from 4 (w + i W) on, i = 0, 1,
+  // ..., in the order given. In their own, neighbours share B entries, which
+  // then come from one L2: the waves of an XCD are next to each other
+  const uint32_t W = gridDim.x * WAVES, wid = xcd_block(blockIdx.x, gridDim.x) * WAVES + w;
   for (uint32_t item = 4u * wid; item < ngroups; item += 4u * W) {
     const uint32_t slot = item + row;
     const bool grp_ok = slot < ngroups;
-    const uint32_t grp = grp_ok ? a.order[slot] : 0u;
+    const uint32_t grp = !grp_ok ? 0u : a.order ? a.order[slot] : slot;
     const GroupRanges* R = grp_ok ? a.ranges + grp : nullptr;
     const uint32_t a_pos = grp * GROUP + l16;
     bool a_ok = grp_ok && a_pos < na;
@@ -890,12 +900,13 @@ __global__ __launch_bounds__(MT) void k_batch_match(BatchMatchArgs a, OutArgs o)
         }
       }
       if (qn >= 64) {
-        bflush<FP32>(a, o, q, qn);
+        bflush<FP32>(a, o, q, qn, tally);
         qn = 0;
       }
     }
   }
-  if (qn) bflush<FP32>(a, o, q, qn);
+  if (qn) bflush<FP32>(a, o, q, qn, tally);
+  if (a.job_count) tally.put(a.job_count);
 }
 
 // band list of the batch (each entry carries its job)

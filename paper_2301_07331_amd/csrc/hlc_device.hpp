@@ -83,7 +83,6 @@ struct Counters {
   unsigned long long n_band;      // entries in the band list
   unsigned long long n_ties;      // decided in double-double
   unsigned int err;               // bit 0: bad coordinate in A, bit 1: in B
-  unsigned int queue;             // work-queue head of persistent kernels
   unsigned int sort_over;         // a bucket of the bucket sort outgrew its block
   unsigned int pad_;
   unsigned long long aux[2];      // entry counts of multi-entry keygens (A, B)

@@ -455,9 +455,8 @@ struct JobGeom {           // the job's local frame (computed on the device)
   uint32_t nbins, zoff;
 };
 struct BatchMatchArgs {
+  const uint32_t* order;   // the groups in the order they are taken (nullptr: their own)
   const GroupRanges* ranges;
-  const uint32_t* order;   // LPT order of the groups
-  unsigned int* queue;     // work-queue head
   DevCount na;
   const uint32_t* keysA;
   const uint32_t* keysB;
@@ -511,6 +510,7 @@ void launch_batch_layout32(const uint32_t* keys, const uint32_t* vals, const Dev
 void launch_batch_zone_tables(const JobGeom* geo, int32_t njobs, const BatchJob* jobs, uint32_t ztotal,
                               int32_t lb_bits, const uint32_t* keysB, const DevCount& nb, int32_t* zmarg,
                               uint32_t* zstart, hipStream_t s);
+// cost_key, cost_val: each group's work and number, for an order by work (may be null)
 void launch_batch_ranges(const uint32_t* keysA, const DevCount& na, const uint32_t* lb, const uint32_t* keysB,
                          const JobGeom* geo, int32_t lb_bits, const int32_t* zmarg, const uint32_t* zstart,
                          GroupRanges* out, uint32_t* cost_key, uint32_t* cost_val, hipStream_t s);
