@@ -177,7 +177,7 @@ void drop_graph(BatchState& B) {
 struct BatchBufs {
   unsigned long long* bounds;
   JobGeom* geo;
-  uint32_t *kA, *vA, *kB, *vB, *lb, *msplit, *zstart, *ckey, *cval, *hcount, *hbase;
+  uint32_t *kA, *vA, *kB, *vB, *zstart, *ckey, *cval, *hcount, *hbase;
   int32_t* zmarg;
   GroupRanges* ranges;
   Rec64 *rA64, *rB64;
@@ -220,8 +220,6 @@ void carve_batch(Carve& c, BatchBufs& b, const BatchPlan& P, bool fp32, const Ca
     b.rA32 = b.rB32 = nullptr;
     b.radecA = b.radecB = nullptr;
   }
-  b.lb = c.take<uint32_t>(NA);
-  b.msplit = c.take<uint32_t>(merge_splits_len(NA, NB2));
   b.ranges = c.take<GroupRanges>(ng);
   b.ckey = b.cval = nullptr;
   if (!P.order_cap) {
@@ -325,8 +323,7 @@ void batch_enqueue(Device& dev, BatchState& BS, const BatchPlan& P, const BatchB
   }
   launch_batch_zone_tables(b.geo, P.njobs, BS.d_jobs, P.ztotal, P.lb_bits, b.kB, cB, b.zmarg, b.zstart, s);
   join(1);
-  launch_merge_lb(b.kA, cA, b.kB, cB, b.msplit, b.lb, s);
-  launch_batch_ranges(b.kA, cA, b.lb, b.kB, b.geo, P.lb_bits, b.zmarg, b.zstart, b.ranges, b.ckey, b.cval, s);
+  launch_batch_ranges(b.kA, cA, b.kB, b.geo, P.lb_bits, b.zmarg, b.zstart, b.ranges, b.ckey, b.cval, s);
   const uint32_t ng = (NA + GROUP - 1) / GROUP;
   // Jobs too large for k_job_order: the groups by descending work, so that a
   // wave's four take as many steps each (100 jobs of 100,000: the match 405 us,

@@ -511,7 +511,7 @@ void launch_batch_zone_tables(const JobGeom* geo, int32_t njobs, const BatchJob*
                               int32_t lb_bits, const uint32_t* keysB, const DevCount& nb, int32_t* zmarg,
                               uint32_t* zstart, hipStream_t s);
 // cost_key, cost_val: each group's work and number, for an order by work (may be null)
-void launch_batch_ranges(const uint32_t* keysA, const DevCount& na, const uint32_t* lb, const uint32_t* keysB,
+void launch_batch_ranges(const uint32_t* keysA, const DevCount& na, const uint32_t* keysB,
                          const JobGeom* geo, int32_t lb_bits, const int32_t* zmarg, const uint32_t* zstart,
                          GroupRanges* out, uint32_t* cost_key, uint32_t* cost_val, hipStream_t s);
 void launch_batch_match(const BatchMatchArgs& a, const OutArgs& o, bool fp32, uint32_t nblocks,
