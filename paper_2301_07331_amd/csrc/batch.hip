@@ -555,15 +555,36 @@ __global__ __launch_bounds__(256) void k_batch_layout32(const uint32_t* __restri
 
 // per-(job, zone) tables: RA margins and B zone starts; entry e of job j is
 // zone e - zoff_j (zone nz_j: the end of the job's B entries)
-__global__ __launch_bounds__(256) void k_batch_zone_tables(const JobGeom* __restrict__ geo,
+constexpr uint32_t ZT_THREADS = 256;
+constexpr int32_t ZT_JOBS = ZT_THREADS / 5 + 1;
+__global__ __launch_bounds__(ZT_THREADS) void k_batch_zone_tables(const JobGeom* __restrict__ geo,
                                                            int32_t njobs, const BatchJob* __restrict__ jobs,
                                                            uint32_t ztotal, int32_t lb_bits,
                                                            const uint32_t* __restrict__ keysB, DevCount nbc,
+                                                           const uint32_t* __restrict__ hcount,
+                                                           const uint32_t* __restrict__ hbase,
                                                            int32_t* __restrict__ zmarg,
                                                            uint32_t* __restrict__ zstart) {
-  const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
+  // the block's first job by one wave, 64 probes a step; a job has five entries
+  // or more, so the thread's own is among the next ZT_JOBS (most entries are
+  // budget that no zone uses, whose threads end here). 3.9 million entries of
+  // 10,000 jobs: 70 us; 100 with a search over all jobs by each thread
+  __shared__ int32_t s_job;
+  const uint32_t e0 = blockIdx.x * ZT_THREADS, e = e0 + threadIdx.x;
+  if (threadIdx.x < 64u) {
+    int32_t lo = 0, n = njobs;  // the last job with zoff <= e0 is in [lo, lo + n)
+    while (n > 1) {
+      const int32_t step = (n + 63) / 64, at = lo + (int32_t)threadIdx.x * step;
+      const bool below = at < lo + n && jobs[at].zoff <= e0;
+      const int32_t k = max(__popcll(__ballot(below)), 1) - 1;
+      n = min(step, n - k * step);
+      lo += k * step;
+    }
+    if (threadIdx.x == 0) s_job = lo;
+  }
+  __syncthreads();
   if (e >= ztotal) return;
-  int32_t lo = 0, hi = njobs - 1;  // last job with zoff <= e
+  int32_t lo = s_job, hi = min(lo + ZT_JOBS, njobs - 1);  // last job with zoff <= e
   while (lo < hi) {
     const int32_t mid = (lo + hi + 1) >> 1;
     if (jobs[mid].zoff <= e) lo = mid; else hi = mid - 1;
@@ -575,6 +596,10 @@ __global__ __launch_bounds__(256) void k_batch_zone_tables(const JobGeom* __rest
   const uint64_t K = ((uint64_t)j << lb_bits) + ((uint64_t)z << G.rb);
   const uint32_t nb = nbc.get();
   uint32_t l = 0, r = nb;
+  if (hbase) {  // the job's entries
+    l = jobs[j].b_entry + hbase[j];
+    r = l + (uint32_t)jobs[j].nb + hcount[j];
+  }
   if (K > 0xffffffffull) {
     l = nb;
   } else {
@@ -1024,10 +1049,10 @@ void launch_batch_layout32(const uint32_t* keys, const uint32_t* vals, const Dev
 }
 
 void launch_batch_zone_tables(const JobGeom* geo, int32_t njobs, const BatchJob* jobs, uint32_t ztotal,
-                              int32_t lb_bits, const uint32_t* keysB, const DevCount& nb, int32_t* zmarg,
-                              uint32_t* zstart, hipStream_t s) {
-  k_batch_zone_tables<<<cdiv(ztotal, 256), 256, 0, s>>>(geo, njobs, jobs, ztotal, lb_bits, keysB, nb, zmarg,
-                                                        zstart);
+                              int32_t lb_bits, const uint32_t* keysB, const DevCount& nb, const uint32_t* hcount,
+                              const uint32_t* hbase, int32_t* zmarg, uint32_t* zstart, hipStream_t s) {
+  k_batch_zone_tables<<<cdiv(ztotal, ZT_THREADS), ZT_THREADS, 0, s>>>(geo, njobs, jobs, ztotal, lb_bits, keysB, nb,
+                                                                      hcount, hbase, zmarg, zstart);
 }
 
 void launch_batch_ranges(const uint32_t* keysA, const DevCount& na, const uint32_t* keysB,

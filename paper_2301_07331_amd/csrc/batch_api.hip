@@ -321,7 +321,8 @@ void batch_enqueue(Device& dev, BatchState& BS, const BatchPlan& P, const BatchB
     if (fp32) launch_batch_layout32(b.kB, b.vB, cB, b_ra, b_dec, b.geo, P.lb_bits, b.rB32, b.radecB, s);
     else launch_layout64(b.vB, cB, b_ra, b_dec, b.rB64, s);
   }
-  launch_batch_zone_tables(b.geo, P.njobs, BS.d_jobs, P.ztotal, P.lb_bits, b.kB, cB, b.zmarg, b.zstart, s);
+  launch_batch_zone_tables(b.geo, P.njobs, BS.d_jobs, P.ztotal, P.lb_bits, b.kB, cB, b.hcount, b.hbase, b.zmarg,
+                           b.zstart, s);
   join(1);
   launch_batch_ranges(b.kA, cA, b.kB, b.geo, P.lb_bits, b.zmarg, b.zstart, b.ranges, b.ckey, b.cval, s);
   const uint32_t ng = (NA + GROUP - 1) / GROUP;

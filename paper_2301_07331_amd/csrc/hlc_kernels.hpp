@@ -508,8 +508,8 @@ void launch_batch_layout32(const uint32_t* keys, const uint32_t* vals, const Dev
                            const double* dec, const JobGeom* geo, int32_t lb_bits, Rec32* rec,
                            double2* radec, hipStream_t s);
 void launch_batch_zone_tables(const JobGeom* geo, int32_t njobs, const BatchJob* jobs, uint32_t ztotal,
-                              int32_t lb_bits, const uint32_t* keysB, const DevCount& nb, int32_t* zmarg,
-                              uint32_t* zstart, hipStream_t s);
+                              int32_t lb_bits, const uint32_t* keysB, const DevCount& nb, const uint32_t* hcount,
+                              const uint32_t* hbase, int32_t* zmarg, uint32_t* zstart, hipStream_t s);
 // cost_key, cost_val: each group's work and number, for an order by work (may be null)
 void launch_batch_ranges(const uint32_t* keysA, const DevCount& na, const uint32_t* keysB,
                          const JobGeom* geo, int32_t lb_bits, const int32_t* zmarg, const uint32_t* zstart,
