@@ -37,10 +37,13 @@ struct BatchPlan {
 // (20,000 of 64 sources: 890 us either way; of 128: 960 and 1,050; 60,000 of
 // 30: 1,980 and 1,790) or so few that the launches count more (100 of 30: 225
 // and 335). Blocks of 1,024 entries below a mean of 700 (10,000 of 512: 930 us,
-// 1,180 by digits).
+// 1,180 by digits). Fewer than JOB_ORDER_JOBS jobs keep the digit sort: a call
+// with one job of 20,000 sources ended in a segmentation fault of the host
+// process once, without a GPU fault; its cause was not found (the host code is
+// clean under the address and undefined-behaviour sanitizers).
 constexpr int64_t JOB_ORDER_MAX = 1 << 18;
 constexpr uint64_t JOB_ORDER_READS = 20, JOB_ORDER_MEAN_MIN = 64, JOB_ORDER_MEAN_SMALL = 700;
-constexpr int32_t JOB_ORDER_FEW = 4096;
+constexpr int32_t JOB_ORDER_JOBS = 16, JOB_ORDER_FEW = 4096;
 
 // The blocks that order a job of n sources on one side: one where the sources
 // and a few halo copies fit it, else with room for a third more than an even
@@ -122,7 +125,7 @@ int build_plan(const hlc_job* jobs, int32_t njobs, int tile, BatchPlan& P) {
       return HLC_E_INVAL;
   }
   const uint64_t mean = (ea + eb) / std::max(2 * (uint64_t)njobs, (uint64_t)1);
-  if (mean >= JOB_ORDER_MEAN_MIN || njobs <= JOB_ORDER_FEW) {
+  if (njobs >= JOB_ORDER_JOBS && (mean >= JOB_ORDER_MEAN_MIN || njobs <= JOB_ORDER_FEW)) {
     P.order_cap = mean < JOB_ORDER_MEAN_SMALL ? JOB_ORDER_CAP_SMALL : JOB_ORDER_CAP;
     uint64_t reads = 0;
     int64_t most = 0;
@@ -517,6 +520,16 @@ int batch_impl(const hlc_job* jobs, int32_t njobs, const double* a_ra, const dou
       // the call itself does, as a captured graph: one untimed replay, then
       // the best of two timed ones
       drop_graph(BS);
+      // (the candidates' graphs go once the device is idle)
+      struct Graphs {
+        std::vector<hipGraph_t> g;
+        std::vector<hipGraphExec_t> x;
+        ~Graphs() {
+          (void)hipDeviceSynchronize();
+          for (hipGraphExec_t e : x) (void)hipGraphExecDestroy(e);
+          for (hipGraph_t e : g) (void)hipGraphDestroy(e);
+        }
+      } graphs;
       auto timed = [&](const BatchConfig& k, double* ms_out) -> int {
         HLC_CHECK(ensure_plan(BS, jobs, njobs, k.tile));
         HLC_CHECK(ensure_tables(BS, s));
@@ -525,7 +538,9 @@ int batch_impl(const hlc_job* jobs, int32_t njobs, const double* a_ra, const dou
         HLC_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
         batch_enqueue(*dev, BS, BS.plan, b, a_ra, a_dec, b_ra, b_dec, out_pairs, sep, cap, jc, k, fp32, s);
         HLC_TRY(hipStreamEndCapture(s, &gr));
+        graphs.g.push_back(gr);
         hipError_t e = hipGraphInstantiate(&ex, gr, nullptr, nullptr, 0);
+        if (e == hipSuccess) graphs.x.push_back(ex);
         double best = 1e30;
         for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {
           if ((e = hipEventRecord(BS.ev_t0, s)) != hipSuccess) break;
@@ -536,8 +551,6 @@ int batch_impl(const hlc_job* jobs, int32_t njobs, const double* a_ra, const dou
           if ((e = hipEventElapsedTime(&ms, BS.ev_t0, BS.ev_t1)) != hipSuccess) break;
           if (rep > 0) best = std::min(best, (double)ms);
         }
-        if (ex) (void)hipGraphExecDestroy(ex);
-        (void)hipGraphDestroy(gr);
         HLC_TRY(e);
         *ms_out = best;
         return HLC_OK;
