@@ -404,8 +404,12 @@ void launch_filter(const MatchArgs& a, const OutArgs& o, bool fp32, int items_pe
 void launch_cand(const MatchArgs& a, const OutArgs& o, bool fp32, hipStream_t s);
 // Re-decide the band list from the original coordinates: FP64 haversine,
 // then double-double inside the FP64 band.
-void launch_certify(const double* a_ra, const double* a_dec, const double* b_ra,
-                    const double* b_dec, double r_arcsec, double H_lo, double H_hi,
+// source i at (ra[i stride], dec[i stride])
+struct Positions {
+  const double *ra, *dec;
+  uint32_t stride = 1;
+};
+void launch_certify(const Positions& a, const Positions& b, double r_arcsec, double H_lo, double H_hi,
                     const Radii& rad, const OutArgs& o, hipStream_t s);
 // codes (bit patterns) of the largest error of each side, a pair of words per
 // block; ERR_BAD (above every valid code) for a negative or non-finite error;

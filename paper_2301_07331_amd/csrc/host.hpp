@@ -290,7 +290,8 @@ struct Side {
   // of a gathered side are computed from it, the filter reads a side in
   // place from it, and the certification reads B's positions from it
   double2* srcrad = nullptr;
-  const double *ra = nullptr, *dec = nullptr;  // original coordinates (for the band list)
+  const double *ra = nullptr, *dec = nullptr;  // original coordinates (for the band list),
+  uint32_t stride = 1;                         // stride elements apart
 };
 
 // Profiling event slots (HLC_PROFILE): per partition, {after keygen,

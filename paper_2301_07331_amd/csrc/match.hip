@@ -698,17 +698,15 @@ __global__ __launch_bounds__(MT, 7) void k_filter(MatchArgs a, OutArgs o) {
 // band list: FP64 haversine from the original coordinates, double-double
 // inside the FP64 band (true ties within TIE_REL of r count as matches)
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_certify(const double* __restrict__ a_ra,
-                                                 const double* __restrict__ a_dec,
-                                                 const double* __restrict__ b_ra,
-                                                 const double* __restrict__ b_dec, double r_arcsec,
-                                                 double H_lo, double H_hi, Radii rad, OutArgs o) {
+__global__ __launch_bounds__(256) void k_certify(Positions a, Positions b, double r_arcsec, double H_lo,
+                                                 double H_hi, Radii rad, OutArgs o) {
   unsigned long long n = o.cnt->n_band;
   if (n > o.band_cap) n = o.band_cap;
   for (unsigned long long i = (unsigned long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (unsigned long long)gridDim.x * blockDim.x) {
     uint2 e = o.band[i];
-    double ra1 = a_ra[e.x], de1 = a_dec[e.x], ra2 = b_ra[e.y], de2 = b_dec[e.y];
+    const size_t ia = (size_t)e.x * a.stride, ib = (size_t)e.y * b.stride;
+    double ra1 = a.ra[ia], de1 = a.dec[ia], ra2 = b.ra[ib], de2 = b.dec[ib];
     double h = haversine64(ra1, de1, ra2, de2);
     double Hlo = H_lo, Hhi = H_hi;
     if (rad.a_err) {
@@ -831,10 +829,9 @@ void launch_cand(const MatchArgs& a, const OutArgs& o, bool fp32, hipStream_t s)
   else k_cand<false, false, CAND_ITEMS><<<blocks, 256, 0, s>>>(a, o);
 }
 
-void launch_certify(const double* a_ra, const double* a_dec, const double* b_ra,
-                    const double* b_dec, double r_arcsec, double H_lo, double H_hi,
+void launch_certify(const Positions& a, const Positions& b, double r_arcsec, double H_lo, double H_hi,
                     const Radii& rad, const OutArgs& o, hipStream_t s) {
-  k_certify<<<256, 256, 0, s>>>(a_ra, a_dec, b_ra, b_dec, r_arcsec, H_lo, H_hi, rad, o);
+  k_certify<<<256, 256, 0, s>>>(a, b, r_arcsec, H_lo, H_hi, rad, o);
 }
 
 }  // namespace hlc

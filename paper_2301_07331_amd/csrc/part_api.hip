@@ -17,8 +17,6 @@ struct hlc_part {
   size_t mem_bytes = 0;
   hlc::Side side;
   uint32_t* zstart = nullptr;
-  double* ra = nullptr;  // private copies of the coordinates
-  double* dec = nullptr;
 };
 
 using namespace hlc;
@@ -66,12 +64,12 @@ int hlc_partition(const double* ra_deg, const double* dec_deg, int64_t n, double
       p->side.plan = plan_sort(n, attempt > 0);
       p->g.frac_sorted = p->side.plan.K ? 1 : 0;
       auto lay = [&](Carve& c) {
-        // FP32: sorted (ra, dec) kept with the part for the certification (its
-        // per-source records are scratch)
+        // FP32: sorted (ra, dec) kept with the part for the certification, and
+        // the sources' (ra, dec), which the keygen writes, for the band list
+        // (2M a side: a pass 457 us with copies of the caller's arrays, 442)
         carve_side(c, p->side, cap, true, true, 0, true, true);
         p->zstart = c.take<uint32_t>((size_t)p->g.nz + 1);
-        p->ra = c.take<double>(std::max(nn, 1u));
-        p->dec = c.take<double>(std::max(nn, 1u));
+        p->side.srcrad = c.take<double2>(std::max(nn, 1u));
       };
       Carve sizing{nullptr};
       lay(sizing);
@@ -82,13 +80,9 @@ int hlc_partition(const double* ra_deg, const double* dec_deg, int64_t n, double
       }
       Carve c{(char*)p->mem};
       lay(c);
-      // sort scratch and the keygen's per-source records come from the shared
-      // workspace (the part keeps only the sorted entries)
+      // sort scratch comes from the shared workspace
       SortScratch sc;
-      auto scratch = [&](Carve& c) {
-        carve_sort(c, sc, std::max(cap, 1u), p->side);
-        p->side.srcrad = p->side.plan.K ? nullptr : c.take<double2>(std::max(nn, 1u));
-      };
+      auto scratch = [&](Carve& c) { carve_sort(c, sc, std::max(cap, 1u), p->side); };
       Carve ss{nullptr};
       scratch(ss);
       st = ensure_ws(*dev, ss.off + 256);
@@ -98,14 +92,11 @@ int hlc_partition(const double* ra_deg, const double* dec_deg, int64_t n, double
       }
       Carve cs{(char*)dev->ws};
       scratch(cs);
-      if (nn && (hipMemcpyAsync(p->ra, ra_deg, (size_t)nn * 8, hipMemcpyDeviceToDevice, s) != hipSuccess ||
-                 hipMemcpyAsync(p->dec, dec_deg, (size_t)nn * 8, hipMemcpyDeviceToDevice, s) != hipSuccess)) {
-        release_part(p, false);
-        return HLC_E_DEVICE;
-      }
       launch_zero_counters(dev->cnt, s, p->side.bws.fine);
-      st = partition(*dev, p->ra, p->dec, nn, p->g, true, true, true, sc, 1u, p->side, NO_SLOTS, s);
-      p->side.srcrad = nullptr;
+      st = partition(*dev, ra_deg, dec_deg, nn, p->g, true, true, true, sc, 1u, p->side, NO_SLOTS, s);
+      p->side.ra = &p->side.srcrad->x;
+      p->side.dec = &p->side.srcrad->y;
+      p->side.stride = 2;
       p->side.bws = BucketWs{};
       if (st == HLC_OK) {
         launch_zone_starts(p->side.keys, p->side.cnt, p->g, p->zstart, s);

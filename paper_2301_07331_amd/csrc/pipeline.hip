@@ -69,7 +69,7 @@ void partition_keys(Device& dev, const double* ra, const double* dec, uint32_t n
   sd.n_cap = halo ? 2 * n : n;
   if (sd.plan.K) {
     const KeygenSample ks = keygen_sample(sd, g);
-    launch_keygen(ra, dec, n, g, halo, err_bit, sc.keys_alt, sc.vals_alt, dev.cnt, s, nullptr, nullptr, true, &ks);
+    launch_keygen(ra, dec, n, g, halo, err_bit, sc.keys_alt, sc.vals_alt, dev.cnt, s, sd.srcrad, nullptr, true, &ks);
     mark(dev, sl.keygen, s);
     sd.cnt = sort_count(dev, n, halo);
     return;
@@ -307,7 +307,7 @@ int finish_match(Device& dev, const Side& A, const Side& B, double r_arcsec, con
   HLC_CHECK(read_counters(dev, s, prof));
   if (dev.cnt_host->n_band == 0) return HLC_OK;
   const Thresholds th = thresholds(r_arcsec);
-  launch_certify(A.ra, A.dec, B.ra, B.dec, r_arcsec, th.H_lo, th.H_hi, rad, w.out, s);
+  launch_certify({A.ra, A.dec, A.stride}, {B.ra, B.dec, B.stride}, r_arcsec, th.H_lo, th.H_hi, rad, w.out, s);
   if (prof) (void)hipEventRecord(dev.ev[10], s);
   return read_counters(dev, s, prof);
 }
