@@ -177,13 +177,12 @@ def pmc_summary(ktrace_dir, pmc_dirs):
     return "\n".join(out)
 
 
-def call_timeline(ktrace_dir, call, first="k_extent_sample", with_kernel=None):
+def call_timeline(ktrace_dir, call, first="k_zero_counters", with_kernel=None):
     """The kernels of one call, in start order, from a rocprofv3
     --kernel-trace -f csv folder: queue, start and end (us from the call's
     first kernel) and duration. A call starts at each launch of `first` (the
-    footprint sample of a single call; k_zero_u64 for the batched form);
-    with `with_kernel` only the calls that launch a kernel of that name
-    count. `call` indexes those calls from 0 (negative: from the last).
+    counters' clearing, of a single call and of the batched form); with
+    `with_kernel` only the calls that launch a kernel of that name count. `call` indexes those calls from 0 (negative: from the last).
     Markdown."""
     import csv
     rows = []
@@ -253,7 +252,7 @@ def parse():
                         "followed by one or more --pmc folders, and exit")
     p.add_argument("--timeline", nargs="+", metavar="ARG",
                    help="KTRACE_DIR CALL [FIRST_KERNEL [WITH_KERNEL]]: print the kernels of one call (numbered "
-                        "from 0, negative from the last; calls start at FIRST_KERNEL, default k_extent_sample, and "
+                        "from 0, negative from the last; calls start at FIRST_KERNEL, default k_zero_counters, and "
                         "count only if they launch WITH_KERNEL) from a rocprofv3 --kernel-trace -f csv folder, "
                         "and exit")
     p.add_argument("--traffic-from", nargs=2, metavar=("FETCH_DIR", "WRITE_DIR"),

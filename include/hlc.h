@@ -200,7 +200,9 @@ int hlc_xmatch_quad(const double *a_ra, const double *a_dec, int64_t na, const d
 /* Reusable device index of one catalogue (section 4.2's first-level
  * partition: positions grouped by Dec zone, then RA). An index built for
  * radius r can serve as either side of hlc_xmatch_part at any radius <= r
- * built with the same zone height. Free with hlc_part_free.                 */
+ * built with the same zone height. Free with hlc_part_free, which keeps up to
+ * two partitions' memory (2 GiB in all) per device for the next hlc_partition;
+ * hlc_shutdown gives it back.                                                */
 struct hlc_part;
 int hlc_partition(const double *ra_deg, const double *dec_deg, int64_t n, double r_arcsec,
                   const hlc_opts *opts, struct hlc_part **out);
@@ -212,8 +214,8 @@ int hlc_xmatch_part(const struct hlc_part *A, const struct hlc_part *B, double r
  * to thousands of calculation blocks at once). Job j matches
  * A[a_off, a_off+na) against B[b_off, b_off+nb) at radius r_arcsec; job
  * ranges may overlap. Each job is partitioned in a local frame derived from
- * its own sources; all jobs share one sort and one persistent match launch
- * over a cost-ordered work queue. Repeated calls with the same arguments
+ * its own sources; all jobs share the launches of one partition and one
+ * persistent match. Repeated calls with the same arguments
  * replay a captured HIP graph.
  *   jobs [njobs]: HOST array, 0 <= njobs <= 65536; r_arcsec in (0, 3600].
  *   a_ra..b_dec: device arrays holding all jobs; the sum of na and the sum

@@ -25,7 +25,8 @@ namespace hlc {
 
 namespace {
 
-constexpr uint32_t PO_MEAN = 768;        // mean pairs per bucket up to PO_RUNS buckets (a self-match, i < j, has twice that first)
+// mean pairs per bucket up to PO_RUNS buckets (a self-match, i < j, has twice that first)
+constexpr uint32_t PO_MEAN = 768;
 constexpr uint32_t PO_RUNS = 1024;       // buckets up to which a scatter tile leaves in runs of 8 records
 constexpr uint32_t PO_MEAN_L = 10240;    // mean that more buckets keep, up to PO_BUCKETS of them
 constexpr uint32_t PO_BUCKETS = 2048;

@@ -57,7 +57,8 @@ __global__ __launch_bounds__(1024) void k_zero_counters(Counters* c, uint32_t* f
   uint32_t* p = reinterpret_cast<uint32_t*>(c);
   for (uint32_t i = threadIdx.x; i < sizeof(Counters) / 4; i += blockDim.x) p[i] = 0u;
   if (fill)
-    for (uint32_t i = threadIdx.x; i < (uint32_t)NREG; i += blockDim.x) fill[i * REG_STRIDE] = cfill[i * REG_STRIDE] = 0ull;
+    for (uint32_t i = threadIdx.x; i < (uint32_t)NREG; i += blockDim.x)
+      fill[i * REG_STRIDE] = cfill[i * REG_STRIDE] = 0ull;
   for (uint32_t* f : {f1, f2})
     if (f)
       for (uint32_t i = threadIdx.x; i < BS_FINE / 4; i += blockDim.x)
