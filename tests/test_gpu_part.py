@@ -142,3 +142,32 @@ def test_part_memory_reuse(hlc, sizes):
         assert np.abs(sep[:m].cpu().numpy() - ref.sep).max(initial=0.0) <= 1e-9
         pa.free()
     pb.free()
+
+
+@pytest.mark.parametrize("prec", [1, 0])
+@pytest.mark.parametrize("n", [3000, 1835009])  # bucket sort, digit sort
+def test_part_ties_after_inputs_change(hlc, n, prec):
+    """Pairs exactly at the radius, and an ulp to either side, are decided from the (ra, dec) that a partition keeps, not
+    from the caller's arrays, which hold something else by then."""
+    rng = np.random.default_rng(n)
+    r = 3600.0 * 2.0 ** -10  # arcsec: 2^-10 degrees on a meridian
+    a_ra, a_dec = rng.uniform(0, 360, n), np.degrees(np.arcsin(rng.uniform(-0.9, 0.9, n)))
+    b_ra, b_dec = rng.uniform(0, 360, n), np.degrees(np.arcsin(rng.uniform(-0.9, 0.9, n)))
+    m = 300
+    at, bt = rng.choice(n, m, replace=False), rng.choice(n, m, replace=False)
+    at[0], bt[1] = n - 1, n - 1
+    a_ra[at] = b_ra[bt] = rng.integers(0, 360 * 256, m) * 2.0 ** -8
+    a_dec[at] = rng.integers(-50 * 256, 50 * 256, m) * 2.0 ** -8
+    far = a_dec[at] + 2.0 ** -10
+    b_dec[bt] = np.where(np.arange(m) % 3 == 0, far, np.nextafter(far, np.where(np.arange(m) % 3 == 1, 90.0, -90.0)))
+    ref = oracle.xmatch(a_ra, a_dec, b_ra, b_dec, r)
+    t = [to_dev(x) for x in (a_ra, a_dec, b_ra, b_dec)]
+    (s1, PA), (s2, PB) = hlc.hlc_partition(t[0], t[1], r), hlc.hlc_partition(t[2], t[3], r)
+    assert s1 == hlc.HLC_OK and s2 == hlc.HLC_OK
+    for x in t:
+        x.fill_(1.0)
+    keys, sep = _run(hlc, PA, PB, r, prec, len(ref) + 1000)
+    assert hlc.last_stats()["n_ties"] > 0
+    assert_same(keys, sep, ref, label=f"ties {n}")
+    PA.free()
+    PB.free()
