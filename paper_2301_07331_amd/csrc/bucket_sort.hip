@@ -221,7 +221,8 @@ __global__ __launch_bounds__(BS_THREADS) void k_bs_scatter(BucketSide first, Buc
   }
 }
 
-// A bucket in order. Keys, indices and places pass through LDS to leave in
+// A bucket in order (one too full for the block is left: the call runs again).
+// Keys, indices and places pass through LDS to leave in
 // whole lines; the (ra, dec) are read from the bucket's stretch.
 template <uint32_t CAP, uint32_t T, bool DIRECT>
 __global__ __launch_bounds__(T, CAP <= 4096 ? 8 : 4) void k_bs_bucket(BucketSide first, BucketSide second) {
@@ -236,7 +237,6 @@ __global__ __launch_bounds__(T, CAP <= 4096 ? 8 : 4) void k_bs_bucket(BucketSide
   if constexpr (DIRECT) {
     m = in.cnt.get();
   } else {
-    if (in.over && *in.over) return;
     s0 = in.starts[blk];
     m = in.starts[blk + 1] - s0;
   }
@@ -322,7 +322,6 @@ void launch_bucket_sort(const BucketSide& a, const BucketSide* b, unsigned long 
     x->in.starts = x->w.starts;
     x->in.kv = x->w.kv;
     x->in.rd = x->w.rd;
-    x->in.over = &cnt->sort_over;
   }
   const uint32_t K = first.p.K + second.p.K, chunks = first.p.chunks + second.p.chunks;
   if (first.p.direct) {

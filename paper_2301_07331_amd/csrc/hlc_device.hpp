@@ -56,15 +56,21 @@ struct Geom {
 // buffer capacity. Kernels read it instead of taking the count from the host,
 // so a call needs no host round-trip before its sort and can be captured.
 // Launch grids are sized from `cap`.
-struct DevCount {
+struct EntryCount {
   uint32_t base, cap;
   const unsigned long long* extra;
-  const unsigned int* none = nullptr;  // device flag: set, there are no entries
   __device__ uint32_t get() const {
-    if (none && *none) return 0u;
     unsigned long long v = (unsigned long long)base + (extra ? *extra : 0ull);
     return v < cap ? (uint32_t)v : cap;
   }
+};
+// The count as the kernels after a sort see it: none once the sort has set its
+// flag. The sort's own kernels take the EntryCount: one that sets the flag, or
+// runs beside one that does, would read it as 0 in some waves of a block and as
+// 1 in others, and what those leave unwritten in LDS would be used as places.
+struct DevCount : EntryCount {
+  const unsigned int* none = nullptr;  // device flag: set, there are no entries
+  __device__ uint32_t get() const { return none && *none ? 0u : EntryCount::get(); }
 };
 
 // Per-group B candidate ranges (positions in the sorted B arrays).

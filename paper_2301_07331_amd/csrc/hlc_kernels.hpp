@@ -162,11 +162,10 @@ struct BucketIn {
   const uint32_t *keys, *vals;  // unsorted; entry i < n_src is source i (vals not read)
   const double *ra, *dec;       // by source
   uint32_t n_src;
-  DevCount cnt;
+  EntryCount cnt;
   const uint32_t* starts;  // (set by the launcher, as the rest)
   const uint2* kv;
   const double2* rd;
-  const unsigned int* over;
 };
 // sorted; each of the records may be null
 struct BucketOut {

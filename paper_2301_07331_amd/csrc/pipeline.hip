@@ -25,15 +25,15 @@ static unsigned long long fine_mul(const Geom& g) {
 static KeygenSample keygen_sample(const Side& sd, const Geom& g) {
   return KeygenSample{sd.plan.direct ? nullptr : sd.bws.fine, bucket_sample_mask(sd.n_src, sd.plan), fine_mul(g)};
 }
-// entries of a bucket-sorted side: none if a bucket outgrew its block
+// entries of a bucket-sorted side: none, for what follows both sorts, if a bucket
+// of either outgrew its block
 static DevCount sort_count(Device& dev, uint32_t n, bool halo) {
   const unsigned int* none = &dev.cnt->sort_over;
   return halo ? DevCount{n, 2 * n, &dev.cnt->n_halo, none} : DevCount{n, n, nullptr, none};
 }
 static BucketSide bucket_side(const Side& sd, const SortScratch& sc) {
   return BucketSide{sd.plan,
-                    BucketIn{sc.keys_alt, sc.vals_alt, sd.ra, sd.dec, sd.n_src, sd.cnt, nullptr, nullptr, nullptr,
-                             nullptr},
+                    BucketIn{sc.keys_alt, sc.vals_alt, sd.ra, sd.dec, sd.n_src, sd.cnt, nullptr, nullptr, nullptr},
                     BucketOut{sd.keys, sd.vals, sd.r64, sd.r32, sd.radec}, sd.bws};
 }
 
