@@ -37,10 +37,15 @@ struct BatchPlan {
 // (20,000 of 64 sources: 890 us either way; of 128: 960 and 1,050; 60,000 of
 // 30: 1,980 and 1,790) or so few that the launches count more (100 of 30: 225
 // and 335). Blocks of 1,024 entries below a mean of 700 (10,000 of 512: 930 us,
-// 1,180 by digits). Fewer than JOB_ORDER_JOBS jobs keep the digit sort: a call
-// with one job of 20,000 sources ended in a segmentation fault of the host
-// process once, without a GPU fault; its cause was not found (the host code is
-// clean under the address and undefined-behaviour sanitizers).
+// 1,180 by digits). Fewer than JOB_ORDER_JOBS jobs keep the digit sort: an
+// autotuned call with one job of 20,000 sources ended in a segmentation fault
+// of the host process once, without a GPU fault. No cause was found: run
+// thread by thread on a CPU, every kernel of a batched call stays within its
+// buffers and its LDS under the address sanitizer (job sizes at the pieces'
+// edges, clumps, one key repeated, the tuner's factors and tiles, that call
+// among them), and so does the host code. What is left is the end of graphs
+// whose replay had only just been waited for, which no longer happens (see
+// BatchState::old_exec); the limit stays because that does not prove it.
 constexpr int64_t JOB_ORDER_MAX = 1 << 18;
 constexpr uint64_t JOB_ORDER_READS = 20, JOB_ORDER_MEAN_MIN = 64, JOB_ORDER_MEAN_SMALL = 700;
 constexpr int32_t JOB_ORDER_JOBS = 16, JOB_ORDER_FEW = 4096;
@@ -159,6 +164,11 @@ struct BatchState {  // per device
   hipGraphExec_t exec = nullptr;
   hipGraph_t graph = nullptr;
   uint64_t graph_key = 0;
+  // graphs that are not replayed any more: destroyed only after a later one's
+  // replay on st has been waited for, when nothing of their own replays can be
+  // in flight, in the runtime's threads included
+  std::vector<hipGraphExec_t> old_exec;
+  std::vector<hipGraph_t> old_graph;
   int ncu = 256;
   // the last batch's plan, reused while the caller's job table repeats
   BatchPlan plan;
@@ -169,9 +179,19 @@ struct BatchState {  // per device
 };
 BatchState g_bstate[MAX_DEVICES];
 
+void destroy_old_graphs(BatchState& B) {
+  for (hipGraphExec_t e : B.old_exec) (void)hipGraphExecDestroy(e);
+  for (hipGraph_t e : B.old_graph) (void)hipGraphDestroy(e);
+  B.old_exec.clear();
+  B.old_graph.clear();
+}
+
+// (the one before it goes now, so that the next finds its memory)
 void drop_graph(BatchState& B) {
-  if (B.exec) (void)hipGraphExecDestroy(B.exec);
-  if (B.graph) (void)hipGraphDestroy(B.graph);
+  if (!B.graph) return;
+  destroy_old_graphs(B);
+  if (B.exec) B.old_exec.push_back(B.exec);
+  B.old_graph.push_back(B.graph);
   B.exec = nullptr;
   B.graph = nullptr;
   B.graph_key = 0;
@@ -520,16 +540,6 @@ int batch_impl(const hlc_job* jobs, int32_t njobs, const double* a_ra, const dou
       // the call itself does, as a captured graph: one untimed replay, then
       // the best of two timed ones
       drop_graph(BS);
-      // (the candidates' graphs go once the device is idle)
-      struct Graphs {
-        std::vector<hipGraph_t> g;
-        std::vector<hipGraphExec_t> x;
-        ~Graphs() {
-          (void)hipDeviceSynchronize();
-          for (hipGraphExec_t e : x) (void)hipGraphExecDestroy(e);
-          for (hipGraph_t e : g) (void)hipGraphDestroy(e);
-        }
-      } graphs;
       auto timed = [&](const BatchConfig& k, double* ms_out) -> int {
         HLC_CHECK(ensure_plan(BS, jobs, njobs, k.tile));
         HLC_CHECK(ensure_tables(BS, s));
@@ -538,9 +548,9 @@ int batch_impl(const hlc_job* jobs, int32_t njobs, const double* a_ra, const dou
         HLC_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
         batch_enqueue(*dev, BS, BS.plan, b, a_ra, a_dec, b_ra, b_dec, out_pairs, sep, cap, jc, k, fp32, s);
         HLC_TRY(hipStreamEndCapture(s, &gr));
-        graphs.g.push_back(gr);
+        BS.old_graph.push_back(gr);
         hipError_t e = hipGraphInstantiate(&ex, gr, nullptr, nullptr, 0);
-        if (e == hipSuccess) graphs.x.push_back(ex);
+        if (e == hipSuccess) BS.old_exec.push_back(ex);
         double best = 1e30;
         for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {
           if ((e = hipEventRecord(BS.ev_t0, s)) != hipSuccess) break;
@@ -618,6 +628,7 @@ int batch_impl(const hlc_job* jobs, int32_t njobs, const double* a_ra, const dou
     if (prof) HLC_TRY(hipEventRecord(BS.ev_t1, s));
     HLC_TRY(hipMemcpyAsync(dev->cnt_host, dev->cnt, sizeof(Counters), hipMemcpyDeviceToHost, s));
     HLC_TRY(hipStreamSynchronize(s));
+    if (BS.old_graph.size() > 1) destroy_old_graphs(BS);  // the tuner's
     HLC_TRY(hipEventRecord(BS.ev_out, s));
     HLC_TRY(hipStreamWaitEvent(us, BS.ev_out, 0));
     const Counters& h = *dev->cnt_host;
@@ -656,6 +667,8 @@ int batch_impl(const hlc_job* jobs, int32_t njobs, const double* a_ra, const dou
 void batch_release_all() {
   for (auto& B : g_bstate) {
     drop_graph(B);
+    if (B.st) (void)hipStreamSynchronize(B.st);
+    destroy_old_graphs(B);
     if (B.tables) (void)hipFree(B.tables);
     if (B.st) (void)hipStreamDestroy(B.st);
     if (B.st2) (void)hipStreamDestroy(B.st2);
