@@ -7,6 +7,12 @@
 namespace hlc {
 
 constexpr uint32_t BIN_FULL = 12;  // keys in a bin of an ordering block
+// Keys in a bin of the second binning beyond which a network of exchanges takes
+// over. A bin of n keys costs each of them n steps: 8,192 sources (of 2,000 to
+// match) of one key took 4,066 us a call by ranks and take 301 by the network,
+// of 8 keys 620 and 213, of 16 keys 375 and 203; of 32 keys, 254 sources each,
+// 248 by ranks.
+constexpr uint32_t BIN_RANKED = 256;
 
 // Exclusive scan of one value per thread over a block of NW waves.
 template <int NW>
@@ -41,16 +47,67 @@ struct OrderLds {
   uint32_t c[BINS + 1 + CAP / 2];  // a word per bin, then 16-bit counts, two a word
   uint32_t red[2][NW];
   uint32_t w[NW];
-  uint32_t most;
+  uint32_t most;  // 1: a bin holds more than BIN_FULL keys; 2: BIN_RANKED in the second binning
 };
+
+// at[j] as order_block's, by a compare-exchange network in LDS: log^2 steps
+// whatever the keys. Every exchange puts the smaller key first, so the places
+// from m on need not exist.
+template <uint32_t CAP, uint32_t T>
+__device__ inline void order_network(uint32_t* s_key, uint16_t* s_src, const uint32_t (&key)[CAP / T],
+                                     uint32_t (&at)[CAP / T], uint32_t m) {
+  constexpr uint32_t PER = CAP / T;
+  const uint32_t t = threadIdx.x;
+#pragma unroll
+  for (uint32_t j = 0; j < PER; ++j)
+    if (t + j * T < m) {
+      s_key[t + j * T] = key[j];
+      s_src[t + j * T] = (uint16_t)(t + j * T);
+    }
+  __syncthreads();
+  auto exchange = [&](uint32_t x, uint32_t y) {
+    if (y >= m) return;
+    const uint32_t kx = s_key[x], ky = s_key[y];
+    if (kx <= ky) return;
+    const uint16_t ix = s_src[x];
+    s_key[x] = ky;
+    s_key[y] = kx;
+    s_src[x] = s_src[y];
+    s_src[y] = ix;
+  };
+  uint32_t n2 = 2;
+  while (n2 < m) n2 <<= 1;
+  for (uint32_t k = 2; k <= n2; k <<= 1) {
+    for (uint32_t p = t; p < n2 / 2; p += T) {
+      const uint32_t i = p & (k / 2 - 1u), base = (p - i) * 2u;
+      exchange(base + i, base + k - 1u - i);
+    }
+    __syncthreads();
+    for (uint32_t j = k >> 2; j > 0; j >>= 1) {
+      for (uint32_t p = t; p < n2 / 2; p += T) {
+        const uint32_t x = 2u * p - (p & (j - 1u));
+        exchange(x, x + j);
+      }
+      __syncthreads();
+    }
+  }
+  // each place's rank, where the keys were
+  uint16_t* const s_at = reinterpret_cast<uint16_t*>(s_key);
+  for (uint32_t p = t; p < m; p += T) s_at[s_src[p]] = (uint16_t)p;
+  __syncthreads();
+#pragma unroll
+  for (uint32_t j = 0; j < PER; ++j)
+    if (t + j * T < m) at[j] = s_at[t + j * T];
+}
 
 // at[j]: the rank of key[j] (thread t's key of place t + j T) among the m keys.
 // The keys are binned in BINS bins evenly between the smallest and the largest;
 // where a bin holds more than BIN_FULL, each of those again in as many bins
 // evenly as it holds keys, so that a clump, which fills few of the first, is
 // spread over the second. A key's rank is its bin's start and the number of
-// smaller keys in the bin. Every thread of the block calls it; no thread may
-// still read L.
+// smaller keys in the bin; where even the second binning leaves more than
+// BIN_RANKED keys in a bin (one key many times: no binning splits it), a network
+// takes over. Every thread of the block calls it; no thread may still read L.
 template <uint32_t CAP, uint32_t T>
 __device__ inline void order_block(OrderLds<CAP, T>& L, const uint32_t (&key)[CAP / T], uint32_t (&at)[CAP / T],
                                    uint32_t m) {
@@ -136,13 +193,19 @@ __device__ inline void order_block(OrderLds<CAP, T>& L, const uint32_t (&key)[CA
       }
     __syncthreads();
     constexpr uint32_t PW = CAP / 2 / T;
-    uint32_t c[PW], sum = 0u, tot;
+    uint32_t c[PW], sum = 0u, most = 0u, tot;
 #pragma unroll
     for (uint32_t k = 0; k < PW; ++k) {
       c[k] = c2[t * PW + k];
       sum += (c[k] & 0xffffu) + (c[k] >> 16);
+      most = max(most, max(c[k] & 0xffffu, c[k] >> 16));
     }
+    if (__any(most > BIN_RANKED) && (t & 63u) == 0u) L.most = 2u;
     uint32_t run = scan_block<NW>(sum, &tot, L.w);
+    if (L.most == 2u) {
+      order_network<CAP, T>(L.key, reinterpret_cast<uint16_t*>(c2), key, at, m);
+      return;
+    }
 #pragma unroll
     for (uint32_t k = 0; k < PW; ++k) {
       const uint32_t mid = run + (c[k] & 0xffffu);
