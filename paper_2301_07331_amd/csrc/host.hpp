@@ -349,7 +349,6 @@ inline KeyIndex key_index_dims(const Geom& g) {
 }
 
 struct MatchWs {
-  uint32_t* lb;
   uint32_t* kidx;
   GroupRanges* ranges;
   int32_t* zmarg;

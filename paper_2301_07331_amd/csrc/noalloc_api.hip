@@ -136,6 +136,13 @@ int noalloc_impl(const double* a_ra, const double* a_dec, int64_t na, const doub
       sizing = Carve{nullptr};
       lay(sizing);
     }
+    for (int k = 0; k < 3 && sizing.off + 256 > ctx.ws_bytes && !(tuned_height(o) > 0); ++k) {
+      // and so do fewer zones, up to those of a group's square (a call of
+      // 98,944 x 989,440 sources along a meridian fits with these only)
+      g = make_geom(r_arcsec, 2.0 * 3600.0 * g.h_deg, na, nb, tuned_bins(o), f);
+      sizing = Carve{nullptr};
+      lay(sizing);
+    }
     g.frac_sorted = B.plan.K || tuned_fraction_sort(o) ? 1 : 0;
     if (sizing.off + 256 > ctx.ws_bytes) return HLC_E_UNSUPPORTED;  // beyond the scratch array
     Carve c{static_cast<char*>(ctx.ws)};

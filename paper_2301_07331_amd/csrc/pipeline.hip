@@ -320,7 +320,6 @@ size_t carve_match_ws(Carve& c, MatchWs& w, uint32_t na_entries, const Geom& g, 
   w.band = c.take<uint2>(band_cap);
   w.band_cap = band_cap;
   carve_regions(c, w.reg, caps, true);
-  w.lb = c.take<uint32_t>(nA);
   w.ranges = c.take<GroupRanges>((nA + GROUP - 1) / GROUP);
   w.zmarg = c.take<int32_t>((size_t)g.nz);
   w.kidx = c.take<uint32_t>(key_index_dims(g).T);

@@ -312,7 +312,7 @@ int hlc_xmatch_quad(const double* a_ra, const double* a_dec, int64_t na, const d
       Side A, B;
       SortScratch sc;
       MatchWs w;
-      uint32_t* msplit = nullptr;
+      uint32_t *msplit = nullptr, *lb = nullptr;
       Geom g{};
       set_radius(g, r_arcsec);
       g.rb = 0;  // keys are pixels: a candidate must share the A entry's pixel
@@ -325,6 +325,7 @@ int hlc_xmatch_quad(const double* a_ra, const double* a_dec, int64_t na, const d
         carve_sort(c, sc, std::max(capA, capB));
         carve_match_ws(c, w, capA, g, caps, false);
         msplit = c.take<uint32_t>(merge_splits_len(capA, capB));
+        lb = c.take<uint32_t>(capA);
       };
       Carve sz{nullptr};
       lay(sz);
@@ -345,8 +346,8 @@ int hlc_xmatch_quad(const double* a_ra, const double* a_dec, int64_t na, const d
       launch_layout64(B.vals, B.cnt, b_ra, b_dec, B.r64, s);
       launch_radec_gather(A.vals, A.cnt, a_ra, a_dec, A.radec, s);
       launch_radec_gather(B.vals, B.cnt, b_ra, b_dec, B.radec, s);
-      launch_merge_lb(A.keys, A.cnt, B.keys, B.cnt, msplit, w.lb, s);
-      launch_equal_ranges(A.keys, A.cnt, w.lb, B.keys, B.cnt, w.ranges, s);
+      launch_merge_lb(A.keys, A.cnt, B.keys, B.cnt, msplit, lb, s);
+      launch_equal_ranges(A.keys, A.cnt, lb, B.keys, B.cnt, w.ranges, s);
       const Thresholds th = thresholds(r_arcsec);
       MatchArgs ma{};
       ma.ranges = w.ranges;
