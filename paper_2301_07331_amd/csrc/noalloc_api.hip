@@ -69,12 +69,12 @@ static_assert(sizeof(Counters) <= 256, "counters must fit before the workspace")
 // call's floors of 4096 slots per region would take most of it); a call
 // that exceeds them runs again with the counted sizes, as hlc_xmatch does.
 // Pairs go straight into the caller's buffer: no pair slots.
-Caps scratch_caps(const ScratchDev& d, uint64_t entries, uint64_t cap) {
-  (void)cap;
+uint64_t cand_estimate(uint64_t entries) { return entries / (2 * NREG) + 64; }
+Caps scratch_caps(const ScratchDev& d, uint64_t entries) {
   Caps k;
   k.band = 1024 + entries / 64;
   k.stage = 0;
-  k.cand = std::max<uint64_t>(entries / (2 * NREG) + 64, d.hint_cand);
+  k.cand = std::max(cand_estimate(entries), d.hint_cand);
   return k;
 }
 
@@ -113,7 +113,7 @@ int noalloc_impl(const double* a_ra, const double* a_dec, int64_t na, const doub
   const Frame f = (!box.any || quarter_sky(box)) ? Frame{} : frame_of_box(box);
   Geom g = make_geom(r_arcsec, tuned_height(o), na, nb, tuned_bins(o), f);
   const uint32_t nA = (uint32_t)na, nB = (uint32_t)nb;
-  Caps caps = scratch_caps(*sd, (uint64_t)(na + nb), (uint64_t)o->capacity);
+  Caps caps = scratch_caps(*sd, (uint64_t)(na + nb));
   double* sep = (o->flags & HLC_NO_SEP) ? nullptr : out_sep;
   for (int attempt = 0; attempt < 4; ++attempt) {
     Side A, B;
@@ -130,6 +130,12 @@ int noalloc_impl(const double* a_ra, const double* a_dec, int64_t na, const doub
     };
     Carve sizing{nullptr};
     lay(sizing);
+    if (sizing.off + 256 > ctx.ws_bytes && attempt == 0) {
+      // without the room for candidates that an earlier call wanted
+      caps.cand = cand_estimate((uint64_t)(na + nb));
+      sizing = Carve{nullptr};
+      lay(sizing);
+    }
     if (sizing.off + 256 > ctx.ws_bytes && (A.plan.K || B.plan.K)) {
       // the digit sort needs less scratch
       A.plan = B.plan = BucketPlan{};
