@@ -32,10 +32,11 @@
  *     a caller pointer after a call returns.
  *   - The library owns a per-device workspace, grown on demand and released
  *     by hlc_shutdown(), and every hlc_part it hands out.
- *   - A call on a device sizes its staging buffers, and (FP32) chooses how
- *     it lays out B's coordinates for the certification, from what earlier
- *     calls on that device counted; results never depend on this, only the
- *     time does.
+ *   - A call on a device sizes its staging buffers, chooses how it sorts
+ *     catalogues of sizes that were crowded before, which pass over the
+ *     footprint goes first and (FP32) how it lays out B's coordinates for the
+ *     certification from what earlier calls on that device found; results
+ *     never depend on this, only the time does.
  *
  * Errors: every int-returning call returns HLC_OK (0) or a negative
  * hlc_status; no C++ exception crosses this boundary. HIP runtime failures

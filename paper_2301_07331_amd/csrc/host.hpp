@@ -53,6 +53,44 @@ struct PoolBlock {
 constexpr int POOL_BLOCKS = 2;
 constexpr size_t POOL_BYTES = size_t(2) << 30;
 
+// Sizes of calls in which a bucket outgrew its block: calls of these sizes take
+// the digit sort at once for a number of times, twice as many whenever they
+// overflow again, so that a crowded catalogue matched over and over rarely pays
+// for the attempt and calls of other sizes never for it. (A partition's second
+// size is -1.)
+struct OverflowNotes {
+  static constexpr int KEPT = 4, FIRST = 15, MOST = 1000;
+  struct Note {
+    int64_t na = -1, nb = -1;
+    int left = 0, next = FIRST;
+  } at[KEPT];
+  int newest = 0;
+  Note* find(int64_t na, int64_t nb) {
+    for (Note& n : at)
+      if (n.na == na && n.nb == nb) return &n;
+    return nullptr;
+  }
+  // the call takes the digit sort
+  bool take(int64_t na, int64_t nb) {
+    Note* n = find(na, nb);
+    if (!n || n->left == 0) return false;
+    --n->left;
+    return true;
+  }
+  void add(int64_t na, int64_t nb) {
+    Note* n = find(na, nb);
+    if (!n) {
+      newest = (newest + 1) % KEPT;
+      n = &at[newest];
+      *n = Note();
+      n->na = na;
+      n->nb = nb;
+    }
+    n->left = n->next;
+    n->next = std::min(2 * n->next, MOST);
+  }
+};
+
 struct Device {
   bool init = false;
   PoolBlock pool[POOL_BLOCKS];  // under the pool's lock
@@ -84,7 +122,7 @@ struct Device {
   double cand_per_b = 0.0;
   int ncu = 0;  // compute units (persistent grids)
   bool last_full = true;  // the last call's frame was the whole sphere
-  int digit_calls = 0;        // calls left that take the digit sort at once
+  OverflowNotes overflows;
   bool last_crowded = false;  // and its sources were crowded (what a speculative keygen assumes)
   // mapped host memory: what kernels tell the host without a copy
   HostMsg* msg = nullptr;
@@ -424,10 +462,6 @@ void carve_sort(Carve& c, SortScratch& sc, uint32_t nmax, Side& sd);
 inline BucketPlan plan_sort(int64_t n, bool digit_sort) {
   return digit_sort || n < 1 || n > (int64_t)BS_MAX ? BucketPlan{} : bucket_plan((uint32_t)n);
 }
-// A bucket outgrew its block: the call runs again with the digit sort, and the
-// next DIGIT_CALLS calls on the device take it at once.
-constexpr int DIGIT_CALLS = 15;
-
 // the coordinates checked (no pairs: one side is empty)
 int validate_only(const double* a_ra, const double* a_dec, int64_t na, const double* b_ra,
                   const double* b_dec, int64_t nb, double r_arcsec, const hlc_opts* o);

@@ -29,6 +29,7 @@ struct ScratchDev {
   Counters host_cnt;              // host copies (plain memory): the counters,
   ExtentSlot host_ext[EXTENT_SLOTS];  // the footprint slots
   uint64_t hint_stage = 0, hint_cand = 0;
+  OverflowNotes overflows;
 };
 ScratchDev g_scratch[MAX_DEVICES];
 
@@ -114,6 +115,7 @@ int noalloc_impl(const double* a_ra, const double* a_dec, int64_t na, const doub
   Geom g = make_geom(r_arcsec, tuned_height(o), na, nb, tuned_bins(o), f);
   const uint32_t nA = (uint32_t)na, nB = (uint32_t)nb;
   Caps caps = scratch_caps(*sd, (uint64_t)(na + nb));
+  caps.digit_sort = sd->overflows.take(na, nb);
   double* sep = (o->flags & HLC_NO_SEP) ? nullptr : out_sep;
   for (int attempt = 0; attempt < 4; ++attempt) {
     Side A, B;
@@ -172,6 +174,7 @@ int noalloc_impl(const double* a_ra, const double* a_dec, int64_t na, const doub
       return HLC_E_INVAL;
     }
     if (h.sort_over) {
+      sd->overflows.add(na, nb);
       caps.digit_sort = true;
       continue;
     }

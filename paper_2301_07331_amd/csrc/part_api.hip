@@ -56,12 +56,13 @@ int hlc_partition(const double* ra_deg, const double* dec_deg, int64_t n, double
     if (!(h_as > 0)) h_as = std::min(std::max(64.0 * r_arcsec, 32.0), 3600.0);
     const uint32_t nn = (uint32_t)n, cap = 2 * nn;
     // (attempt 1: the digit sort, where a bucket outgrew its block)
+    const bool digit_sort = dev->overflows.take(n, -1);
     for (int attempt = 0; attempt < 2; ++attempt) {
       auto* p = new hlc_part();
       p->device = dev_id;
       p->r_build = r_arcsec;
       p->g = make_geom(r_arcsec, h_as, n, n, tuned_bins(opts));
-      p->side.plan = plan_sort(n, attempt > 0);
+      p->side.plan = plan_sort(n, digit_sort || attempt > 0);
       p->g.frac_sorted = p->side.plan.K ? 1 : 0;
       auto lay = [&](Carve& c) {
         // FP32: sorted (ra, dec) kept with the part for the certification, and
@@ -113,6 +114,7 @@ int hlc_partition(const double* ra_deg, const double* dec_deg, int64_t n, double
       }
       release_part(p, st == HLC_OK);
       if (st != HLC_OK) return st;
+      dev->overflows.add(n, -1);
     }
     return HLC_E_DEVICE;
   } catch (const std::bad_alloc&) {

@@ -183,7 +183,7 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
     return HLC_E_INVAL;
   }
   if (h.sort_over) {
-    dev->digit_calls = DIGIT_CALLS;
+    dev->overflows.add(na, nb);
     caps.digit_sort = true;
     *again = true;
     return HLC_OK;
@@ -208,10 +208,7 @@ int xmatch_core(const double* a_ra, const double* a_dec, int64_t na, const doubl
   Device* dev = nullptr;
   HLC_CHECK(get_device(&dev));
   Caps caps = initial_caps(*dev, (uint64_t)(na + nb), (uint64_t)o->capacity, true, false);
-  if (dev->digit_calls > 0) {
-    --dev->digit_calls;
-    caps.digit_sort = true;
-  }
+  caps.digit_sort = dev->overflows.take(na, nb);
   for (int attempt = 0; attempt < 4; ++attempt) {
     bool again = false;
     int st = xmatch_impl(a_ra, a_dec, na, b_ra, b_dec, nb, r_arcsec, out_pairs, out_sep, o, caps, &again, rad);
