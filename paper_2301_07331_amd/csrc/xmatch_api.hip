@@ -375,7 +375,7 @@ int hlc_xmatch_quad(const double* a_ra, const double* a_dec, int64_t na, const d
                                   (uint64_t)opts->capacity, w.band, w.band_cap, w.reg, dev->cnt);
       launch_regions_reset(oa, s);
       launch_filter(ma, oa, false, 1, s);
-      launch_cand(ma, oa, false, s);
+      launch_cand(ma, oa, false, true, s);
       launch_certify({a_ra, a_dec}, {b_ra, b_dec}, r_arcsec, th.H_lo, th.H_hi, Radii{nullptr, nullptr, 0.0}, oa, s);
       launch_compact(oa, s);
       HLC_CHECK(read_counters(*dev, s, false));
