@@ -73,7 +73,7 @@ def recorded_traffic():
     return float(fields["traffic_bytes"])
 
 
-def traffic_from_pmc(fetch_dir, write_dir, kernel="k_filter<true>"):
+def traffic_from_pmc(fetch_dir, write_dir, kernel="k_filter<true, false>"):
     """HBM bytes per launch of `kernel` from two rocprofv3 --pmc runs of
     `bench.py --copy-calibration` (FETCH_SIZE, WRITE_SIZE in KiB per
     dispatch), each scaled so that the 1 GiB device copy reads / writes 1 GiB."""

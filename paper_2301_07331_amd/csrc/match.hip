@@ -575,7 +575,11 @@ __device__ inline ARaw load_a(const MatchArgs& a, const ItemHead& h) {
 // one per 16-lane row). The next item's ranges and A index are loaded
 // while the current one is tested, and its A records once the current one's
 // chunks are done (their loads then overlap the drain of the queue).
-template <bool F32>
+// SELF: a self-match, in a kernel of its own. With its test for an entry's
+// meeting with itself in every drain step, which then waits for the position,
+// calls of many hits lost up to 10 % (2,000 x 4M, 3.1M hits: 11.3 ms a call, 10.2
+// without; as a branch in one kernel the loop over B took 3 % longer than here).
+template <bool F32, bool SELF>
 __global__ __launch_bounds__(MT, 7) void k_filter(MatchArgs a, OutArgs o) {
   using V = typename std::conditional<F32, float, double>::type;
   __shared__ uint2 s_q[WAVES][QCAP];
@@ -665,13 +669,13 @@ __global__ __launch_bounds__(MT, 7) void k_filter(MatchArgs a, OutArgs o) {
       tests<0, V>(A, B, thr, nmax, mask);
       // drain the hits into the queue, lowest bit first
       while (__ballot(mask != 0u)) {
-        const bool has = mask != 0u;
-        const uint32_t bit = has ? (uint32_t)__builtin_ctz(mask) : 0u;
+        bool push = mask != 0u;
+        const uint32_t bit = push ? (uint32_t)__builtin_ctz(mask) : 0u;
         const uint32_t bpos = (uint32_t)__shfl((int)bp, (int)((lane & 48u) | bit));
         // (a self-match's entry meets itself: dropped here, or every source
         // would be staged and certified for nothing; 4M sources, 9,000 pairs:
         // filter and certification 98 us against 223)
-        const bool push = has && !(a.self_only && bpos == cur.a_pos);
+        if constexpr (SELF) push = push && bpos != cur.a_pos;
         const uint64_t m = __ballot(push);
         if (push) q[qn + rank_in(m)] = make_uint2(cur.a_pos, bpos);
         qn += (uint32_t)__popcll(m);
@@ -805,8 +809,10 @@ void launch_filter(const MatchArgs& a, const OutArgs& o, bool fp32, int items_pe
   const uint32_t items = (ngroups + 3) / 4;
   const uint32_t per_block = WAVES * (uint32_t)std::max(items_per_wave, 1);
   const uint32_t blocks = (items + per_block - 1) / per_block;
-  if (fp32) k_filter<true><<<blocks, MT, 0, s>>>(a, o);
-  else k_filter<false><<<blocks, MT, 0, s>>>(a, o);
+  if (fp32 && a.self_only) k_filter<true, true><<<blocks, MT, 0, s>>>(a, o);
+  else if (fp32) k_filter<true, false><<<blocks, MT, 0, s>>>(a, o);
+  else if (a.self_only) k_filter<false, true><<<blocks, MT, 0, s>>>(a, o);
+  else k_filter<false, false><<<blocks, MT, 0, s>>>(a, o);
 }
 
 void launch_cand(const MatchArgs& a, const OutArgs& o, bool fp32, bool many, hipStream_t s) {
