@@ -115,7 +115,7 @@ Geom make_geom(double r_arcsec, double h_as, int64_t na, int64_t nb, int ra_bits
 
 FrameQuery frame_begin(Device& dev, const double* a_ra, const double* a_dec, int64_t na, const double* b_ra,
                        const double* b_dec, int64_t nb, bool crowd, hipStream_t s) {
-  FrameQuery q{++dev.fseq, 0u, !dev.last_full, crowd};
+  FrameQuery q{++dev.fseq, 0u, !dev.last_full && (na + nb <= EXACT_FIRST_MAX || dev.large_partial >= 2), crowd};
   if (q.exact)
     q.slots = launch_extent(a_ra, a_dec, (uint32_t)na, b_ra, b_dec, (uint32_t)nb, dev.msg_dev->ext, q.seq, s,
                             q.crowd ? &dev.msg_dev->sample : nullptr);
@@ -192,7 +192,12 @@ int frame_finish(Device& dev, FrameQuery q, const double* a_ra, const double* a_
     *crowded = met >= 8.0 * GROUP;
   }
   if (q.exact) HLC_CHECK(wait_box(dev.msg->ext, q.seq, q.slots, qs, &b));
-  if (!b.any || quarter_sky(b)) return HLC_OK;
+  const bool large = na + nb > EXACT_FIRST_MAX;
+  if (!b.any || quarter_sky(b)) {
+    if (large) dev.large_partial = 0;
+    return HLC_OK;
+  }
+  if (large) ++dev.large_partial;
   if (!q.exact) HLC_CHECK(exact_box(dev, a_ra, a_dec, na, b_ra, b_dec, nb, s, &b));
   *out = frame_of_box(b);
   return HLC_OK;

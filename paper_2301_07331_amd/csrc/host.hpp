@@ -122,6 +122,7 @@ struct Device {
   double cand_per_b = 0.0;
   int ncu = 0;  // compute units (persistent grids)
   bool last_full = true;  // the last call's frame was the whole sphere
+  int large_partial = 0;  // calls of more than EXACT_FIRST_MAX sources since one whose frame was
   OverflowNotes overflows;
   bool last_crowded = false;  // and its sources were crowded (what a speculative keygen assumes)
   // mapped host memory: what kernels tell the host without a copy
@@ -243,7 +244,12 @@ inline Box read_box(const ExtentSlot* slots, uint32_t n) {
 // a sample of both catalogues first: where its box covers over a quarter of
 // the sphere the whole sphere is the frame, otherwise one pass over every
 // source gives the exact box. After a call with a smaller frame that pass runs
-// at once (a sample would only add a round trip).
+// at once (a sample would only add a round trip). Above EXACT_FIRST_MAX sources,
+// where it takes longer than the sample, only once two such calls in a row had
+// smaller frames: 10M x 10M over the whole sphere after a patch 1,037 us a call
+// with the sample first, 1,091 with the pass; patches of 4M x 4M one after the
+// other 517 and 497; 1M x 1M after a patch 200 either way.
+constexpr int64_t EXACT_FIRST_MAX = 1 << 22;
 struct FrameQuery {
   unsigned long long seq;
   uint32_t slots;
