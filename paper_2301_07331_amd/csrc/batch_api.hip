@@ -200,7 +200,7 @@ void drop_graph(BatchState& B) {
 struct BatchBufs {
   unsigned long long* bounds;
   JobGeom* geo;
-  uint32_t *kA, *vA, *kB, *vB, *zstart, *ckey, *cval, *hcount, *hbase;
+  uint32_t *kA, *vA, *kB, *vB, *zstart, *ckey, *cval, *hcount, *hbase, *heavy;
   int32_t* zmarg;
   GroupRanges* ranges;
   Rec64 *rA64, *rB64;
@@ -244,8 +244,10 @@ void carve_batch(Carve& c, BatchBufs& b, const BatchPlan& P, bool fp32, const Ca
     b.radecA = b.radecB = nullptr;
   }
   b.ranges = c.take<GroupRanges>(ng);
-  b.ckey = b.cval = nullptr;
-  if (!P.order_cap) {
+  b.ckey = b.cval = b.heavy = nullptr;
+  if (P.order_cap) {
+    b.heavy = c.take<uint32_t>(ng);
+  } else {
     b.ckey = c.take<uint32_t>(ng);
     b.cval = c.take<uint32_t>(ng);
   }
@@ -347,7 +349,8 @@ void batch_enqueue(Device& dev, BatchState& BS, const BatchPlan& P, const BatchB
   launch_batch_zone_tables(b.geo, P.njobs, BS.d_jobs, P.ztotal, P.lb_bits, b.kB, cB, b.hcount, b.hbase, b.zmarg,
                            b.zstart, s);
   join(1);
-  launch_batch_ranges(b.kA, cA, b.kB, b.geo, P.lb_bits, b.zmarg, b.zstart, b.ranges, b.ckey, b.cval, s);
+  launch_batch_ranges(b.kA, cA, b.kB, b.geo, P.lb_bits, b.zmarg, b.zstart, b.ranges, b.ckey, b.cval, b.heavy,
+                      dev.cnt, s);
   const uint32_t ng = (NA + GROUP - 1) / GROUP;
   // Jobs too large for k_job_order: the groups by descending work, so that a
   // wave's four take as many steps each (100 jobs of 100,000: the match 405 us,
@@ -358,6 +361,7 @@ void batch_enqueue(Device& dev, BatchState& BS, const BatchPlan& P, const BatchB
   if (b.ckey) radix_sort(b.ckey, b.cval, DevCount{ng, ng, nullptr}, 32, b.sc, s);
   BatchMatchArgs ma{};
   ma.order = b.cval;
+  ma.heavy = b.heavy;
   ma.ranges = b.ranges;
   ma.na = cA;
   ma.keysA = b.kA;

@@ -90,7 +90,7 @@ struct Counters {
   unsigned long long n_ties;      // decided in double-double
   unsigned int err;               // bit 0: bad coordinate in A, bit 1: in B
   unsigned int sort_over;         // a bucket of the bucket sort outgrew its block
-  unsigned int pad_;
+  unsigned int n_heavy;           // batched form: groups in the list of heavy ones
   unsigned long long aux[2];      // entry counts of multi-entry keygens (A, B)
   unsigned long long region_max;  // largest pair-region fill (compaction)
   unsigned long long cand_max;    // largest candidate-region fill

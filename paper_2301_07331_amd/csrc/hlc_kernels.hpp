@@ -460,6 +460,7 @@ struct JobGeom {           // the job's local frame (computed on the device)
 };
 struct BatchMatchArgs {
   const uint32_t* order;   // the groups in the order they are taken (nullptr: their own)
+  const uint32_t* heavy;   // those taken before all others (cnt->n_heavy; nullptr: none)
   const GroupRanges* ranges;
   DevCount na;
   const uint32_t* keysA;
@@ -514,10 +515,12 @@ void launch_batch_layout32(const uint32_t* keys, const uint32_t* vals, const Dev
 void launch_batch_zone_tables(const JobGeom* geo, int32_t njobs, const BatchJob* jobs, uint32_t ztotal,
                               int32_t lb_bits, const uint32_t* keysB, const DevCount& nb, const uint32_t* hcount,
                               const uint32_t* hbase, int32_t* zmarg, uint32_t* zstart, hipStream_t s);
-// cost_key, cost_val: each group's work and number, for an order by work (may be null)
+// cost_key, cost_val: each group's work and number, for an order by work (may be
+// null); heavy: the list of the groups of much work, cnt->n_heavy of them (may be null)
 void launch_batch_ranges(const uint32_t* keysA, const DevCount& na, const uint32_t* keysB,
                          const JobGeom* geo, int32_t lb_bits, const int32_t* zmarg, const uint32_t* zstart,
-                         GroupRanges* out, uint32_t* cost_key, uint32_t* cost_val, hipStream_t s);
+                         GroupRanges* out, uint32_t* cost_key, uint32_t* cost_val, uint32_t* heavy, Counters* cnt,
+                         hipStream_t s);
 void launch_batch_match(const BatchMatchArgs& a, const OutArgs& o, bool fp32, uint32_t nblocks,
                         hipStream_t s);
 void launch_batch_certify(const double* a_ra, const double* a_dec, const double* b_ra, const double* b_dec,
