@@ -202,8 +202,9 @@ int hlc_xmatch_quad(const double *a_ra, const double *a_dec, int64_t na, const d
  * partition: positions grouped by Dec zone, then RA). An index built for
  * radius r can serve as either side of hlc_xmatch_part at any radius <= r
  * built with the same zone height. Free with hlc_part_free, which keeps up to
- * two partitions' memory (2 GiB in all) per device for the next hlc_partition;
- * hlc_shutdown gives it back.                                                */
+ * two partitions' memory (2 GiB in all) per device for the next hlc_partition
+ * (which takes a kept block up to twice the size that it needs); hlc_shutdown
+ * gives it back, and a partition freed after it keeps none.                  */
 struct hlc_part;
 int hlc_partition(const double *ra_deg, const double *dec_deg, int64_t n, double r_arcsec,
                   const hlc_opts *opts, struct hlc_part **out);

@@ -91,8 +91,13 @@ int pool_take(Device& d, size_t bytes, void** p, size_t* got) {
 }
 
 // (the block freed longest ago makes room: a loop's own block stays whatever
-// other programs' parts left here)
+// other programs' parts left here; a part that outlives hlc_shutdown gives its
+// memory back at once)
 void pool_put(Device& d, void* p, size_t bytes) {
+  if (!d.init) {
+    (void)hipFree(p);
+    return;
+  }
   void* out[POOL_BLOCKS + 1] = {};
   {
     std::lock_guard<std::mutex> hold(g_pool_lock);
