@@ -1,6 +1,6 @@
 """HLC_SORTED at the edges of the pair ordering: one block in LDS (up to 4,096 pairs), the bucket pass (blocks of 2,048
-or 8,192 pairs), full bins (indices in dense clusters), buckets taken in rounds and buckets far too large (digit
-sort)."""
+or 6,144 pairs), full bins (indices in dense clusters), buckets taken in rounds and too few first indices for buckets
+(digit sort). Blocks of 12,288 pairs and buckets far too large: test_gpu_pair_order_limits.py."""
 import numpy as np
 import pytest
 
