@@ -19,6 +19,7 @@
 // 700 pairs 8 us, bound by one block's chain of barriers, against 160.
 #include <hip/hip_runtime.h>
 
+#include "bucket_order.hpp"
 #include "hlc_kernels.hpp"
 
 namespace hlc {
@@ -108,32 +109,8 @@ __device__ inline PairPlan plan_of(const PairRun& r) {
   return p;
 }
 
-// Exclusive scan of one value per thread over a block of NW waves.
-template <int NW>
-__device__ inline uint32_t scan_block(uint32_t v, uint32_t* total, uint32_t* s_w) {
-  const uint32_t t = threadIdx.x, lane = t & 63u, w = t >> 6;
-  uint32_t x = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(x, off);
-    if (lane >= (uint32_t)off) x += y;
-  }
-  if (lane == 63u) s_w[w] = x;
-  __syncthreads();
-  uint32_t base = 0, tot = 0;
-#pragma unroll
-  for (int k = 0; k < NW; ++k) {
-    const uint32_t s = s_w[k];
-    if ((uint32_t)k < w) base += s;
-    tot += s;
-  }
-  __syncthreads();
-  *total = tot;
-  return base + x - v;
-}
-
 template <uint32_t CAP, uint32_t T>
-struct OrderLds {
+struct PairLds {
   static constexpr int LOG_BINS = 12;
   static constexpr uint32_t BINS = 1u << LOG_BINS;
   u64 key[CAP];
@@ -180,10 +157,10 @@ __device__ inline int shift_to(u64 diff, int want) {
 // LDS to leave in whole lines: fetched from the records by place in rank
 // order, the separations cost a line each (54 us for 4.07M pairs).
 template <uint32_t CAP, uint32_t T, class SepAt>
-__device__ inline void order_pairs(OrderLds<CAP, T>& L, const u64 (&key)[CAP / T], const uint32_t (&src)[CAP / T],
+__device__ inline void order_pairs(PairLds<CAP, T>& L, const u64 (&key)[CAP / T], const uint32_t (&src)[CAP / T],
                                    const double (&sp)[CAP / T], uint32_t m, uint2* __restrict__ pairs, double* sep,
                                    SepAt sep_at) {
-  constexpr uint32_t PER = CAP / T, BINS = OrderLds<CAP, T>::BINS;
+  constexpr uint32_t PER = CAP / T, BINS = PairLds<CAP, T>::BINS;
   const uint32_t t = threadIdx.x;
   for (uint32_t i = t; i < BINS; i += T) L.cnt[i] = 0u;
   if (t == 0) L.full = 0u;
@@ -195,7 +172,7 @@ __device__ inline void order_pairs(OrderLds<CAP, T>& L, const u64 (&key)[CAP / T
       hi = max(hi, key[j]);
     }
   block_min_max<T>(lo, hi, L.red);
-  const int sh = shift_to(hi - lo, OrderLds<CAP, T>::LOG_BINS);
+  const int sh = shift_to(hi - lo, PairLds<CAP, T>::LOG_BINS);
 #pragma unroll
   for (uint32_t j = 0; j < PER; ++j)
     if (t + j * T < m && atomicAdd(&L.cnt[(uint32_t)((key[j] - lo) >> sh)], 1u) >= PO_BIN_MAX) L.full = 1u;
@@ -314,7 +291,7 @@ __global__ __launch_bounds__(PO_THREADS_1) void k_po_block(uint2* pairs, double*
     if (found > most || found < 2ull) return;
     n = (uint32_t)found;
   }
-  __shared__ OrderLds<PAIR_ORDER_LDS, PO_THREADS_1> L;
+  __shared__ PairLds<PAIR_ORDER_LDS, PO_THREADS_1> L;
   constexpr uint32_t PER = PAIR_ORDER_LDS / PO_THREADS_1;
   u64 key[PER];
   uint32_t src[PER];
@@ -519,7 +496,7 @@ __global__ __launch_bounds__(T, CAP <= PO_CAP_M ? 8 : 4) void k_po_bucket(PairRu
   const uint32_t* __restrict__ starts = run.w.starts;
   uint2* __restrict__ pairs = run.pairs;
   double* __restrict__ sep = run.sep;
-  __shared__ OrderLds<CAP, T> L;
+  __shared__ PairLds<CAP, T> L;
   if (starts[K] == 0xffffffffu) return;  // nothing was moved
   const uint32_t t = threadIdx.x;
   const uint32_t s0 = starts[blockIdx.x], m = starts[blockIdx.x + 1] - s0;
@@ -548,7 +525,7 @@ template <uint32_t CAP, uint32_t T>
 __global__ __launch_bounds__(T) void k_po_rounds(const PairRec* __restrict__ rec,
                                                  const uint32_t* __restrict__ starts, uint32_t K, uint32_t done_cap,
                                                  uint2* __restrict__ pairs, double* __restrict__ sep) {
-  __shared__ OrderLds<CAP, T> L;
+  __shared__ PairLds<CAP, T> L;
   __shared__ uint32_t s_n;
   if (starts[K] == 0xffffffffu) return;  // nothing was moved
   const uint32_t t = threadIdx.x;
@@ -566,7 +543,7 @@ __global__ __launch_bounds__(T) void k_po_rounds(const PairRec* __restrict__ rec
   }
   block_min_max<T>(lo, top, L.red);
   uint32_t* s_outer = L.cnt;  // PO_OUTER + 1 words, done with before a round is ordered
-  static_assert(OrderLds<CAP, T>::BINS > PO_OUTER, "the splitting bins share the ordering bins' words");
+  static_assert(PairLds<CAP, T>::BINS > PO_OUTER, "the splitting bins share the ordering bins' words");
   u64 hi = top;  // the keys in [lo, top] are the m - done that are left
   for (uint32_t done = 0; done < m;) {
     const int sh = shift_to(hi - lo, 10);
