@@ -30,7 +30,6 @@ int get_device(Device** out, int* dev_id) {
     for (auto& e : d.ev) HLC_TRY(hipEventCreate(&e));
     HLC_TRY(hipDeviceGetAttribute(&d.ncu, hipDeviceAttributeMultiprocessorCount, dev));
     HLC_TRY(hipStreamCreateWithFlags(&d.side, hipStreamNonBlocking));
-    HLC_TRY(hipStreamCreateWithFlags(&d.sample, hipStreamNonBlocking));
     HLC_TRY(hipEventCreateWithFlags(&d.fork, hipEventDisableTiming));
     HLC_TRY(hipEventCreateWithFlags(&d.bsorted, hipEventDisableTiming));
     HLC_TRY(hipEventCreateWithFlags(&d.prepped, hipEventDisableTiming));
@@ -250,8 +249,7 @@ void hlc_shutdown(void) {
       if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : {d.fork, d.bsorted, d.prepped})
       if (e) (void)hipEventDestroy(e);
-    for (hipStream_t s : {d.side, d.sample})
-      if (s) (void)hipStreamDestroy(s);
+    if (d.side) (void)hipStreamDestroy(d.side);
     for (void* p : d.sarena)
       if (p) (void)hipFree(p);
     if (d.harena) (void)hipHostFree(d.harena);

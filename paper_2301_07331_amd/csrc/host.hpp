@@ -110,10 +110,6 @@ struct Device {
   double stream_rate = 0.0;
   // A's partition runs on `side` beside B's on the caller's stream
   hipStream_t side = nullptr;
-  // the footprint sample of a speculative call, beside both keygens: ahead of
-  // A's on `side` its 20 us delayed that chain (10M x 10M, unordered: FP32 1.217
-  // ms a call, 1.211 on a stream of its own; FP64 1.252, 1.245)
-  hipStream_t sample = nullptr;
   hipEvent_t fork = nullptr;
   // B sorted (the ranges start) and ranges done (the filter may start)
   hipEvent_t bsorted = nullptr, prepped = nullptr;

@@ -99,20 +99,20 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
     if (prof) HLC_TRY(hipEventRecord(dev->ev[14], s));
     clear();
     // B's on the caller's stream, launched first (B's chain is the longer
-    // one); A's keygen beside it on the side stream, where A's sort follows
-    // (the places of B's buffers do not depend on the frame either), and the
-    // sample on its own
+    // one); the sample and A's keygen beside it on the side stream, where A's
+    // sort follows (the places of B's buffers do not depend on the frame
+    // either)
     HLC_TRY(hipEventRecord(dev->fork, s));
     // (a self-match's one keygen goes ahead of the sample: 4M, 442 us a call
     // before, 420; with two, A's would wait for the sample beside B's: no gain)
-    if (self) partition_keys(*dev, b_ra, b_dec, nB, g, true, !fp32, fp32, sc, 2u, B, slB, s);
-    HLC_TRY(hipStreamWaitEvent(dev->sample, dev->fork, 0));
-    fq = frame_begin(*dev, a_ra, a_dec, na_frame, b_ra, b_dec, nb, crowd, dev->sample);
+    const bool ahead = self && !both;
+    if (ahead) partition_keys(*dev, b_ra, b_dec, nB, g, true, !fp32, fp32, sc, 2u, B, slB, s);
     HLC_TRY(hipStreamWaitEvent(dev->side, dev->fork, 0));
+    fq = frame_begin(*dev, a_ra, a_dec, na_frame, b_ra, b_dec, nb, crowd, dev->side);
     if (both) {
       partition_keys_both(*dev, a_ra, a_dec, nA, scA, A, b_ra, b_dec, nB, sc, B, g, s);
     } else {
-      if (!self) partition_keys(*dev, b_ra, b_dec, nB, g, true, !fp32, fp32, sc, 2u, B, slB, s);
+      if (!ahead) partition_keys(*dev, b_ra, b_dec, nB, g, true, !fp32, fp32, sc, 2u, B, slB, s);
       if (!self) partition_keys(*dev, a_ra, a_dec, nA, gA, false, !fp32, fp32, scA, 1u, A, slA, dev->side);
     }
   } else {
@@ -127,8 +127,7 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   }
   Frame f;
   bool crowded = false;
-  HLC_CHECK(frame_finish(*dev, fq, a_ra, a_dec, na_frame, b_ra, b_dec, nb, s, spec ? dev->sample : s, &f,
-                         &crowded));
+  HLC_CHECK(frame_finish(*dev, fq, a_ra, a_dec, na_frame, b_ra, b_dec, nb, s, spec ? dev->side : s, &f, &crowded));
   dev->last_full = is_full(f);
   const bool same_crowd = crowded == dev->last_crowded;
   dev->last_crowded = crowded;
