@@ -22,8 +22,8 @@
 //   k_bs_bucket    the order in LDS and the output
 // A catalogue that fits one block (8,192 sources) goes straight from its keys
 // to the last kernel. A bucket that outgrows its block (2,000 entries or more
-// in one part) sets Counters::sort_over: the sides then count as empty
-// and the call runs again with the digit sort.
+// in one part) sets Counters::sort_over: the sides then count as empty for
+// what follows both sorts, and the call runs again with the digit sort.
 #include <hip/hip_runtime.h>
 
 #include "bucket_order.hpp"

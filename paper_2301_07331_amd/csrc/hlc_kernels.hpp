@@ -400,8 +400,7 @@ void launch_compact(const OutArgs& o, hipStream_t s);
 // the filter writes candidates into the candidate regions; the
 // certification kernel decides them and writes pairs and the band list
 void launch_filter(const MatchArgs& a, const OutArgs& o, bool fp32, int items_per_wave, hipStream_t s);
-// (many: more candidates are expected than the estimate of the staging)
-void launch_cand(const MatchArgs& a, const OutArgs& o, bool fp32, bool many, hipStream_t s);
+void launch_cand(const MatchArgs& a, const OutArgs& o, bool fp32, hipStream_t s);
 // Re-decide the band list from the original coordinates: FP64 haversine,
 // then double-double inside the FP64 band.
 // source i at (ra[i stride], dec[i stride])

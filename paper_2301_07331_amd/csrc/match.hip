@@ -72,7 +72,7 @@ constexpr int MT = 256;     // threads per block
 constexpr int WAVES = MT / 64;
 constexpr int QCAP = 256;   // per-wave candidate queue, staged above QCAP - 64
 constexpr unsigned long long CAND_BLOCKS_MAX = 8192;  // grid cap of the certification walk
-constexpr uint32_t CAND_BLOCKS_MIN = 256;             // and its least: a block a CU
+constexpr uint32_t CAND_BLOCKS_MIN = 512;             // and its least
 
 // Thresholds of the eq. (4) radius of one pair (arcsec): chord^2 bounds of
 // the FP64 filter and the haversine band. r carries <= 3u from the sqrt and
@@ -815,7 +815,7 @@ void launch_filter(const MatchArgs& a, const OutArgs& o, bool fp32, int items_pe
   else k_filter<false, false><<<blocks, MT, 0, s>>>(a, o);
 }
 
-void launch_cand(const MatchArgs& a, const OutArgs& o, bool fp32, bool many, hipStream_t s) {
+void launch_cand(const MatchArgs& a, const OutArgs& o, bool fp32, hipStream_t s) {
   // one candidate per thread when the staging is full; the walk is
   // grid-stride beyond that
   const unsigned long long slots = (unsigned long long)NREG * o.reg.Sc;
@@ -823,12 +823,12 @@ void launch_cand(const MatchArgs& a, const OutArgs& o, bool fp32, bool many, hip
       CAND_BLOCKS_MAX, std::max(1ull, (slots + 256 * CAND_ITEMS - 1) / (256 * CAND_ITEMS)));
   // Up to 2M A entries each block makes the regions' prefix itself (2 us of
   // every block, against a launch of 5 us and its gap), in a grid for a few
-  // candidates an A entry: the staging of a small call is far larger (2,000 a
-  // side: 256 blocks cost as much as 64). Where the staging was made larger for
-  // counted candidates the grid follows it. 5,000 sources against 100,000, 967,000
-  // candidates: 533 us a call, 634 in 64 blocks; 2,000 against 4M, 3.1M candidates:
-  // 10.98 ms and 11.42.
-  if (o.direct && !many && a.na.cap <= (1u << 21)) {
+  // candidates an A entry, as the staging of a small call is far larger: two
+  // blocks a CU or more, which calls of many candidates an entry need (5,000 x
+  // 100,000, 967,000 candidates: 501 us a call, 634 in 64 blocks, 514 in 256; in
+  // 1,024, or in as many as the staging has grown to, small calls after it take 4 to
+  // 8 us longer; 2,000 a side 77 us in 512 and in 64).
+  if (o.direct && a.na.cap <= (1u << 21)) {
     blocks = std::min(blocks, std::max(CAND_BLOCKS_MIN, a.na.cap / 256u));
     if (fp32) k_cand<true, false, CAND_ITEMS, true><<<blocks, 256, 0, s>>>(a, o);
     else k_cand<false, false, CAND_ITEMS, true><<<blocks, 256, 0, s>>>(a, o);

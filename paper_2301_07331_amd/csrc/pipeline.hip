@@ -127,14 +127,11 @@ uint64_t stage_guess(uint64_t cap) {
   return std::min<uint64_t>(s, 1ull << 22);
 }
 
-// candidate slots a region before any are counted
-static uint64_t cand_estimate(uint64_t entries) { return std::min<uint64_t>(entries / (2 * NREG) + 4096, 1ull << 22); }
-
 Caps initial_caps(const Device& d, uint64_t entries, uint64_t cap, bool stage_cand, bool pair_regions) {
   Caps k;
   k.band = (1u << 20) + entries / 64;
   k.stage = pair_regions ? std::max(stage_guess(cap), d.hint_stage) : 0;
-  k.cand = stage_cand ? std::max(cand_estimate(entries), d.hint_cand) : 0;
+  k.cand = stage_cand ? std::max(std::min<uint64_t>(entries / (2 * NREG) + 4096, 1ull << 22), d.hint_cand) : 0;
   return k;
 }
 
@@ -253,7 +250,7 @@ void match(Device& dev, const Side& A, const Side& B, const Geom& g, double r_ar
   ma.hp_order = -1;
   launch_filter(ma, oa, fp32, filter_items, ts);
   if (prof) (void)hipEventRecord(dev.ev[9], ts);
-  launch_cand(ma, oa, fp32, w.reg.Sc > cand_estimate((uint64_t)A.n_cap + B.n_cap), ts);
+  launch_cand(ma, oa, fp32, ts);
   if (prof >= PROF_ALL) (void)hipEventRecord(dev.ev[10], ts);
   if (w.ahead.most) launch_pair_order_ahead(oa.pairs, oa.sep, cap, w.ahead_na, w.ahead, dev.cnt, ts);
   w.out = oa;
@@ -263,7 +260,7 @@ void match(Device& dev, const Side& A, const Side& B, const Geom& g, double r_ar
 // pairs; the bucket pass for up to PAIR_AHEAD_MAX pairs of up to 2M sources of
 // A. The host then waits once, not twice: 2k cones 83 us a call against
 // 101, 300k a side 189 against 202, 1.4M 270 against 290; a pass that finds nothing to
-// do costs its four launches, 12 us.
+// do costs its four launches, 12 us alone and 18 among a call's kernels.
 void carve_order_ahead(Carve& c, MatchWs& w, Device& dev, const hlc_opts* o, int64_t na, int64_t nb) {
   w.ahead = PairOrderAhead{};
   if (!(o->flags & HLC_SORTED) || prof_level(o->flags) || !dev.msg_dev || na > (int64_t(1) << 21)) return;

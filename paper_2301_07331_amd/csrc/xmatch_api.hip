@@ -105,14 +105,13 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
     HLC_TRY(hipEventRecord(dev->fork, s));
     // (a self-match's one keygen goes ahead of the sample: 4M, 442 us a call
     // before, 420; with two, A's would wait for the sample beside B's: no gain)
-    const bool ahead = self && !both;
-    if (ahead) partition_keys(*dev, b_ra, b_dec, nB, g, true, !fp32, fp32, sc, 2u, B, slB, s);
+    if (self) partition_keys(*dev, b_ra, b_dec, nB, g, true, !fp32, fp32, sc, 2u, B, slB, s);
     HLC_TRY(hipStreamWaitEvent(dev->side, dev->fork, 0));
     fq = frame_begin(*dev, a_ra, a_dec, na_frame, b_ra, b_dec, nb, crowd, dev->side);
     if (both) {
       partition_keys_both(*dev, a_ra, a_dec, nA, scA, A, b_ra, b_dec, nB, sc, B, g, s);
     } else {
-      if (!ahead) partition_keys(*dev, b_ra, b_dec, nB, g, true, !fp32, fp32, sc, 2u, B, slB, s);
+      if (!self) partition_keys(*dev, b_ra, b_dec, nB, g, true, !fp32, fp32, sc, 2u, B, slB, s);
       if (!self) partition_keys(*dev, a_ra, a_dec, nA, gA, false, !fp32, fp32, scA, 1u, A, slA, dev->side);
     }
   } else {
@@ -375,7 +374,7 @@ int hlc_xmatch_quad(const double* a_ra, const double* a_dec, int64_t na, const d
                                   (uint64_t)opts->capacity, w.band, w.band_cap, w.reg, dev->cnt);
       launch_regions_reset(oa, s);
       launch_filter(ma, oa, false, 1, s);
-      launch_cand(ma, oa, false, true, s);
+      launch_cand(ma, oa, false, s);
       launch_certify({a_ra, a_dec}, {b_ra, b_dec}, r_arcsec, th.H_lo, th.H_hi, Radii{nullptr, nullptr, 0.0}, oa, s);
       launch_compact(oa, s);
       HLC_CHECK(read_counters(*dev, s, false));
