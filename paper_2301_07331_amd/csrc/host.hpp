@@ -124,7 +124,7 @@ struct Device {
   bool last_full = true;  // the last call's frame was the whole sphere
   int large_partial = 0;  // calls of more than EXACT_FIRST_MAX sources since one whose frame was
   OverflowNotes overflows;
-  bool last_crowded = false;  // and its sources were crowded (what a speculative keygen assumes)
+  bool last_crowded = false;  // the sources of the last call that asked were crowded
   // mapped host memory: what kernels tell the host without a copy
   HostMsg* msg = nullptr;
   HostMsg* msg_dev = nullptr;  // its device address

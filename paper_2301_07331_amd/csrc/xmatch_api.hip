@@ -31,12 +31,15 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   const Slots slB = prof ? Slots{1, 2, 3, 4} : NO_SLOTS;
   const Slots slA = prof ? Slots{5, -1, 6, 7} : NO_SLOTS;
 
-  Geom g = make_geom(r_arcsec, tuned_height(o), na, nb, tuned_bins(o), Frame{}, dev->last_crowded);
-  // (set before A's speculative keygen: the number of radix passes decides
-  // which buffer that keygen writes)
   Side A, B;
   A.plan = plan_sort(na, caps.digit_sort);
   B.plan = plan_sort(nb, caps.digit_sort);
+  // what the speculative keygens assume of the crowding (calls that do not ask
+  // neither take it from the last that did nor change it for the next; set before
+  // A's: the number of radix passes decides which buffer that keygen writes)
+  const bool crowd = !B.plan.K && std::max(na, nb) >= CROWD_MIN;
+  const bool assumed = crowd && dev->last_crowded;
+  Geom g = make_geom(r_arcsec, tuned_height(o), na, nb, tuned_bins(o), Frame{}, assumed);
   // B's windows are cut at sub-bin resolution when its sort orders those bits
   // too: the bucket sort always does. A's digit sort orders them only where the
   // sources are crowded: its groups' windows take the least and largest of their
@@ -47,7 +50,7 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
     gA.frac_sorted = crowded || tuned_fraction_sort(o) ? 1 : 0;
     g.frac_sorted = B.plan.K || gA.frac_sorted ? 1 : 0;
   };
-  sub_bins(dev->last_crowded);
+  sub_bins(assumed);
   SortScratch sc, scA;
   MatchWs w;
   // FP32: B in the sorted certification layout when the last FP32 call on
@@ -91,7 +94,6 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   auto cleared = [&]() { return Cleared{dev->ws_bytes, {dev->ws, A.bws.fine, B.bws.fine, w.reg.cfill}}; };
   auto clear = [&]() { launch_zero_counters(dev->cnt, s, A.bws.fine, B.bws.fine, &w.reg); };
   Cleared early{};
-  const bool crowd = !B.plan.K && std::max(na, nb) >= CROWD_MIN;
   FrameQuery fq;
   if (spec) {
     Carve c{(char*)dev->ws};
@@ -128,11 +130,10 @@ int xmatch_impl(const double* a_ra, const double* a_dec, int64_t na, const doubl
   bool crowded = false;
   HLC_CHECK(frame_finish(*dev, fq, a_ra, a_dec, na_frame, b_ra, b_dec, nb, s, spec ? dev->side : s, &f, &crowded));
   dev->last_full = is_full(f);
-  const bool same_crowd = crowded == dev->last_crowded;
-  dev->last_crowded = crowded;
+  if (crowd) dev->last_crowded = crowded;
   g = make_geom(r_arcsec, tuned_height(o), na, nb, tuned_bins(o), f, crowded);
   sub_bins(crowded);
-  const bool keep = spec && dev->last_full && same_crowd;  // the speculative keys stand
+  const bool keep = spec && dev->last_full && crowded == assumed;  // the speculative keys stand
   Carve sizing{nullptr};
   lay(sizing);
   HLC_CHECK(ensure_ws(*dev, sizing.off + 256));
