@@ -232,6 +232,8 @@ __global__ void k_job_frames(const BatchJob* __restrict__ jobs, int32_t njobs,
   float Tf = (float)T;
   if ((double)Tf < T) Tf = __uint_as_float(__float_as_uint(Tf) + 1u);
   G.thr32 = Tf;
+  // (a window's density times the circle of r)
+  G.pair_scale = (float)(M_PI * G.r_deg * G.r_deg * G.bin_scale / (cmid * h));
   geo[j] = G;
 }
 
@@ -389,7 +391,7 @@ __global__ __launch_bounds__(HS_THREADS) void k_job_halo_scan(const uint32_t* __
 // layouts 1,350, the order alone 1,020, both together 1,530
 // (the call 6,100 us, 5,250, 4,650).
 template <uint32_t CAP, uint32_t T, bool FP32>
-__global__ __launch_bounds__(T, 4) void k_job_order(JobOrder o) {
+__global__ __launch_bounds__(T, CAP <= 1024 ? 5 : 4) void k_job_order(JobOrder o) {
   constexpr uint32_t PER = CAP / T, Q = CAP / 4;
   __shared__ __align__(16) OrderLds<CAP, T> L;
   __shared__ uint32_t s_n, s_less;
@@ -675,7 +677,7 @@ constexpr float HEAVY_PAIRS = 256.f;
 constexpr uint32_t HEAVY_BIT = 0x80000000u;  // in GroupRanges::count
 
 // per group of 16 A entries: B ranges (runs split by job and zone)
-__global__ __launch_bounds__(256) void k_batch_ranges(const uint32_t* __restrict__ keysA, DevCount nac,
+__global__ __launch_bounds__(256, 7) void k_batch_ranges(const uint32_t* __restrict__ keysA, DevCount nac,
                                                       const uint32_t* __restrict__ keysB,
                                                       const JobGeom* __restrict__ geo, int32_t lb_bits,
                                                       const int32_t* __restrict__ zmarg,
@@ -692,15 +694,10 @@ __global__ __launch_bounds__(256) void k_batch_ranges(const uint32_t* __restrict
   const uint32_t gn = min((uint32_t)GROUP, na - p0);
   RangeList L;
   L.clear();
-  uint32_t met = 0u;
-  auto add = [&](uint32_t a, uint32_t b) {
-    L.add(a, b);
-    met += b > a ? b - a : 0u;
-  };
-  float pairs = 0.f;  // expected of the group
+  auto add = [&](uint32_t a, uint32_t b) { L.add(a, b); };
+  float per_entry = 0.f;  // pairs expected of a source and B entry (the last zone's window)
   uint32_t q = 0;
   while (q < gn) {
-    met = 0u;
     const uint32_t k0 = keysA[p0 + q];
     const int32_t j = (int32_t)(k0 >> lb_bits);
     const JobGeom G = geo[j];
@@ -714,6 +711,7 @@ __global__ __launch_bounds__(256) void k_batch_ranges(const uint32_t* __restrict
     const int64_t bf = k0 & (G.nbins - 1), bl = keysA[p0 + qe] & (G.nbins - 1);
     const int32_t m = zmarg[G.zoff + z];
     const int64_t lo = bf - m, hi = bl + m;
+    per_entry = G.pair_scale / (float)(m < 0 ? (int32_t)G.nbins : (int32_t)(bl - bf) + 2 * m + 1);
     const uint32_t jz = (uint32_t)j << lb_bits | ((uint32_t)z << G.rb);
     // where bin b would be if the zone's entries lay evenly from the first to the
     // last: a few steps away (66 million entries: 221 us; 203 with the exact
@@ -737,10 +735,6 @@ __global__ __launch_bounds__(256) void k_batch_ranges(const uint32_t* __restrict
         add(s, e);
         if (lo < 0) add(gallop_lower_b(keysB, jz | (uint32_t)(nbins + lo), ze, zs, ze), ze);
       }
-      // the window's density times the circle of r
-      const float cd = sqrtf(fmaxf(1.f - (float)(G.cz * G.cz), 1e-4f)), r = (float)G.r_deg;
-      const float bins = (float)(m < 0 ? nbins : min(hi - lo + 1, nbins));
-      pairs += (float)(qe - q + 1u) * (float)met * 3.14f * r * r * (float)G.bin_scale / (bins * cd * (float)G.h_deg);
     }
     q = qe + 1;
   }
@@ -756,7 +750,7 @@ __global__ __launch_bounds__(256) void k_batch_ranges(const uint32_t* __restrict
   R.count = (uint32_t)n;
   R.pad_[0] = R.pad_[1] = R.pad_[2] = 0u;
   if (heavy) {
-    const bool h = pairs >= HEAVY_PAIRS;
+    const bool h = (float)gn * (float)work * per_entry >= HEAVY_PAIRS;
     const uint64_t m = __ballot(h);
     if (m) {
       const int first = (int)__builtin_ctzll(m);

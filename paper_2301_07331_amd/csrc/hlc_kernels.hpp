@@ -454,6 +454,7 @@ struct JobGeom {           // the job's local frame (computed on the device)
   double c_r, t_lo64, t_hi64, H_lo, H_hi;
   double cx, cy, cz;       // FP32 frame centre (snapped)
   float thr32;
+  float pair_scale;        // pairs expected of a source: a window's B entries / its bins * this
   int32_t nz, rb, full_ra;
   uint32_t nbins, zoff;
 };
