@@ -385,7 +385,8 @@ __global__ __launch_bounds__(HS_THREADS) void k_job_halo_scan(const uint32_t* __
 // after the sort fetches every (ra, dec) from a line of its own. Two blocks of
 // 512 threads a CU with the registers that the records want: four, with
 // spills, took 13 % longer, and blocks of 2,048 entries as much or up to 25 %
-// longer where jobs are large.
+// longer where jobs are large; five waves a SIMD for blocks of 1,024 entries
+// (10,000 jobs of 512: 702 us a call, 725 with the four that two registers more leave).
 // Bound by each block's chain of LDS steps and barriers. 10,000 cones of about
 // 3,300 sources a side: four digit passes of both sides 2,200 us and the
 // layouts 1,350, the order alone 1,020, both together 1,530
@@ -670,9 +671,9 @@ __device__ inline uint32_t gallop_upper_b(const uint32_t* keys, uint32_t K, uint
 // windows times the circle of r) is listed too, and the match takes the listed
 // groups first, spread over all waves: what a wave then finds takes it longer than
 // the tests do, and waves that meet several such groups ran on alone. 2,000 jobs
-// of 1,000, 50 of them 4,000 sources within 14 arcsec among the others: 821 us a
+// of 1,000, 50 of them 4,000 sources within 14 arcsec among the others: 814 us a
 // call, 1,164 without the list (838 from 64 pairs on, 891 from 1,024); 200 of 2,000
-// sources: 799 and 978; 10,000 ordinary cones: 3,172 and 3,208.
+// sources: 807 and 978; 10,000 ordinary cones: 3,194 and 3,258.
 constexpr float HEAVY_PAIRS = 256.f;
 constexpr uint32_t HEAVY_BIT = 0x80000000u;  // in GroupRanges::count
 
